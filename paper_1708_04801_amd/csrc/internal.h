@@ -83,6 +83,7 @@ struct Plan {
     int threads;     // workgroup size
     int ept;         // model elements per thread (DenseReg)
     int vec;         // elements per global load instruction
+    int align;       // elements the rows are aligned to (1, or 16 bytes' worth); vec may exceed it (DenseReg, rows = 1)
     int block_steps; // B
     int prefetch;    // P: rounds in flight
     int rows;        // DenseReg: 1 rows wait in registers, 2 next row staged in LDS, 3 rows streamed twice

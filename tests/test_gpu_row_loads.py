@@ -1,0 +1,52 @@
+"""Rows that are not 16-byte aligned: fp32 rows are fetched four dwords at a time whatever their length,
+stride and base, so what lies behind a row's last column must never reach the result."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import oracle as orc
+from paper_1708_04801_amd import api
+from paper_1708_04801_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+K_STEPS = np.array([130, 0, 1, 65, 64], dtype=np.int64)
+
+
+def _embedded(X, ld, shift):
+    """X as a view with row stride ld whose base lies `shift` elements behind a 256-byte boundary; NaN all around."""
+    m, d = X.shape
+    flat = torch.full((m * ld + shift + 8,), math.nan, dtype=torch.float32, device="cuda")
+    view = flat[shift:shift + m * ld].view(m, ld)[:, :d]
+    view.copy_(torch.from_numpy(X))
+    return flat, api.Matrix(m, d, dense=view)
+
+
+@pytest.mark.parametrize("d,ld,shift", [
+    (1, 1, 0), (3, 5, 1), (63, 63, 2), (65, 66, 3), (101, 101, 0), (254, 255, 1), (257, 257, 1), (515, 515, 2),
+    (1023, 1025, 3), (1297, 1297, 0), (2049, 2050, 1), (3001, 3001, 0), (4093, 4093, 1), (4095, 4096, 0), (8190, 8191, 2),
+    (16387, 16387, 1)])                                    # the last one: column slices
+@pytest.mark.parametrize("loss", [wl.HINGE, wl.LOGISTIC])
+def test_rows_at_any_dword(d, ld, shift, loss):
+    rng = np.random.default_rng(d * 3 + loss)
+    m = 128
+    X = (rng.standard_normal((m, d)) / math.sqrt(d)).astype(np.float32)
+    y = np.where(rng.random(m) < 0.5, 1.0, -1.0).astype(np.float32)
+    flat, Xg = _embedded(X, ld, shift)
+    yg = torch.from_numpy(y).cuda()
+    W = api.wpsgd_run_chains(Xg, yg, K_STEPS, 0.5, 1e-3, loss, 9)
+    ref = orc.run_chains(orc.Dense(X), y, K_STEPS, 0.5, 1e-3, loss, 9)
+    ref = ref[0] if isinstance(ref, tuple) else ref
+    got = W.cpu().numpy()
+    for i in range(len(K_STEPS)):
+        scale = max(np.linalg.norm(ref[i]), 1e-30)
+        assert np.linalg.norm(got[i] - ref[i]) <= 1e-4 * scale, (d, ld, shift, i)
+    # the objective reads rows and model with the same kind of load; its sums are fp64 (order of the sum only)
+    out = api.wpsgd_objective(Xg, yg, W[0].contiguous(), 1e-3, loss).cpu().numpy()
+    w = got[0].astype(np.float64)
+    z = y * (X.astype(np.float64) @ w)
+    l = np.maximum(0.0, 1.0 - z) if loss == wl.HINGE else np.logaddexp(0.0, -z)
+    assert abs(out[0] - (0.5e-3 * (w @ w) + l.mean())) <= 1e-11 * max(1.0, abs(out[0]))
+    assert abs(out[1] - (z <= 0).mean()) <= 1.0 / m
