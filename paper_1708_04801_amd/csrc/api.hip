@@ -144,7 +144,7 @@ static int resolve_plan(const wpsgd_matrix *X, int k, wpsgd_loss loss, const wps
     // which checks every step.
     const bool mild_shrink = rho >= 0.55;
     if (!f.state_in_hbm && mild_shrink) {
-        static const int kThreads[] = {64, 256, 512, 1024};
+        static const int kThreads[] = {64, 128, 256, 512, 1024};
         static const int kEpt[] = {1, 2, 4, 8, 16, 32, 64, 128};
         // smallest workgroup first, then the smallest fragment that covers d; fragments much
         // narrower than one wide load use scalar loads so that all lanes carry data
@@ -156,6 +156,9 @@ static int resolve_plan(const wpsgd_matrix *X, int k, wpsgd_loss loss, const wps
                 // the shape covers d, or one slice of it with no slice left empty
                 if ((int64_t)nt * ept * slices < X->d) continue;
                 if (slices > 1 && (int64_t)nt * ept * (slices - 1) >= X->d) break;
+                // bf16 rows of 513 to 1024 elements: with a compute unit to itself a chain is faster on two
+                // waves (0.204 us per step, fp64 state; one wave 0.222), beyond that on one (0.237 against 0.244)
+                if (nt == 64 && ept == 16 && !f.threads && k <= compute_units()) continue;
                 int vec = wide;
                 if (wide > 1 && ept * 4 <= wide) vec = 1;
                 if (ept % vec != 0) continue;
@@ -182,12 +185,16 @@ static int resolve_plan(const wpsgd_matrix *X, int k, wpsgd_loss loss, const wps
                     if (!q.block_steps) q.block_steps = 2;             // one exchange per two steps
                     if (q.block_steps > (p.loss == WPSGD_LOGISTIC ? 4 : 2)) continue;
                 }
-                // Few chains of 16 KiB fp32 rows, each alone on a compute unit, are bound by the
-                // latency of a step: two steps per reduction round (three sums instead of two, one
-                // exchange instead of two) are 8 % faster there.  With more chains than compute
-                // units the extra Gram products would only cost throughput.
-                if (!f.block_steps && !f.prefetch && !f.rows && nt == 256 && ept == 16 && vec == 4 &&
-                    p.loss == WPSGD_LOGISTIC && p.dtype == WPSGD_F32 && k <= compute_units()) {
+                // A workgroup of two or more waves with a compute unit (nearly) to itself is bound by the
+                // latency of a step: two steps per reduction round (three sums instead of two, one exchange
+                // instead of two) shorten it by 8 to 17 % (us per step, one -> two: fp32 hinge d = 1024
+                // 0.219 -> 0.183, d = 2048 0.246 -> 0.216, d = 4096 0.296 -> 0.267; logistic 0.179 -> 0.148,
+                // 0.199 -> 0.176, 0.238 -> 0.213; bf16 d = 2048 0.253 -> 0.223).  At two chains per compute unit the
+                // two are within 2 %; with more the extra Gram products only cost throughput.  Rows of
+                // 8192 elements (32 per thread) gained nothing.
+                const bool few = k <= 2 * compute_units() && slices == 1 && nt <= 256;
+                const bool few_sliced = k <= compute_units() && slices > 1 && p.loss == WPSGD_LOGISTIC && p.dtype == WPSGD_F32 && ept == 16;
+                if (!f.block_steps && !f.prefetch && !f.rows && nt >= 128 && ept <= 16 && (few || few_sliced)) {
                     Plan two = q;
                     two.block_steps = 2;
                     two.prefetch = 4;

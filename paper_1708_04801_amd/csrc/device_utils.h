@@ -260,6 +260,77 @@ __device__ inline T wave_sum(T v)
     return read_lane63(wave_sum_lane63(v));
 }
 
+// Two values per lane become one.  v_permlane32_swap exchanges the upper half of one register with the lower
+// half of another, v_permlane16_swap the odd rows of 16 lanes with the even ones: adding the two results
+// leaves each half (row) with one value's partial sums, at one swap per register and one addition.
+// merge_halves(a, b): lanes 0-31 hold a's sums, lanes 32-63 b's.  merge_rows(p, q): of each half's two rows
+// the even one holds p's sums, the odd one q's.
+__device__ inline void swap_halves(uint32_t &a, uint32_t &b)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+    a = r[0];
+    b = r[1];
+}
+__device__ inline void swap_rows(uint32_t &a, uint32_t &b)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+    a = r[0];
+    b = r[1];
+}
+template <bool ROWS>
+__device__ inline float merge_values(float a, float b)
+{
+    uint32_t x = __float_as_uint(a), y = __float_as_uint(b);
+    if constexpr (ROWS) swap_rows(x, y);
+    else swap_halves(x, y);
+    return __uint_as_float(x) + __uint_as_float(y);
+}
+template <bool ROWS>
+__device__ inline double merge_values(double a, double b)
+{
+    const uint64_t p = (uint64_t)__double_as_longlong(a), q = (uint64_t)__double_as_longlong(b);
+    uint32_t xl = (uint32_t)p, xh = (uint32_t)(p >> 32), yl = (uint32_t)q, yh = (uint32_t)(q >> 32);
+    if constexpr (ROWS) {
+        swap_rows(xl, yl);
+        swap_rows(xh, yh);
+    } else {
+        swap_halves(xl, yl);
+        swap_halves(xh, yh);
+    }
+    return __longlong_as_double((long long)(((uint64_t)xh << 32) | xl)) + __longlong_as_double((long long)(((uint64_t)yh << 32) | yl));
+}
+
+// Sums of N values over the 64 lanes, four values to a register: the total of v[4*q + r] ends up in all
+// lanes of row merged_row(r) of t[q].  Ten fp64 sums take 60 instructions this way and 180 one by one,
+// six dependent levels either way.
+__device__ __host__ constexpr int merged_row(int r) { return r == 1 ? 2 : (r == 2 ? 1 : r); }
+template <typename T, int N>
+__device__ inline void wave_sums_merged(const T (&v)[N], T (&t)[(N + 3) / 4])
+{
+    constexpr int Q = (N + 3) / 4;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const T a = v[4 * q], b = 4 * q + 1 < N ? v[4 * q + 1 < N ? 4 * q + 1 : 0] : a;
+        const T p = merge_values<false>(a, b);
+        T r = p;
+        if (4 * q + 2 < N) {
+            const T c = v[4 * q + 2 < N ? 4 * q + 2 : 0], e = 4 * q + 3 < N ? v[4 * q + 3 < N ? 4 * q + 3 : 0] : c;
+            r = merge_values<false>(c, e);
+        }
+        t[q] = merge_values<true>(p, r);
+    }
+    // all registers level by level, so that no level waits for the one before it
+    T moved[Q];
+#define WPSGD_LEVEL(CTRL)                                                   \
+    _Pragma("unroll") for (int q = 0; q < Q; ++q) moved[q] = dpp_move<CTRL, 0xF>(t[q]); \
+    _Pragma("unroll") for (int q = 0; q < Q; ++q) t[q] += moved[q];
+    WPSGD_LEVEL(0xB1)
+    WPSGD_LEVEL(0x4E)
+    WPSGD_LEVEL(0x141)
+    WPSGD_LEVEL(0x140)
+#undef WPSGD_LEVEL
+}
+
 // Wave-uniform read of lane j of a per-lane value.
 __device__ inline float lane_read(float t, int j)
 {

@@ -50,3 +50,21 @@ def test_rows_at_any_dword(d, ld, shift, loss):
     l = np.maximum(0.0, 1.0 - z) if loss == wl.HINGE else np.logaddexp(0.0, -z)
     assert abs(out[0] - (0.5e-3 * (w @ w) + l.mean())) <= 1e-11 * max(1.0, abs(out[0]))
     assert abs(out[1] - (z <= 0).mean()) <= 1.0 / m
+
+
+@pytest.mark.parametrize("d", [480, 501, 512, 520, 1000, 1001, 1024, 1032, 2001, 2048, 4001, 4096])
+@pytest.mark.parametrize("k", [5, 300])
+@pytest.mark.parametrize("loss", [wl.HINGE, wl.LOGISTIC])
+def test_bf16_rows_on_every_workgroup_size(d, k, loss):
+    """Few chains and many take different workgroup sizes and steps per round; both match the oracle."""
+    rng = np.random.default_rng(d * 5 + loss)
+    m = 96
+    bits = wl.f32_to_bf16_bits((rng.standard_normal((m, d)) / math.sqrt(d)).astype(np.float32))
+    y = np.where(rng.random(m) < 0.5, 1.0, -1.0).astype(np.float32)
+    n = np.resize(K_STEPS, k)
+    Xg = api.Matrix(m, d, dense=torch.from_numpy(bits.view(np.int16)).cuda().view(torch.bfloat16))
+    W = api.wpsgd_run_chains(Xg, torch.from_numpy(y).cuda(), n, 0.5, 1e-3, loss, 9).cpu().numpy()
+    ids = np.array([0, 1, 2, 3, 4, k - 1])
+    ref = orc.run_chains(orc.Dense(bits), y, n, 0.5, 1e-3, loss, 9, chain_ids=ids)[0]
+    for q, i in enumerate(ids):
+        assert np.linalg.norm(W[i] - ref[q]) <= 1e-4 * max(np.linalg.norm(ref[q]), 1e-30), (d, k, i)
