@@ -74,7 +74,8 @@ typedef struct wpsgd_matrix {
  * Used by the tests and the tuner to reach every kernel variant at any size.      */
 typedef struct wpsgd_plan {
     int threads;         /* workgroup size of a chain: 64, 128, 256, 512 or 1024 (dense); 64 or 192 (CSR)    */
-    int block_steps;     /* dense: SGD steps folded into one reduction round: 1, 2, 4 or 8              */
+    int block_steps;     /* dense: SGD steps folded into one reduction round: 1, 2 or 4; 16: blocks of
+                            sixteen steps prepared by three more waves (rows of 4 to 256 elements)    */
     int prefetch;        /* dense: rounds of sample rows kept in flight ahead of the one being consumed.
                             CSR: selects the kernel - 1 plain gather/scatter; 4 one wave per chain, hot
                             columns in LDS, cold model values fetched 4 steps ahead; 8 the same with two

@@ -34,6 +34,7 @@ UNITS = [
     ("combine", "combine.hip", []),
     ("objective", "objective.hip", []),
     ("chain_dense_mem", "chain_dense_mem.hip", []),
+    ("chain_dense_block", "chain_dense_block.hip", []),
     ("chain_delay", "chain_delay.hip", []),
     ("chain_csr", "chain_csr.hip", []),
     ("chain_csr_pair", "chain_csr_pair.hip", []),

@@ -230,6 +230,29 @@ static int resolve_plan(const wpsgd_matrix *X, int k, wpsgd_loss loss, const wps
                 }
             }
         }
+        // Short rows, chains few enough: sixteen steps per block, three more waves per chain.  The lines are where the
+        // one-wave kernel catches up, which runs more chains on a compute unit (us per step, one wave | blocks): d = 64
+        // hinge, 1024 chains 0.130 | 0.099, 2048 chains 0.145 | 0.164; d = 128, 1024 chains, hinge 0.157 | 0.161, logistic 0.123 |
+        // 0.107; d = 256 logistic, 256 chains 0.108 | 0.097, 512 chains 0.119 | 0.123.  fp32 hinge rows of more than 128
+        // elements gain nothing (0.135 | 0.132 with eight chains, 0.148 | 0.189 with 512).
+        const int64_t block_chains = X->d <= 64 ? 4 * compute_units()
+                                     : X->d <= 128 ? (loss == WPSGD_LOGISTIC ? 4 : 2) * compute_units()
+                                     : (loss == WPSGD_LOGISTIC || X->dtype == WPSGD_BF16) ? compute_units() : 0;
+        const bool block_shape = X->d >= kBlockMinColumns && X->d <= kBlockMaxColumns && (uintptr_t)X->dense % (X->dtype == WPSGD_BF16 ? 2 : 4) == 0;
+        const bool asked_block = f.block_steps == 16 && (!f.threads || f.threads == kWave) && !f.prefetch && !f.rows && f.slices <= 1;
+        if (block_shape && (asked_block || (have && !f.threads && !f.block_steps && !f.prefetch && !f.rows && f.slices <= 1 && k <= block_chains))) {
+            if (!have) found = p;
+            found.family = Family::DenseReg;
+            found.threads = kWave;
+            found.ept = X->d <= 64 ? 1 : (X->d <= 128 ? 2 : 4);
+            found.block_steps = 16;
+            found.prefetch = 2;
+            found.rows = 1;
+            found.slices = 1;
+            found.scouts = 3;
+            found.state_bytes_per_elem = 0;
+            have = true;
+        }
         if (have) {
             *out = found;
             return WPSGD_OK;
@@ -414,6 +437,7 @@ int wpsgd_describe_plan(const wpsgd_matrix *X, int k, wpsgd_loss loss, const wps
     const int hp = helpers_per_chain(p, X, k, plan);
     if (hp > 0) std::snprintf(helped, sizeof(helped), " helpers=%d", hp);
     if (p.family == Family::DenseReg && p.slices > 1) std::snprintf(helped, sizeof(helped), " slices=%d", p.slices);
+    if (p.scouts > 0) std::snprintf(helped, sizeof(helped), " scouts=%d", p.scouts);
     std::snprintf(buf, buf_bytes, "%s %s %s nt=%d ept=%d vec=%d B=%d P=%d state=%s%s%s",
                   family_name(p.family), p.dtype == WPSGD_BF16 ? "bf16" : "f32",
                   p.loss == WPSGD_HINGE ? "hinge" : "logistic", p.threads, p.ept, std::min(p.vec, p.align),
@@ -583,7 +607,7 @@ static int run_chains_from(const wpsgd_matrix *X, const float *y, int k, const i
         }
     } else {
         switch (p.family) {
-        case Family::DenseReg: e = dense_reg_dispatch(p, &a, s); break;
+        case Family::DenseReg: e = p.scouts > 0 ? launch_dense_block(p, a, s) : dense_reg_dispatch(p, &a, s); break;
         case Family::DenseMem: e = launch_dense_mem(p, a, s); break;
         default: e = launch_csr(p, a, s); break;
         }

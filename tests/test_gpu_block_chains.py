@@ -1,0 +1,76 @@
+"""Chains of short rows, sixteen steps per block: every way a row, a block or a window can end, against the oracle."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import oracle as orc
+from paper_1708_04801_amd import api
+from paper_1708_04801_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+BLOCK = {"block_steps": 16}
+STEPS = np.array([0, 1, 15, 16, 17, 47, 48, 63, 64, 65, 128, 300], dtype=np.int64)
+
+
+def _data(m, d, bf16, seed):
+    rng = np.random.default_rng(seed)
+    X = (rng.standard_normal((m, d)) / math.sqrt(d)).astype(np.float32)
+    y = np.where(rng.random(m) < 0.5, 1.0, -1.0).astype(np.float32)
+    if bf16:
+        bits = wl.f32_to_bf16_bits(X)
+        return bits, torch.from_numpy(bits.view(np.int16)).cuda().view(torch.bfloat16), y
+    return X, torch.from_numpy(X).cuda(), y
+
+
+def _compare(W, ref, tol):
+    for i in range(len(ref)):
+        assert np.linalg.norm(W[i] - ref[i]) <= tol * max(np.linalg.norm(ref[i]), 1e-30), i
+
+
+# fp64 state leaves the rounding of the result to fp32 (6e-8 an element); fp32 state some 300 roundings of it
+TOL = {wl.HINGE: 2e-7, wl.LOGISTIC: 2e-5}
+
+
+@pytest.mark.parametrize("d", [4, 5, 15, 16, 17, 31, 63, 64, 65, 98, 127, 128, 129, 191, 255, 256])
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("loss", [wl.HINGE, wl.LOGISTIC])
+def test_every_row_end_and_chain_end(d, bf16, loss):
+    host, dev, y = _data(200, d, bf16, d + 7 * loss)
+    X = api.Matrix(200, d, dense=dev)
+    yg = torch.from_numpy(y).cuda()
+    assert ("scouts=3" in api.wpsgd_describe_plan(X, len(STEPS), loss)) == (d <= 128 or bf16 or loss == wl.LOGISTIC)
+    W = api.wpsgd_run_chains(X, yg, STEPS, 0.5, 1e-3, loss, 9, plan=BLOCK)
+    ref = orc.run_chains(orc.Dense(host), y, STEPS, 0.5, 1e-3, loss, 9)[0]
+    _compare(W.cpu().numpy(), ref, TOL[loss])
+    assert torch.equal(W, api.wpsgd_run_chains(X, yg, STEPS, 0.5, 1e-3, loss, 9, plan=BLOCK))
+
+
+@pytest.mark.parametrize("loss", [wl.HINGE, wl.LOGISTIC])
+@pytest.mark.parametrize("sampling", [api.SAMPLE_STREAM, api.SAMPLE_SHARDS])
+def test_start_vector_offsets_and_shards(loss, sampling):
+    d, m = 77, 61                                 # shares of five or six rows: a block runs round them several times
+    host, dev, y = _data(m, d, False, 5)
+    X, yg = api.Matrix(m, d, dense=dev), torch.from_numpy(y).cuda()
+    w0 = torch.linspace(-1.0, 1.0, d, device="cuda")
+    off = np.arange(len(STEPS), dtype=np.int64) * 37
+    W = api.wpsgd_run_chains_from(X, yg, STEPS, 0.3, 1e-2, loss, 3, w_start=w0, step_offsets=off, sampling=sampling, plan=BLOCK)
+    other = api.wpsgd_run_chains_from(X, yg, STEPS, 0.3, 1e-2, loss, 3, w_start=w0, step_offsets=off, sampling=sampling,
+                                      plan={"threads": 64, "block_steps": 1, "prefetch": 8})
+    _compare(W.cpu().numpy(), other.cpu().numpy().astype(np.float64), TOL[loss])
+    assert torch.equal(W[0], w0)
+
+
+@pytest.mark.parametrize("loss", [wl.HINGE, wl.LOGISTIC])
+def test_scale_is_folded_and_many_chains_run(loss):
+    """eta*lambda = 0.4: the scale falls below 2^-30 within a window.  900 chains: several to a compute unit."""
+    d, k = 130, 900
+    host, dev, y = _data(64, d, False, 8)
+    n = np.resize(STEPS, k)
+    X, yg = api.Matrix(64, d, dense=dev), torch.from_numpy(y).cuda()
+    W = api.wpsgd_run_chains(X, yg, n, 0.8, 0.5, loss, 4, plan=BLOCK).cpu().numpy()
+    ref = orc.run_chains(orc.Dense(host), y, n, 0.8, 0.5, loss, 4, chain_ids=np.arange(24))[0]
+    _compare(W[:24], ref, TOL[loss])
+    _compare(W[-12:], orc.run_chains(orc.Dense(host), y, n, 0.8, 0.5, loss, 4, chain_ids=np.arange(k - 12, k))[0], TOL[loss])
