@@ -686,7 +686,7 @@ int wpsgd_run_delay_chains(const wpsgd_matrix *X, const float *y, int k, const i
                       : nullptr;
     const bool start_ok = !w_start || (uintptr_t)w_start % 4 == 0;
     if (!start_ok) return WPSGD_INVALID_ARG;
-    hipError_t e = launch_delay_servers(a, (int)X->dtype, dense_vec(X), s);
+    hipError_t e = launch_delay_servers(a, (int)X->dtype, dense_vec(X), buffer_vec(X), s);
     return e == hipSuccess ? WPSGD_OK : hip_fail(e);
 }
 

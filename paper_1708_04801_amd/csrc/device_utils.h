@@ -138,6 +138,17 @@ struct RowWindow {
         }
         return (uint32_t)__builtin_amdgcn_readlane((int)rows, (int)(step & (kWave - 1)));
     }
+    // the with-replacement stream, its sampler in line: a call in a loop keeps the caller's registers
+    // where the calling convention wants them, which costs moves all around it
+    __device__ uint32_t get_stream(int64_t step)
+    {
+        const int64_t b = step & ~(int64_t)(kWave - 1);
+        if (b != base) {
+            base = b;
+            rows = sample_row(seed_lo, seed_hi, chain, (uint64_t)(b + (int)(threadIdx.x & (kWave - 1))), m);
+        }
+        return (uint32_t)__builtin_amdgcn_readlane((int)rows, (int)(step & (kWave - 1)));
+    }
 };
 
 // ---------------------------------------------------------------------------------------------

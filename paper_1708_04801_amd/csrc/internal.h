@@ -102,7 +102,8 @@ hipError_t launch_csr(const Plan &p, const ChainArgs &a, hipStream_t s);
 hipError_t launch_csr_pair(const Plan &p, const ChainArgs &a, hipStream_t s);   // two waves per chain
 bool dense_reg_has(const Plan &p);   // is (dtype, loss, threads, ept, vec, B, P) instantiated?
 
-hipError_t launch_delay_servers(const DelayArgs &a, int dtype, int vec, hipStream_t s);
+// vec: elements per load where rows are whole 16-byte pieces, else 1; buffer_vec: elements per raw buffer load
+hipError_t launch_delay_servers(const DelayArgs &a, int dtype, int vec, int buffer_vec, hipStream_t s);
 hipError_t launch_zero_words(uint32_t *p, size_t words, hipStream_t s);
 hipError_t launch_combine(const float *W, const double *a_dev, int k, int64_t d, float *w_out,
                           hipStream_t s);

@@ -68,3 +68,23 @@ def test_bf16_rows_on_every_workgroup_size(d, k, loss):
     ref = orc.run_chains(orc.Dense(bits), y, n, 0.5, 1e-3, loss, 9, chain_ids=ids)[0]
     for q, i in enumerate(ids):
         assert np.linalg.norm(W[i] - ref[q]) <= 1e-4 * max(np.linalg.norm(ref[q]), 1e-30), (d, k, i)
+
+
+@pytest.mark.parametrize("d", [50, 333, 542, 1023, 2047, 4095])
+@pytest.mark.parametrize("tau", [0, 1, 4])
+@pytest.mark.parametrize("check", [True, False])
+def test_delay_servers_on_rows_at_any_dword(d, tau, check):
+    """fp32 rows without 16-byte alignment take the register kernel of the servers; NaN around the rows shows a
+    column too many.  fp64 state: only the rounding of W is left (6e-8 an element)."""
+    w = wl.delay_servers(m=150, d=d, k=5, n_lo=1, n_hi=60)
+    flat, Xg = _embedded(w.dense, d + 2, 1)
+    Wg, acc = api.wpsgd_run_delay_chains(Xg, torch.from_numpy(w.y).cuda(), w.n_steps, w.eta, w.lam, w.loss, w.seed, tau, check=check,
+                                         w_start=torch.from_numpy(w.meta["w_start"]).cuda())
+    for i in range(w.k):
+        idx = orc.sample_indices(w.seed, i, 0, int(w.n_steps[i]), w.m)
+        ref, acc_o, gap = orc.delay_sgd(orc.Dense(w.dense), w.y, idx, w.eta, w.lam, w.loss, tau,
+                                        w0=w.meta["w_start"].astype(np.float64), check=check)
+        if gap < 1e-12:
+            continue
+        assert int(acc[i]) == acc_o, (d, tau, check, i)
+        assert np.linalg.norm(Wg[i].cpu().numpy() - ref) <= 2e-7 * np.linalg.norm(ref)
