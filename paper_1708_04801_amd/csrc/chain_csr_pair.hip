@@ -1,4 +1,5 @@
-// Sparse-row (CSR) SGD chains, three wavefronts per chain.
+// Sparse-row (CSR) SGD chains, three wavefronts per chain.  (Matrices whose rows have at most 16 entries
+// run four steps at a time instead: chain_csr_short.h.)
 //
 // A step of a sparse chain is a short dependent recursion (gather the model at the row's columns,
 // reduce, decide, scatter), and one wavefront issues one instruction at a time: with a single
@@ -168,13 +169,21 @@ __device__ inline void store_state(__amdgpu_buffer_rsrc_t r, uint32_t off, float
 __device__ inline uint32_t stamp_slot_a(uint32_t col) { return col & (kPStamps - 1); }
 __device__ inline uint32_t stamp_slot_b(uint32_t col) { return (col + (col >> 13) * 2731u) & (kPStamps - 1); }
 
+}  // namespace
+}  // namespace wpsgd
+
+#include "chain_csr_short.h"
+
+namespace wpsgd {
+namespace {
+
 template <int LOSS>
 __global__ __launch_bounds__(kPairThreads) void chain_csr_pair_kernel(ChainArgs a)
 {
     using TV = typename StateType<LOSS>::type;
     using L = Lds<TV>;
-    static_assert(L::bytes <= 160 * 1024, "LDS block too large");
-    __shared__ __attribute__((aligned(16))) char lds[L::bytes];
+    static_assert(L::bytes <= 160 * 1024 && ShortLds<TV>::bytes <= 160 * 1024, "LDS block too large");
+    __shared__ __attribute__((aligned(16))) char lds[L::bytes > ShortLds<TV>::bytes ? L::bytes : ShortLds<TV>::bytes];
 
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1);
@@ -192,6 +201,21 @@ __global__ __launch_bounds__(kPairThreads) void chain_csr_pair_kernel(ChainArgs 
     // then only shrinks the vector), has nothing to do here.
     if (nnz == 0 || n == 0) return;
     TV *head = reinterpret_cast<TV *>(lds + L::head);
+    if (rows_are_short(a)) {                         // four steps at a time: chain_csr_short.h
+        using S = ShortLds<TV>;
+        static_assert(S::head == L::head, "both keep the same columns at the same place");
+        for (int c = tid; c < kPHead + kWave; c += kPairThreads)
+            head[c] = (a.w_start && c < kPHead && c < d) ? (TV)a.w_start[c] : (TV)0;
+        for (int c = tid; c < 2 * (kPStamps + kWave); c += kPairThreads) reinterpret_cast<uint16_t *>(lds + S::stamp_a)[c] = 0;
+        __syncthreads();
+        constexpr int kSteps = kG * kShortRows;      // steps per section
+        const int64_t nsections = (n + kSteps - 1) / kSteps;
+        if (wave == 0) short_worker<LOSS, TV>(a, lds, v, nsections);
+        else short_scout<LOSS, TV>(a, lds, chain, n, step0, nsections, wave == 2);
+        __syncthreads();
+        for (int c = tid; c < kPHead && c < d; c += kPairThreads) v[c] = head[c];
+        return;
+    }
     for (int c = tid; c < kPHead + kSlots; c += kPairThreads)                             // values and scratch slots
         head[c] = (a.w_start && c < kPHead && c < d) ? (TV)a.w_start[c] : (TV)0;
     for (int c = tid; c < 2 * (kPStamps + kSlots); c += kPairThreads) reinterpret_cast<uint16_t *>(lds + L::stamp_a)[c] = 0;

@@ -1,0 +1,335 @@
+// Sparse chains whose rows are short (at most 16 entries, nearly all of them): four steps at a time, one row of
+// 16 lanes each.
+//
+// A short row leaves most of a wave idle, and two short rows of a wide matrix seldom share a column.  Steps
+// whose rows share none are independent of each other but for the shrink, which the per-step scalars carry:
+// their products, slopes and updates can be taken side by side with the results of one step after the
+// other.  A group is four consecutive steps; lane 16*r + e holds entry e of the row of its step r.
+//
+// The waves and the ring are those of chain_csr_pair_kernel with a group in the place of a step: the record scout
+// writes 64 records and four steps' scalars per group, the stamp scout marks
+//   stale      groups whose HBM-resident values were fetched before one of the last 2*kShortAhead groups wrote them,
+//   in turn    groups in which two rows share a column (or a slot of the table that finds them: every lane
+//              writes its number to the slot of its column and reads the slot back; of two lanes with one
+//              column at most one finds its own number), or in which a row is longer than 16 entries.
+// The worker takes a group in turn step by step, reading every value when its step comes.  The steps after a long
+// row re-read their values, since its columns leave no stamps.
+//
+// What bounds it: some 510 cycles a group, much the same with fp64 and with fp32 state: the scouts' LDS and load
+// traffic beside the worker's dependent chain (LDS read, product, four levels of a sum over 16 lanes, slope, LDS write);
+// groups that re-read or run in turn add an eighth.  Ten chains of up to 100000 steps, rows of 5 to 10 entries, d = 100000:
+// 0.213 us per step one at a time, 0.060 this way (21.3 -> 6.0 ms).  Requests six groups ahead instead of four: 0.077
+// against 0.076 in an earlier form.
+#pragma once
+
+namespace wpsgd {
+namespace {
+
+constexpr int kShortLen = 16;                // entries per row of lanes
+constexpr int kShortRows = 4;                // steps per group
+constexpr int kShortLead = 2 * kG;           // scouts: groups between a row's request and its records: one window of 64 steps
+static_assert(kShortLead * kShortRows == kWave, "one window ahead: requests read the next window's tables");
+constexpr uint32_t kShortScalars = 32;       // bytes per step: StepScalars, StepRow
+constexpr uint32_t kGroupBytes = kWave * 16 + kShortRows * kShortScalars;
+constexpr uint32_t kShortSectionBytes = kG * kGroupBytes;
+constexpr int kShortAhead = 4;               // worker: HBM-resident values are requested this many groups ahead
+constexpr uint16_t kShortRecent = 2 * kShortAhead;
+static_assert(kShortAhead + 1 < kG, "record and value rings are indexed modulo kG");
+constexpr int kStale = 1, kInTurn = 2;       // marks of a group, in the pad of its first StepRow
+
+constexpr int kOwners = 16384;               // slots of the table that finds shared columns
+struct __attribute__((aligned(16))) RowToRequest {
+    int64_t lo;           // first entry (1 for a row without entries: its lanes request entry 0 and drop it)
+    int32_t len, pad;
+};
+
+template <typename TV>
+struct ShortLds {
+    static constexpr uint32_t head = 0;                                           // kPHead model values, then one scratch slot per lane
+    static constexpr uint32_t head_scratch = head + kPHead * sizeof(TV);
+    static constexpr uint32_t stamp_a = head_scratch + kWave * sizeof(TV);        // kPStamps + scratch slots
+    static constexpr uint32_t stamp_b = stamp_a + (kPStamps + kWave) * 2;
+    static constexpr uint32_t owner = stamp_b + (kPStamps + kWave) * 2;           // which lane of a group holds a column
+    static constexpr uint32_t rows = (owner + (kOwners + kWave) + 15u) & ~15u;    // per scout, 64 rows to request: RowToRequest
+    static constexpr uint32_t ring = rows + 2 * kWave * 16;
+    static constexpr uint32_t bytes = ring + kSections * kShortSectionBytes;
+};
+
+// Are the matrix's rows short?  768 rows spread over it are looked at (the same ones by every workgroup); if hardly any
+// is longer than 16 entries the answer is yes.  Either answer gives correct results.
+__device__ inline bool rows_are_short(const ChainArgs &a)
+{
+    constexpr int kLook = 768;
+    int too_long = 0;
+    for (int i = (int)threadIdx.x; i < kLook; i += kPairThreads) {
+        const int64_t row = (int64_t)((uint64_t)i * (uint64_t)a.m / kLook);
+        too_long |= a.row_ptr[row + 1] - a.row_ptr[row] > kShortLen;
+    }
+    return __syncthreads_count(too_long) <= 1;
+}
+
+template <int LOSS, typename TV>
+__device__ inline void short_scout(const ChainArgs &a, char *lds, int chain, int64_t n, int64_t step0, int64_t nsections, bool marks)
+{
+    using L = ShortLds<TV>;
+    const int lane = (int)(threadIdx.x & (kWave - 1)), r = lane / kShortLen, e = lane % kShortLen;
+    const double rho = a.rho, inv_rho = 1.0 / rho;
+    const double rho64 = a.pow_tab[kWave - 1] * rho, inv_rho64 = a.pow_tab[2 * kWave - 1];
+    const double rho_pow = a.pow_tab[lane], inv_rho_pow1 = a.pow_tab[kWave + lane];
+    double s_w = 1.0, eos_w = a.eta;
+    // per lane: the row of step (window start + lane), for the window being written (A), the next (B) and the one after (C)
+    // (as loaded: a difference taken here would wait for the loads, and with them for every row on its way)
+    struct Window { int64_t lo, end; float y; };
+    auto load_window = [&](int64_t w) {
+        const uint64_t step = (uint64_t)(step0 + w * kWave + lane);
+        const uint32_t row = a.perm ? a.perm[shard_position((uint32_t)chain, (uint32_t)a.k, step, (uint32_t)a.m)]
+                                    : sample_row(a.seed_lo, a.seed_hi, (uint32_t)chain, step, (uint32_t)a.m);
+        Window t;
+        t.lo = a.row_ptr[row];
+        t.end = a.row_ptr[(int64_t)row + 1];
+        t.y = a.y[row];
+        return t;
+    };
+    Window A = load_window(0), B = load_window(1), C = load_window(2);
+
+    auto run = [&](auto role_tag) {
+        constexpr bool MARKS = decltype(role_tag)::value;
+        uint32_t er_col[kShortLead];
+        float er_val[kShortLead];
+        int er_len[kShortLead];
+        // The rows to request pass through LDS once per window, so that a group costs one 16-byte read at a fixed place
+        // (three exchanges between lanes per group had made the scouts the slowest waves: 0.076 us per step against 0.066).
+        RowToRequest *const rows = reinterpret_cast<RowToRequest *>(lds + L::rows) + (MARKS ? kWave : 0);
+        auto announce = [&](const Window &t) {
+            RowToRequest q;
+            q.len = (int)(t.end - t.lo);
+            q.lo = q.len > 0 ? t.lo : 1;
+            q.pad = 0;
+            rows[lane] = q;
+        };
+        // entry e of the row of step 4*u + r of the window announced last
+        auto request = [&](int u, const RowToRequest &q) {
+            const int64_t at = q.lo + (e < q.len ? e : q.len - 1);
+            er_len[u] = q.len;
+            er_col[u] = (uint32_t)a.col_idx[at];
+            if constexpr (!MARKS) er_val[u] = a.vals[at];
+        };
+        announce(A);
+#pragma unroll
+        for (int u = 0; u < kShortLead; ++u) request(u, rows[kShortRows * u + r]);
+        __builtin_amdgcn_s_waitcnt(0x0F70);      // enter the loop with an empty queue
+        StepScalars<TV> sc_tab;
+        int64_t redo_until = -1;                 // (marks) groups up to this one re-read their values: they follow a long row
+        struct { bool tail, real, forced; uint16_t now, sa, sb; uint8_t who; bool in_turn; char *pad; } prev;
+        prev.pad = nullptr;
+        auto settle = [&]() {                    // the verdict on a group, when its table reads have arrived
+            const bool stale = __any(prev.tail & ((uint16_t)(prev.now - prev.sa) < kShortRecent) & ((uint16_t)(prev.now - prev.sb) < kShortRecent)) | prev.forced;
+            const bool shared = __any(prev.real & ((int)prev.who / kShortLen != r)) | prev.in_turn;
+            if (lane == 0) *reinterpret_cast<int32_t *>(prev.pad) = (stale ? kStale : 0) | (shared ? kInTurn : 0);
+        };
+
+        // one section: groups kG*i .. kG*i + kG-1, HALF = i & 1 of the window
+        auto write_section = [&](int64_t i, auto half_tag) {
+            constexpr int HALF = decltype(half_tag)::value;
+            const int64_t w = i / 2;
+            if constexpr (HALF == 0) {
+                if (w > 0) {
+                    s_w *= rho64;
+                    eos_w *= inv_rho64;
+                    A = B;
+                    B = C;
+                    C = load_window(w + 2);
+                }
+                announce(B);
+                if constexpr (!MARKS) {
+                    const double yd = (double)A.y;
+                    const double sl = yd * s_w * rho_pow, el = yd * eos_w * inv_rho_pow1;
+                    const bool live = w * kWave + lane < n;
+                    if constexpr (LOSS == kLossHinge) {
+                        sc_tab.zs = sl;
+                        sc_tab.cs = live ? el : 0.0;
+                    } else {
+                        sc_tab.zs = (float)(sl * 1.4426950408889634);
+                        sc_tab.cs = live ? (float)el : 0.0f;
+                    }
+                }
+            }
+            RowToRequest ask[kG];                // the rows this section requests, read at once
+#pragma unroll
+            for (int u = 0; u < kG; ++u) ask[u] = rows[kShortRows * (HALF * kG + u) + r];
+            char *sec = lds + L::ring + (uint32_t)(i % kSections) * kShortSectionBytes;
+            if constexpr (!MARKS) {              // the lanes that hold this section's 32 steps publish their scalars
+                if (lane / 32 == HALF) {
+                    const int t = lane % 32;
+                    char *h = sec + (t / kShortRows) * kGroupBytes + kWave * 16 + (t % kShortRows) * kShortScalars;
+                    *reinterpret_cast<StepScalars<TV> *>(h) = sc_tab;
+                    reinterpret_cast<StepRow *>(h + 16)->lo = A.lo;
+                    reinterpret_cast<StepRow *>(h + 16)->len = (int)(A.end - A.lo);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < kG; ++u) {
+                const int slot = HALF * kG + u;
+                const int len = er_len[slot];
+                const uint32_t col = er_col[slot];
+                const bool in = e < len, tail = in && col >= (uint32_t)kPHead;
+                if constexpr (MARKS) {
+                    const int64_t grp = i * kG + u;
+                    const uint16_t now = (uint16_t)grp;
+                    uint16_t *const pa = reinterpret_cast<uint16_t *>(lds + L::stamp_a) + (tail ? stamp_slot_a(col) : (uint32_t)(kPStamps + lane));
+                    uint16_t *const pb = reinterpret_cast<uint16_t *>(lds + L::stamp_b) + (tail ? stamp_slot_b(col) : (uint32_t)(kPStamps + lane));
+                    uint8_t *const po = reinterpret_cast<uint8_t *>(lds + L::owner) + (in ? col & (kOwners - 1) : (uint32_t)(kOwners + lane));
+                    const uint16_t sa = *pa, sb = *pb;
+                    *pa = now;
+                    *pb = now;
+                    *po = (uint8_t)lane;
+                    asm volatile("" ::: "memory");          // the slot is read back after all lanes have written (one wave's LDS accesses keep their order)
+                    const uint8_t who = *po;
+                    const bool has_long = __any(len > kShortLen);
+                    if (has_long) redo_until = grp + kShortRecent - 1;
+                    const bool forced = grp <= redo_until;
+                    if (u > 0) settle();         // (a section's last group is settled before its barrier)
+                    prev.tail = tail; prev.real = in; prev.forced = forced; prev.now = now; prev.sa = sa; prev.sb = sb; prev.who = who;
+                    prev.in_turn = has_long;
+                    prev.pad = sec + u * kGroupBytes + kWave * 16 + 16 + offsetof(StepRow, pad);
+                    if (u == kG - 1) settle();
+                } else {
+                    pu32x4 rec;
+                    rec[0] = in ? __float_as_uint(er_val[slot]) : 0u;
+                    rec[1] = in && !tail ? L::head + col * (uint32_t)sizeof(TV) : L::head_scratch + lane * (uint32_t)sizeof(TV);
+                    rec[2] = tail ? col * (uint32_t)sizeof(TV) : 0xFFFFFFF0u;        // (past the end of the vector: no access)
+                    rec[3] = tail ? 0x80000000u : 0u;
+                    *reinterpret_cast<pu32x4 *>(sec + u * kGroupBytes + lane * 16) = rec;
+                }
+                request(slot, ask[u]);
+            }
+        };
+        for (int64_t i = 0; i <= nsections; i += 2) {
+            write_section(i, std::integral_constant<int, 0>{});
+            wait_lds_then_barrier();
+            if (i + 1 <= nsections) {
+                write_section(i + 1, std::integral_constant<int, 1>{});
+                wait_lds_then_barrier();
+            }
+        }
+    };
+    if (marks) run(std::true_type{});
+    else run(std::false_type{});
+}
+
+template <int LOSS, typename TV>
+__device__ inline TV short_coefficient(const StepScalars<TV> &sc, TV dot)
+{
+    if constexpr (LOSS == kLossHinge) return sc.zs * dot < 1.0 ? sc.cs : 0.0;
+    else return sc.cs * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(sc.zs * dot));
+}
+
+// sum over a row of 16 lanes, in every lane of it
+template <typename TV>
+__device__ inline TV row_sum(TV v)
+{
+    v += dpp_move<0xB1, 0xF>(v);
+    v += dpp_move<0x4E, 0xF>(v);
+    v += dpp_move<0x141, 0xF>(v);
+    v += dpp_move<0x140, 0xF>(v);
+    return v;
+}
+
+template <int LOSS, typename TV>
+__device__ inline void short_worker(const ChainArgs &a, char *lds, TV *v, int64_t nsections)
+{
+    using L = ShortLds<TV>;
+    const int lane = (int)(threadIdx.x & (kWave - 1)), r = lane / kShortLen;
+    const uint32_t v_bytes = (uint32_t)(a.d * (int64_t)sizeof(TV));
+    const __amdgpu_buffer_rsrc_t vres = __builtin_amdgcn_make_buffer_rsrc(v, 0, (int)v_bytes, 0x00020000);
+    const pu32x4 vdesc = descriptor(v, v_bytes);
+    TV *head = reinterpret_cast<TV *>(lds + L::head);
+    pu32x4 rec[kG];
+    TV vr[kG];
+    StepScalars<TV> scr[kG];
+    int markr[kG];
+    const char *ring = lds + L::ring;
+    auto fetch = [&](int q, const char *group) {
+        rec[q] = *reinterpret_cast<const pu32x4 *>(group + lane * 16);
+        scr[q] = *reinterpret_cast<const StepScalars<TV> *>(group + kWave * 16 + r * kShortScalars);
+        markr[q] = reinterpret_cast<const StepRow *>(group + kWave * 16 + 16)->pad;
+    };
+    wait_lds_then_barrier();          // section 0 written
+    wait_lds_then_barrier();          // section 1 written
+#pragma unroll
+    for (int q = 0; q <= kShortAhead; ++q) fetch(q, ring + q * kGroupBytes);
+#pragma unroll
+    for (int q = 0; q < kShortAhead; ++q) vr[q] = load_state(vres, rec[q][2], TV{});
+    __builtin_amdgcn_s_waitcnt(0x0F70);      // enter the loop with an empty queue
+
+    for (int64_t g = 0; g < nsections; ++g) {
+        if (g > 0) wait_lds_then_barrier();  // section g+1 written
+        const char *cur = ring + (uint32_t)(g % kSections) * kShortSectionBytes;
+        const char *nxt = ring + (uint32_t)((g + 1) % kSections) * kShortSectionBytes;
+#pragma unroll
+        for (int u = 0; u < kG; ++u) {
+            const TV hv = *reinterpret_cast<const TV *>(lds + rec[u][1]);
+            fetch((u + kShortAhead + 1) % kG, (u + kShortAhead + 1 < kG ? cur : nxt) + ((u + kShortAhead + 1) % kG) * kGroupBytes);
+            const bool tail = (int32_t)rec[u][3] < 0;
+            const TV val = (TV)__uint_as_float(rec[u][0]);
+            TV vv = tail ? vr[u] : hv;
+            const int marks = __builtin_amdgcn_readfirstlane(markr[u]);
+            if (__builtin_expect((marks & kInTurn) == 0, 1)) {
+                if (__builtin_expect(marks != 0, 0)) {
+                    const TV fresh = drained_buffer_load(vdesc, rec[u][2], TV{});
+                    if (tail) vv = fresh;
+                }
+                const TV coef = short_coefficient<LOSS, TV>(scr[u], row_sum(vv * val));
+                const TV nv = vv + coef * val;
+                *reinterpret_cast<TV *>(lds + rec[u][1]) = nv;
+                store_state(vres, rec[u][2], nv);
+            } else {
+                const bool far = __any(tail);    // (no HBM-resident column in the group: its short rows leave the queue alone)
+#pragma unroll 1
+                for (int t = 0; t < kShortRows; ++t) {          // step by step, each value read when its step comes
+                    const StepRow row = *reinterpret_cast<const StepRow *>(cur + u * kGroupBytes + kWave * 16 + t * kShortScalars + 16);
+                    const StepScalars<TV> sc = *reinterpret_cast<const StepScalars<TV> *>(cur + u * kGroupBytes + kWave * 16 + t * kShortScalars);
+                    const int len = __builtin_amdgcn_readfirstlane(row.len);
+                    if (len <= kShortLen) {
+                        const uint32_t off = r == t ? rec[u][2] : 0xFFFFFFF0u;
+                        TV now = *reinterpret_cast<const TV *>(lds + rec[u][1]);
+                        if (far) {
+                            const TV fresh = drained_buffer_load(vdesc, off, TV{});
+                            if (tail) now = fresh;
+                        }
+                        const TV nv = now + short_coefficient<LOSS, TV>(sc, row_sum(now * val)) * val;
+                        if (r == t) *reinterpret_cast<TV *>(lds + rec[u][1]) = nv;
+                        if (far) drained_buffer_store(vdesc, off, nv);
+                    } else {
+                        TV acc = (TV)0;
+                        for (int e0 = 0; e0 < len; e0 += kWave) {
+                            const bool in = e0 + lane < len;
+                            const uint32_t xc = drained_global_load_u32(a.col_idx + (in ? row.lo + e0 + lane : row.lo));
+                            const float xv = __uint_as_float(drained_global_load_u32(a.vals + (in ? row.lo + e0 + lane : row.lo)));
+                            const bool hd = xc < (uint32_t)kPHead;
+                            const TV old = drained_buffer_load(vdesc, in && !hd ? xc * (uint32_t)sizeof(TV) : 0xFFFFFFF0u, TV{});
+                            if (in) acc += (hd ? head[xc] : old) * (TV)xv;
+                        }
+                        const TV coef = short_coefficient<LOSS, TV>(sc, wave_sum(acc));
+                        for (int e0 = 0; e0 < len; e0 += kWave) {
+                            const bool in = e0 + lane < len;
+                            const uint32_t xc = drained_global_load_u32(a.col_idx + (in ? row.lo + e0 + lane : row.lo));
+                            const float xv = __uint_as_float(drained_global_load_u32(a.vals + (in ? row.lo + e0 + lane : row.lo)));
+                            const bool hd = xc < (uint32_t)kPHead;
+                            const uint32_t off = in && !hd ? xc * (uint32_t)sizeof(TV) : 0xFFFFFFF0u;
+                            const TV old = drained_buffer_load(vdesc, off, TV{});
+                            if (in && hd) head[xc] += coef * (TV)xv;
+                            drained_buffer_store(vdesc, off, old + coef * (TV)xv);
+                        }
+                    }
+                }
+            }
+            // HBM-resident values of group u + kShortAhead (its records arrived one group ago)
+            vr[(u + kShortAhead) % kG] = load_state(vres, rec[(u + kShortAhead) % kG][2], TV{});
+        }
+    }
+    __builtin_amdgcn_s_waitcnt(0x0F70);      // all stores done before the vector is read back
+}
+
+}  // namespace
+}  // namespace wpsgd
