@@ -1,12 +1,15 @@
 // Regularised objective and prediction error of a model on a data set (Eq. 3 with Eq. 4):
 //     c(w) = lambda/2 |w|^2 + (1/m) sum_j L(x_j, y_j, w.x_j),   error = #{ j : y_j (w.x_j) <= 0 } / m.
 //
-// A pure stream over the data: one wavefront takes one row at a time (lanes across the row's
-// columns or entries), accumulates w.x in fp64 (the products of two fp32 numbers are exact in
-// fp64, so the only rounding is in the order of the sum), reduces across the wave and adds the
-// row's loss to its own running total.  Which rows a wave takes, and the order in which the
-// waves' totals are added, are fixed by the launch shape, so the result does not depend on
-// timing.  The model vector is read through the cache hierarchy (it is at most a few MiB).
+// A pure stream over the data.  w.x is accumulated in fp64 (the products of two fp32 numbers are exact
+// in fp64, so the only rounding is in the order of the sum) by as many lanes as a row keeps busy: the
+// whole wave for long dense rows, 4 to 32 lanes for dense rows of up to 128 elements, 16 for sparse
+// rows.  Losses are taken 64 at a time: a wave collects the results of 64 rows, one per lane, and every lane
+// evaluates its own (one row at a time the fp64 logarithm and exponential were most of a short row's
+// instructions).  Which rows a wave takes, and the order in which lanes' and waves' totals are
+// added, are fixed by the launch shape, so the result does not depend on timing.  The model vector is read through
+// the cache hierarchy (it is at most a few MiB).
+#include <algorithm>
 #include <atomic>
 
 #include "device_utils.h"
@@ -41,6 +44,29 @@ __device__ inline double squares_of_my_share(const float *w, int64_t d, int64_t 
     return wave_sum(sq);
 }
 
+// One lane's totals, and the row it holds the result of until the wave has 64 of them.
+struct LossTotals {
+    double loss = 0.0, wrong = 0.0;
+    __device__ void add(int kind, const float *y, int64_t row, int64_t m, double yhat)
+    {
+        if (row < m) {
+            double l, wr;
+            row_loss(kind, (double)y[row] * yhat, l, wr);
+            loss += l;
+            wrong += wr;
+        }
+    }
+    __device__ void store(double *partials, int64_t wave_id, int lane, double sq) const
+    {
+        const double l = wave_sum(loss), wr = wave_sum(wrong);
+        if (lane == 0) {
+            partials[3 * wave_id] = l;
+            partials[3 * wave_id + 1] = wr;
+            partials[3 * wave_id + 2] = sq;
+        }
+    }
+};
+
 // Rows are read once and the model vector over and over: the rows' loads carry the non-temporal
 // hint (cache-policy bit 1 of a buffer load), which keeps them from displacing it (+4 % at 16 KiB rows).
 constexpr int kReadOnce = 2;
@@ -58,7 +84,11 @@ __global__ __launch_bounds__(kObjThreads) void objective_dense_kernel(const char
     const __amdgpu_buffer_rsrc_t wres =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(w), 0, (int)(uint32_t)(d * 4), 0x00020000);
     const int64_t span = (int64_t)kWave * VEC;                 // columns one wave covers per load
-    double loss_sum = 0.0, wrong_sum = 0.0;
+    LossTotals totals;
+    constexpr int kTurns = kWave / RB;        // turns of RB rows until every lane holds a row's result
+    double held = 0.0;
+    int64_t held_row = m;                     // (m: none)
+    int turn = 0;
 
     for (int64_t row0 = wave_id * RB; row0 < m; row0 += nwaves * RB) {
         double acc[RB];
@@ -108,49 +138,154 @@ __global__ __launch_bounds__(kObjThreads) void objective_dense_kernel(const char
                 for (int i = 0; i < VEC; ++i) acc[r] += (double)wv[i] * (double)xv[i];
             }
         }
-#pragma unroll
-        for (int r = 0; r < RB; ++r) {
-            const double yhat = wave_sum(acc[r]);
-            if (row0 + r < m) {                                 // uniform
-                double l, wr;
-                row_loss(loss, (double)y[row0 + r] * yhat, l, wr);
-                loss_sum += l;
-                wrong_sum += wr;
-            }
+        double yhat;
+        int64_t row;
+        if constexpr (RB == 4) {              // four sums share a register: row r's ends up in row merged_row(r) of 16 lanes
+            double t[1];
+            wave_sums_merged(acc, t);
+            yhat = t[0];
+            row = row0 + merged_row(lane / 16);
+        } else {
+            yhat = wave_sum(acc[0]);
+            row = row0;
+        }
+        if (lane % kTurns == turn) {
+            held = yhat;
+            held_row = row;
+        }
+        if (++turn == kTurns) {
+            totals.add(loss, y, held_row, m, held);
+            held_row = m;
+            turn = 0;
         }
     }
-    const double sq = squares_of_my_share(w, d, wave_id, nwaves, lane);
-    if (lane == 0) {
-        partials[3 * wave_id] = loss_sum;
-        partials[3 * wave_id + 1] = wrong_sum;
-        partials[3 * wave_id + 2] = sq;
-    }
+    totals.add(loss, y, held_row, m, held);
+    totals.store(partials, wave_id, lane, squares_of_my_share(w, d, wave_id, nwaves, lane));
 }
 
-__global__ __launch_bounds__(kObjThreads) void objective_csr_kernel(const int64_t *row_ptr, const int32_t *col_idx,
-                                                                   const float *vals, int64_t m, int64_t d, const float *y,
-                                                                   const float *w, int loss, double *partials)
+// Dense rows of at most 128 elements: LPR lanes per row, four elements each, 64/LPR rows per load instruction, LPR
+// instructions for 64 consecutive rows.  A piece that reaches past the row's end is read from d-4 on and meets
+// weights that are zero where the piece before has counted already.  A million rows of 16 elements: 215 -> 20 us
+// (hinge), 450 -> 27 us (logistic), of 100: 249 -> 86 and 463 -> 92 us (4.6 TB/s).
+template <typename TX, int LPR>
+__global__ __launch_bounds__(kObjThreads) void objective_short_rows_kernel(const TX *X, int64_t ld, int64_t m, int d, const float *y,
+                                                                          const float *w, int loss, double *partials)
 {
+    constexpr int ROWS = kWave / LPR;
+    constexpr int kAtOnce = LPR < 8 ? LPR : 8;      // loads in flight per lane
+    typedef TX four __attribute__((ext_vector_type(4), aligned(sizeof(TX))));
     const int lane = threadIdx.x & (kWave - 1);
     const int64_t wave_id = (int64_t)blockIdx.x * kObjWaves + threadIdx.x / kWave;
     const int64_t nwaves = (int64_t)gridDim.x * kObjWaves;
-    double loss_sum = 0.0, wrong_sum = 0.0;
-    for (int64_t row = wave_id; row < m; row += nwaves) {
-        const int64_t p0 = row_ptr[row], p1 = row_ptr[row + 1];
-        double acc = 0.0;
-        for (int64_t p = p0 + lane; p < p1; p += kWave) acc += (double)w[col_idx[p]] * (double)vals[p];
-        const double yhat = wave_sum(acc);
-        double l, wr;
-        row_loss(loss, (double)y[row] * yhat, l, wr);
-        loss_sum += l;
-        wrong_sum += wr;
+    const int c = lane % LPR, col = c * 4 < d - 4 ? c * 4 : d - 4;
+    double wv[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) wv[e] = col + e >= c * 4 ? (double)w[col + e] : 0.0;
+    LossTotals totals;
+    for (int64_t row0 = wave_id * kWave; row0 < m; row0 += nwaves * kWave) {
+        double held = 0.0;
+#pragma unroll
+        for (int it0 = 0; it0 < LPR; it0 += kAtOnce) {
+            four q[kAtOnce];
+#pragma unroll
+            for (int i = 0; i < kAtOnce; ++i) {
+                const int64_t row = row0 + (it0 + i) * ROWS + lane / LPR;
+                q[i] = *reinterpret_cast<const four *>(X + (row < m ? row : m - 1) * ld + col);
+            }
+#pragma unroll
+            for (int i = 0; i < kAtOnce; ++i) {
+                double acc = 0.0;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    float x;
+                    if constexpr (sizeof(TX) == 2) x = bf16_one(q[i][e]);
+                    else x = q[i][e];
+                    acc += wv[e] * (double)x;
+                }
+                acc += dpp_move<0xB1, 0xF>(acc);
+                acc += dpp_move<0x4E, 0xF>(acc);
+                if constexpr (LPR >= 8) acc += dpp_move<0x141, 0xF>(acc);
+                if constexpr (LPR >= 16) acc += dpp_move<0x140, 0xF>(acc);
+                if constexpr (LPR >= 32) acc = merge_values<true>(acc, acc);
+                held = c == it0 + i ? acc : held;
+            }
+        }
+        totals.add(loss, y, row0 + c * ROWS + lane / LPR, m, held);
     }
-    const double sq = squares_of_my_share(w, d, wave_id, nwaves, lane);
-    if (lane == 0) {
-        partials[3 * wave_id] = loss_sum;
-        partials[3 * wave_id + 1] = wrong_sum;
-        partials[3 * wave_id + 2] = sq;
+    totals.store(partials, wave_id, lane, squares_of_my_share(w, d, wave_id, nwaves, lane));
+}
+
+// Sparse rows: 16 lanes per row, four rows at a time; 4*turns <= 64 consecutive rows make a batch, whose offsets are
+// loaded at once (fewer turns where the rows would not keep all waves busy).  Bound by the gathers of the model: from the caches a compute unit serves a third to half a lane per cycle, from
+// LDS many.  HEAD > 0: the model's first HEAD columns are copied to LDS, and only the others are gathered from
+// memory (lanes that need none ask for an offset past the end, which is no access).  A million rows of 80 entries, 2^20 columns
+// (Zipf): 0.41 -> 0.31 ms (2.1 TB/s), the same without the copy 0.41; half a million rows of 40, logistic: 225 -> 70 us.
+template <int THREADS, int HEAD>
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(HEAD > 0 ? 8 : 1)))
+void objective_csr_kernel(const int64_t *row_ptr, const int32_t *col_idx,
+                                                                   const float *vals, int64_t m, int64_t d, const float *y,
+                                                                   const float *w, int loss, int turns, double *partials)
+{
+    constexpr int LPR = 16, ROWS = kWave / LPR, WAVES = THREADS / kWave;
+    constexpr int kAtOnce = 4;                // entries in flight per lane
+    __shared__ float head[HEAD > 0 ? HEAD : 1];
+    const int lane = threadIdx.x & (kWave - 1), c = lane % LPR, r = lane / LPR;
+    const int64_t wave_id = (int64_t)blockIdx.x * WAVES + threadIdx.x / kWave;
+    const int64_t nwaves = (int64_t)gridDim.x * WAVES;
+    const bool any_entries = row_ptr[m] > 0;
+    const __amdgpu_buffer_rsrc_t wres =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(w), 0, (int)(uint32_t)(d * 4), 0x00020000);
+    if constexpr (HEAD > 0) {
+        for (int i = (int)threadIdx.x; i < HEAD; i += THREADS) head[i] = i < d ? w[i] : 0.0f;
+        __syncthreads();
     }
+    LossTotals totals;
+    const int batch = ROWS * turns;
+    for (int64_t row0 = wave_id * batch; row0 < m; row0 += nwaves * batch) {
+        const int64_t mine = row0 + lane < m ? row0 + lane : m - 1;
+        const int64_t lo = row_ptr[mine];
+        const int len = (int)(row_ptr[mine + 1] - lo);
+        double held = 0.0;
+        if (any_entries) {
+            for (int it = 0; it < turns; ++it) {
+                const int from = it * ROWS + r;
+                const int64_t p0 = (int64_t)(((uint64_t)(uint32_t)__shfl((int)(lo >> 32), from) << 32) | (uint32_t)__shfl((int)(uint32_t)lo, from));
+                const int n = __shfl(len, from);
+                double acc = 0.0;
+                for (int e0 = 0; __any(e0 < n); e0 += kAtOnce * LPR) {
+                    uint32_t col[kAtOnce];
+                    float val[kAtOnce], wv[kAtOnce];
+#pragma unroll
+                    for (int i = 0; i < kAtOnce; ++i) {
+                        const int e = e0 + i * LPR + c;
+                        const int64_t p = e < n ? p0 + e : 0;    // (entry 0 exists)
+                        col[i] = (uint32_t)col_idx[p];
+                        val[i] = vals[p];
+                    }
+#pragma unroll
+                    for (int i = 0; i < kAtOnce; ++i) {
+                        const bool in = e0 + i * LPR + c < n;
+                        if constexpr (HEAD > 0) {
+                            const bool near = col[i] < (uint32_t)HEAD;
+                            const float far = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(wres, in && !near ? col[i] * 4u : 0xFFFFFFF0u, 0, 0));
+                            wv[i] = near ? head[near ? col[i] : 0u] : far;
+                        } else {
+                            wv[i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(wres, in ? col[i] * 4u : 0xFFFFFFF0u, 0, 0));
+                        }
+                    }
+#pragma unroll
+                    for (int i = 0; i < kAtOnce; ++i) acc += e0 + i * LPR + c < n ? (double)wv[i] * (double)val[i] : 0.0;
+                }
+                acc += dpp_move<0xB1, 0xF>(acc);
+                acc += dpp_move<0x4E, 0xF>(acc);
+                acc += dpp_move<0x141, 0xF>(acc);
+                acc += dpp_move<0x140, 0xF>(acc);
+                held = c == it ? acc : held;
+            }
+        }
+        if (c < turns) totals.add(loss, y, row0 + c * ROWS + r, m, held);
+    }
+    totals.store(partials, wave_id, lane, squares_of_my_share(w, d, wave_id, nwaves, lane));
 }
 
 // One workgroup: adds the waves' totals (losses, wrong predictions, squares) in wave order and writes the two results.
@@ -209,6 +344,26 @@ unsigned resident_grid(unsigned most)
         cached.store(resident, std::memory_order_relaxed);
     }
     return resident < most ? resident : most;
+}
+
+template <typename TX, int LPR>
+unsigned launch_short_rows(unsigned most, hipStream_t s, const ChainArgs &a, int loss, const float *w, double *partials)
+{
+    // one batch of 64 rows per wave at least
+    const unsigned rows = (unsigned)std::min<int64_t>((a.m + kWave * kObjWaves - 1) / (kWave * kObjWaves), most);
+    const unsigned grid = resident_grid<objective_short_rows_kernel<TX, LPR>>(rows);
+    hipLaunchKernelGGL((objective_short_rows_kernel<TX, LPR>), dim3(grid), dim3(kObjThreads), 0, s, static_cast<const TX *>(a.dense), a.ld,
+                       a.m, (int)a.d, a.y, w, loss, partials);
+    return grid;
+}
+
+template <typename TX>
+unsigned launch_short_rows(unsigned most, hipStream_t s, const ChainArgs &a, int loss, const float *w, double *partials)
+{
+    if (a.d <= 16) return launch_short_rows<TX, 4>(most, s, a, loss, w, partials);
+    if (a.d <= 32) return launch_short_rows<TX, 8>(most, s, a, loss, w, partials);
+    if (a.d <= 64) return launch_short_rows<TX, 16>(most, s, a, loss, w, partials);
+    return launch_short_rows<TX, 32>(most, s, a, loss, w, partials);
 }
 
 template <typename TX, int VEC>
@@ -272,8 +427,11 @@ hipError_t launch_objective(const ChainArgs &a, int dtype, int vec, int loss, co
         const char *X = static_cast<const char *>(a.dense);
         const int elem = dtype == WPSGD_BF16 ? 2 : 4;
         const int64_t stride = a.ld * elem;
+        const bool elements = (uintptr_t)a.dense % (unsigned)elem == 0;
         const int rb = a.d <= (int64_t)kWave * vec * 2 ? 4 : 1;     // short rows: several in flight per wave
-        if (dtype == WPSGD_BF16) {
+        if (a.d >= 4 && a.d <= 128 && elements) {
+            grid = dtype == WPSGD_BF16 ? launch_short_rows<uint16_t>(most, s, a, loss, w, partials) : launch_short_rows<float>(most, s, a, loss, w, partials);
+        } else if (dtype == WPSGD_BF16) {
             if (vec > 1) grid = launch_dense_rows<uint16_t, 8>(rb, most, s, X, stride, a.m, a.d, a.y, w, loss, partials);
             else grid = launch_dense_rows<uint16_t, 1>(rb, most, s, X, stride, a.m, a.d, a.y, w, loss, partials);
         } else {
@@ -281,9 +439,22 @@ hipError_t launch_objective(const ChainArgs &a, int dtype, int vec, int loss, co
             else grid = launch_dense_rows<float, 1>(rb, most, s, X, stride, a.m, a.d, a.y, w, loss, partials);
         }
     } else {
-        grid = resident_grid<objective_csr_kernel>(most);
-        hipLaunchKernelGGL(objective_csr_kernel, dim3(grid), dim3(kObjThreads), 0, s, a.row_ptr, a.col_idx, a.vals, a.m,
-                           a.d, a.y, w, loss, partials);
+        // As many rows per batch as leave every wave of the device one (8192 waves).  A copy of the model's head per
+        // workgroup pays when a wave has several batches' worth of rows to use it on; two workgroups of 1024 threads fill
+        // a compute unit's waves, with 64 KiB of LDS each.
+        const int turns = (int)std::max<int64_t>(1, std::min<int64_t>(a.m / (4 * 8192), 16));
+        const int64_t batches = (a.m + 4 * turns - 1) / (4 * turns);
+        constexpr int kHeadThreads = 1024, kHeadWaves = kHeadThreads / kWave, kHead = 16384;
+        if (a.m >= 131072) {
+            grid = (unsigned)std::min<int64_t>((batches + kHeadWaves - 1) / kHeadWaves, 512);
+            hipLaunchKernelGGL((objective_csr_kernel<kHeadThreads, kHead>), dim3(grid), dim3(kHeadThreads), 0, s, a.row_ptr, a.col_idx, a.vals,
+                               a.m, a.d, a.y, w, loss, turns, partials);
+            grid *= kHeadWaves / kObjWaves;              // (what the finish kernel counts in)
+        } else {
+            grid = most;                                 // (waves without rows still add up their share of the model's squares)
+            hipLaunchKernelGGL((objective_csr_kernel<kObjThreads, 0>), dim3(grid), dim3(kObjThreads), 0, s, a.row_ptr, a.col_idx, a.vals,
+                               a.m, a.d, a.y, w, loss, turns, partials);
+        }
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
