@@ -22,7 +22,7 @@ __global__ __launch_bounds__(kWave) void chain_csr_kernel(ChainArgs a)
 
     for (int64_t col = lane; col < d; col += kWave) v[col] = a.w_start ? (TV)a.w_start[col] : (TV)0;
     __syncthreads();   // the start values must be visible to whichever lane gathers them later
-    const int64_t step0 = a.step0[blockIdx.x];
+    const int64_t step0 = first_step(a, (int)blockIdx.x);
 
     RowWindow win;
     win.init(a.seed_lo, a.seed_hi, (uint32_t)chain, (uint32_t)a.m, a.perm, (uint32_t)a.k);
@@ -150,7 +150,7 @@ __global__ __launch_bounds__(kWave) void chain_csr_cached_kernel(ChainArgs a)
     float *out = a.W + (int64_t)chain * d;
     const int64_t nnz = a.row_ptr[a.m];
 
-    const int64_t step0 = a.step0[blockIdx.x];
+    const int64_t step0 = first_step(a, (int)blockIdx.x);
     if (nnz == 0) {                     // no entries at all: every step only shrinks the start vector
         double s_all = 1.0, pw = a.rho;
         for (int64_t e = n; e > 0; e >>= 1) {

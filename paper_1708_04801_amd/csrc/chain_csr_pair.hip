@@ -194,18 +194,19 @@ __global__ __launch_bounds__(kPairThreads) void chain_csr_pair_kernel(ChainArgs 
     TV *v = static_cast<TV *>(a.state) + (int64_t)chain * d;
     const int64_t nnz = a.row_ptr[a.m];
 
-    const int64_t step0 = a.step0[blockIdx.x];
+    const int64_t step0 = first_step(a, (int)blockIdx.x);
     // The vector in the workspace holds the chain's start vector on entry (csr_state_start_kernel)
     // and is scaled into W after the launch (csr_state_finish_kernel): the chain itself touches
     // only what its rows touch.  A chain without steps, or a matrix without entries (every step
     // then only shrinks the vector), has nothing to do here.
     if (nnz == 0 || n == 0) return;
+    const RowLook look(a);
     TV *head = reinterpret_cast<TV *>(lds + L::head);
-    if (rows_are_short(a)) {                         // four steps at a time: chain_csr_short.h
-        using S = ShortLds<TV>;
-        static_assert(S::head == L::head, "both keep the same columns at the same place");
-        for (int c = tid; c < kPHead + kWave; c += kPairThreads)
-            head[c] = (a.w_start && c < kPHead && c < d) ? (TV)a.w_start[c] : (TV)0;
+    using S = ShortLds<TV>;
+    static_assert(S::head == L::head && kWave <= kSlots, "both forms keep the same columns at the same place");
+    for (int c = tid; c < kPHead + kSlots; c += kPairThreads)                             // values and scratch slots
+        head[c] = (a.w_start && c < kPHead && c < d) ? (TV)a.w_start[c] : (TV)0;
+    if (look.rows_are_short()) {                     // four steps at a time: chain_csr_short.h
         for (int c = tid; c < 2 * (kPStamps + kWave); c += kPairThreads) reinterpret_cast<uint16_t *>(lds + S::stamp_a)[c] = 0;
         __syncthreads();
         constexpr int kSteps = kG * kShortRows;      // steps per section
@@ -216,8 +217,6 @@ __global__ __launch_bounds__(kPairThreads) void chain_csr_pair_kernel(ChainArgs 
         for (int c = tid; c < kPHead && c < d; c += kPairThreads) v[c] = head[c];
         return;
     }
-    for (int c = tid; c < kPHead + kSlots; c += kPairThreads)                             // values and scratch slots
-        head[c] = (a.w_start && c < kPHead && c < d) ? (TV)a.w_start[c] : (TV)0;
     for (int c = tid; c < 2 * (kPStamps + kSlots); c += kPairThreads) reinterpret_cast<uint16_t *>(lds + L::stamp_a)[c] = 0;
     __syncthreads();
 

@@ -56,17 +56,29 @@ struct ShortLds {
 };
 
 // Are the matrix's rows short?  768 rows spread over it are looked at (the same ones by every workgroup); if hardly any
-// is longer than 16 entries the answer is yes.  Either answer gives correct results.
-__device__ inline bool rows_are_short(const ChainArgs &a)
-{
-    constexpr int kLook = 768;
-    int too_long = 0;
-    for (int i = (int)threadIdx.x; i < kLook; i += kPairThreads) {
-        const int64_t row = (int64_t)((uint64_t)i * (uint64_t)a.m / kLook);
-        too_long |= a.row_ptr[row + 1] - a.row_ptr[row] > kShortLen;
+// is longer than 16 entries the answer is yes.  Either answer gives correct results.  Loaded first and asked for
+// later, so that the loads are on their way while the workgroup clears its LDS.
+struct RowLook {
+    static constexpr int kEach = 4;          // per thread
+    int64_t lo[kEach], hi[kEach];
+    __device__ RowLook(const ChainArgs &a)
+    {
+#pragma unroll
+        for (int q = 0; q < kEach; ++q) {
+            const uint64_t i = (uint64_t)threadIdx.x * kEach + q;
+            const int64_t row = (int64_t)(i * (uint64_t)a.m / (kEach * kPairThreads));
+            lo[q] = a.row_ptr[row];
+            hi[q] = a.row_ptr[row + 1];
+        }
     }
-    return __syncthreads_count(too_long) <= 1;
-}
+    __device__ bool rows_are_short() const   // (a barrier)
+    {
+        int too_long = 0;
+#pragma unroll
+        for (int q = 0; q < kEach; ++q) too_long |= hi[q] - lo[q] > kShortLen;
+        return __syncthreads_count(too_long) <= 1;
+    }
+};
 
 template <int LOSS, typename TV>
 __device__ inline void short_scout(const ChainArgs &a, char *lds, int chain, int64_t n, int64_t step0, int64_t nsections, bool marks)

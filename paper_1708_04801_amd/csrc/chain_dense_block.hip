@@ -187,14 +187,14 @@ __global__ __launch_bounds__(kBlockThreads) void chain_dense_block_kernel(ChainA
     // ----------------------------------------------------------------------------- scouts
     const int h = wave - 1;
     const TX *X = static_cast<const TX *>(a.dense);
-    const int64_t step0 = a.step0[blockIdx.x];
+    const int64_t step0 = first_step(a, (int)blockIdx.x);
     const uint32_t m32 = (uint32_t)a.m;
     uint32_t shard_lo = 0, shard_len = 1, shard_inc = 0, shard_pos = 0;
     if (a.perm) {
         shard_lo = a.shard[blockIdx.x];
         shard_len = a.shard[a.k + blockIdx.x];
         shard_inc = (uint32_t)(kScouts * kBlock) % shard_len;
-        shard_pos = (uint32_t)(((uint64_t)a.shard[2 * a.k + blockIdx.x] + (uint32_t)(kBlock * h + j)) % shard_len);
+        shard_pos = (uint32_t)(((uint64_t)step0 + (uint32_t)(kBlock * h + j)) % shard_len);
     }
     // row of step 16*b + j; asked for b = h, h+3, h+6, .. in turn
     auto sample = [&](int64_t b) {

@@ -54,7 +54,7 @@ __global__ __launch_bounds__(NT) void chain_dense_mem_kernel(ChainArgs a)
     for (int64_t col = (int64_t)tid * VEC; col < d; col += (int64_t)NT * VEC)
 #pragma unroll
         for (int j = 0; j < VEC; ++j) v[col + j] = a.w_start ? (TV)a.w_start[col + j] : (TV)0;
-    const int64_t step0 = a.step0[blockIdx.x];
+    const int64_t step0 = first_step(a, (int)blockIdx.x);
 
     RowWindow win;
     win.init(a.seed_lo, a.seed_hi, (uint32_t)chain, (uint32_t)a.m, a.perm, (uint32_t)a.k);

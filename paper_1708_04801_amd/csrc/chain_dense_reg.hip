@@ -109,7 +109,7 @@ __global__ __launch_bounds__(NT) void chain_dense_reg_kernel(ChainArgs a)
         const int64_t col = col0 + ((int64_t)(e / VEC) * NT + tid) * VEC + (e % VEC);
         v[e] = (a.w_start && col < a.d) ? (TV)a.w_start[col] : (TV)0;
     }
-    const int64_t step0 = a.step0[cb];
+    const int64_t step0 = first_step(a, cb);
 
     if (n > 0) {
         uint32_t off[Frag::kChunks];               // this lane's byte offset of each chunk
@@ -140,7 +140,7 @@ __global__ __launch_bounds__(NT) void chain_dense_reg_kernel(ChainArgs a)
         if (a.perm) {
             shard_lo = a.shard[cb];
             shard_len = a.shard[a.k + cb];
-            const uint32_t pos0 = a.shard[2 * a.k + cb], room = shard_len - pos0;
+            const uint32_t pos0 = (uint32_t)((uint64_t)step0 % shard_len), room = shard_len - pos0;
             shard_inc = (uint32_t)kWave % shard_len;
             shard_pos = (uint32_t)lane < room ? pos0 + (uint32_t)lane : ((uint32_t)lane - room) % shard_len;
         }

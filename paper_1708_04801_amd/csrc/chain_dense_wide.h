@@ -38,7 +38,7 @@ __global__ __launch_bounds__(NT) void chain_dense_wide_kernel(ChainArgs a)
         const int64_t col = ((int64_t)(e / VEC) * NT + tid) * VEC + (e % VEC);
         v[e] = (a.w_start && col < a.d) ? (TV)a.w_start[col] : (TV)0;
     }
-    const int64_t step0 = a.step0[blockIdx.x];
+    const int64_t step0 = first_step(a, (int)blockIdx.x);
 
     if (n > 0) {
         const uint32_t off0 = (uint32_t)((tid * VEC) * sizeof(TX));          // chunk c adds c*NT*VEC elements
@@ -177,7 +177,7 @@ __global__ __launch_bounds__(NT) void chain_dense_lds_kernel(ChainArgs a)
         const int64_t col = ((int64_t)(e / VEC) * NT + tid) * VEC + (e % VEC);
         v[e] = (a.w_start && col < a.d) ? (TV)a.w_start[col] : (TV)0;
     }
-    const int64_t step0 = a.step0[blockIdx.x];
+    const int64_t step0 = first_step(a, (int)blockIdx.x);
 
     if (n > 0) {
         const uint32_t off0 = (uint32_t)(tid * 16);                           // chunk c adds c*NT*16 bytes

@@ -360,7 +360,7 @@ __device__ inline void run_ahead_of_chain(const ChainArgs &a, uint32_t *lds_sink
     const int b = which < first ? nth_set_bit(on0, which) : kWave + nth_set_bit(on1, which - first);
     const int chain = a.order[b];
     const int64_t n = a.nsteps[b];
-    const int64_t step0 = a.step0[b];
+    const int64_t step0 = first_step(a, b);
     const char *X = static_cast<const char *>(a.dense);
     const int64_t row_stride = a.ld * (int64_t)sizeof(TX);
     const uint32_t row_bytes = (uint32_t)(a.d * (int64_t)sizeof(TX));

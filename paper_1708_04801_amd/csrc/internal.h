@@ -25,13 +25,14 @@ struct ChainArgs {
     int k;
     const int32_t *order;     // DEVICE, k entries: chain id run by workgroup b
     const int64_t *nsteps;    // DEVICE, k entries: steps of that chain
-    const int64_t *step0;     // DEVICE, k entries: position in that chain's sample stream of its first step
+    const int64_t *step0;     // DEVICE, k entries: position in that chain's sample stream of its first step in span 0
+    int64_t span;             // how many spans of nsteps steps each chain has behind it (0 outside periodic averaging)
     const double *pow_tab;    // DEVICE, 128 entries: (1-eta*lambda)^l for l = 0..63, then (1-eta*lambda)^-(l+1)
     const float *w_start;     // DEVICE, d entries: every chain starts from this vector; NULL: from zero
     const uint32_t *perm;     // DEVICE, m entries: shuffled row order for partition-and-shuffle sampling;
                               // NULL: the with-replacement stream
-    const uint32_t *shard;    // DEVICE, 3k entries when perm is set: for workgroup b, its chain's first
-                              // position shard[b], share size shard[k+b], and step0 mod size shard[2k+b]
+    const uint32_t *shard;    // DEVICE, 2k entries when perm is set: for workgroup b, its chain's first
+                              // position shard[b] and share size shard[k+b]
     // hyper-parameters (fp64 on purpose: (1-eta*lambda)^n must not be compounded in fp32)
     double eta, rho;          // rho = 1 - eta*lambda
     uint32_t seed_lo, seed_hi;
@@ -52,6 +53,9 @@ struct ChainArgs {
     float *W;                 // k x d
     void *state;              // k x d model vectors in HBM (state_in_hbm plans), else unused
 };
+
+// position in the sample stream of workgroup b's first step of this launch
+__device__ inline int64_t first_step(const ChainArgs &a, int b) { return a.step0[b] + a.span * a.nsteps[b]; }
 
 // Arguments of the delay-SGD servers (Section IV, Algorithms 3 and 4): workgroup i is server i.
 constexpr int kDelayMaxTau = 16;
