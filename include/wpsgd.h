@@ -89,7 +89,7 @@ typedef struct wpsgd_plan {
                             it on otherwise idle compute units and pull its rows into the L2 cache the
                             chain's compute unit shares.  0: choose (2 when compute units are to spare
                             and rows are 8 KiB or longer); -1: none; 1..3: that many, room permitting  */
-    int slices;          /* dense, 256 threads, rows in registers: compute units per chain.  Each takes a
+    int slices;          /* dense, 256 or 512 threads, rows in registers: compute units per chain.  Each takes a
                             slice of 256 x (elements per thread) columns of the model vector and of every
                             row; the slices add their partial sums through global memory once per round
                             (logistic: up to 4 steps per round; hinge: up to 2).  k*slices must not exceed

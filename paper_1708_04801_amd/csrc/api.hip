@@ -151,7 +151,7 @@ static int resolve_plan(const wpsgd_matrix *X, int k, wpsgd_loss loss, const wps
         auto search_loads = [&](int slices, int wide, Plan *found) -> bool {
         for (int nt : kThreads) {
             if (f.threads && f.threads != nt) continue;
-            if (slices > 1 && nt != 256) continue;
+            if (slices > 1 && nt != 256 && nt != 512) continue;
             for (int ept : kEpt) {
                 // the shape covers d, or one slice of it with no slice left empty
                 if ((int64_t)nt * ept * slices < X->d) continue;
@@ -159,6 +159,11 @@ static int resolve_plan(const wpsgd_matrix *X, int k, wpsgd_loss loss, const wps
                 // bf16 rows of 513 to 1024 elements: with a compute unit to itself a chain is faster on two
                 // waves (0.204 us per step, fp64 state; one wave 0.222), beyond that on one (0.237 against 0.244)
                 if (nt == 64 && ept == 16 && !f.threads && k <= compute_units()) continue;
+                // fp32 column slices of more than 4096 elements: two waves per SIMD with half the columns each keep four
+                // rounds of rows on their way where one wave has registers for two (us per step, 8 slices of 8192
+                // columns, four chains, one wave | two: logistic 1.24 | 0.92, hinge 1.43 | 1.11).  Slices of up to 4096
+                // have the registers (logistic 0.69 | 0.73, hinge 0.80 | 0.93).
+                if (slices > 1 && !f.threads && p.dtype == WPSGD_F32 && nt == 256 && ept == 32 && !f.block_steps && !f.prefetch) continue;
                 int vec = wide;
                 if (wide > 1 && ept * 4 <= wide) vec = 1;
                 if (ept % vec != 0) continue;
@@ -193,7 +198,7 @@ static int resolve_plan(const wpsgd_matrix *X, int k, wpsgd_loss loss, const wps
                 // two are within 2 %; with more the extra Gram products only cost throughput.  Rows of
                 // 8192 elements (32 per thread) gained nothing.
                 const bool few = k <= 2 * compute_units() && slices == 1 && nt <= 256;
-                const bool few_sliced = k <= compute_units() && slices > 1 && p.loss == WPSGD_LOGISTIC && p.dtype == WPSGD_F32 && ept == 16;
+                const bool few_sliced = slices > 1 && p.dtype == WPSGD_F32 && ept == 16;      // (hinge: four rounds on their way 0.80, two 1.09)
                 if (!f.block_steps && !f.prefetch && !f.rows && nt >= 128 && ept <= 16 && (few || few_sliced)) {
                     Plan two = q;
                     two.block_steps = 2;
@@ -220,8 +225,11 @@ static int resolve_plan(const wpsgd_matrix *X, int k, wpsgd_loss loss, const wps
         // per 1024-thread workgroup, cut each chain into as many column slices as there are compute
         // units for (the widest workload: 8 slices of 8192 columns run 3 times as fast as one
         // workgroup of 1024; with fp64 state that row length has no one-workgroup shape at all).
-        if (f.slices == 0 && !f.threads && !f.block_steps && !f.prefetch && !f.rows && (!have || found.threads == 1024)) {
-            for (int c = 8; c >= 2; --c) {
+        // bf16 rows of 8193 to 16384 elements fit 256 threads, but with 64 elements each: six slices take 0.72 us per step
+        // instead of 1.48 (hinge) and 0.61 instead of 0.74 (logistic, which two slices would slow down to 0.77).
+        const bool crowded = have && found.threads == 256 && found.ept >= 64;
+        if (f.slices == 0 && !f.threads && !f.block_steps && !f.prefetch && !f.rows && (!have || found.threads == 1024 || crowded)) {
+            for (int c = 8; c >= (crowded && loss == WPSGD_LOGISTIC ? 3 : 2); --c) {
                 Plan cut;
                 if (k * c <= compute_units() && search(c, &cut)) {
                     found = cut;

@@ -243,23 +243,25 @@ __global__ __launch_bounds__(kPairThreads) void chain_csr_pair_kernel(ChainArgs 
         double s_w = 1.0, eos_w = a.eta;
 
         // per-lane tables of the window being written (a) and the next one (b)
-        int64_t lo_a, lo_b;
-        int len_a, len_b;
+        // (the next window's row ends are kept as loaded until they are needed: a length taken at once would wait
+        // for these loads, and with them for every row on its way, once per window)
+        int64_t lo_a, lo_b, end_a, end_b;
+        int len_a, len_b = 0;
         float y_a, y_b;
-        auto load_window = [&](int64_t w, int64_t &lo, int &len, float &y) {
+        auto load_window = [&](int64_t w, int64_t &lo, int64_t &end, float &y) {
             // (The sampler is written out here rather than called: after a call the compiler no longer knows
             // which loads are outstanding and drains the whole queue at the top of every iteration of the loop
             // below, rows requested kLead steps ahead included.)
             const uint64_t step = (uint64_t)(step0 + w * kWave + lane);
             const uint32_t row = a.perm ? a.perm[shard_position((uint32_t)chain, (uint32_t)a.k, step, m32)]
                                         : sample_row(seed_lo, seed_hi, (uint32_t)chain, step, m32);
-            const int64_t p0 = a.row_ptr[row], p1 = a.row_ptr[(int64_t)row + 1];
-            lo = p0;
-            len = (int)(p1 - p0);
+            lo = a.row_ptr[row];
+            end = a.row_ptr[(int64_t)row + 1];
             y = a.y[row];
         };
-        load_window(0, lo_a, len_a, y_a);
-        load_window(1, lo_b, len_b, y_b);
+        load_window(0, lo_a, end_a, y_a);
+        load_window(1, lo_b, end_b, y_b);
+        len_a = (int)(end_a - lo_a);
         StepScalars<TV> sc_tab;          // per lane: the scalars of step (window start + lane)
 
         auto scout = [&](auto role_tag) {
@@ -305,7 +307,7 @@ __global__ __launch_bounds__(kPairThreads) void chain_csr_pair_kernel(ChainArgs 
                         lo_a = lo_b;
                         len_a = len_b;
                         y_a = y_b;
-                        load_window(w + 1, lo_b, len_b, y_b);
+                        load_window(w + 1, lo_b, end_b, y_b);
                     }
                     if constexpr (!MARKS) {
                         const double yd = (double)y_a;
@@ -320,6 +322,7 @@ __global__ __launch_bounds__(kPairThreads) void chain_csr_pair_kernel(ChainArgs 
                         }
                     }
                 }
+                if (j0 == kWave / 2) len_b = (int)(end_b - lo_b);       // (asked for half a window ago, used from the last quarter on)
                 // the rows requested now lie kLead steps ahead: in this window while j0 + u + kLead < 64
                 const bool ahead_in_next = j0 + kLead >= kWave;
                 const int64_t lo_t = ahead_in_next ? lo_b : lo_a;

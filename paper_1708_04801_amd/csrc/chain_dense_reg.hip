@@ -571,7 +571,7 @@ __global__ __launch_bounds__(NT) void chain_dense_reg_kernel(ChainArgs a)
     V(256, 4, 4, 4, 2) V(256, 8, 4, 4, 2) V(256, 16, 4, 4, 2) V(256, 16, 4, 1, 4)              \
     V(256, 16, 4, 2, 2) V(256, 16, 4, 2, 4) V(256, 16, 4, 2, 8) V(256, 32, 4, 4, 2)            \
     V(256, 4, 4, 2, 4) V(256, 8, 4, 2, 4) V(256, 32, 4, 2, 2)                                  \
-    V(512, 8, 4, 1, 8) V(512, 8, 4, 4, 2) V(512, 8, 4, 2, 4)                                   \
+    V(512, 8, 4, 1, 8) V(512, 8, 4, 4, 2) V(512, 8, 4, 2, 4) V(512, 16, 4, 2, 4)               \
     V(1024, 4, 4, 1, 8) V(1024, 4, 4, 4, 2) V(1024, 4, 4, 2, 4)                                \
     V(1024, 16, 4, 1, -1) V(1024, 32, 4, 1, -1)                                                \
     V(1024, 16, 4, 1, 0) V(1024, 32, 4, 1, 0) WPSGD_WIDEST(V, 4)
@@ -584,7 +584,7 @@ __global__ __launch_bounds__(NT) void chain_dense_reg_kernel(ChainArgs a)
 // registers, and sums that fit the slices' records (twelve 32-bit words).
 constexpr bool can_slice(int nt, int vec, int bb, int pp)
 {
-    return nt == 256 && vec > 1 && pp > 0 &&
+    return (nt == 256 || nt == 512) && vec > 1 && pp > 0 &&
            (bb + bb * (bb - 1) / 2) * sizeof(typename StateType<kLoss>::type) <= (size_t)kSliceMaxWords * 4;
 }
 

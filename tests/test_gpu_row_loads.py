@@ -88,3 +88,23 @@ def test_delay_servers_on_rows_at_any_dword(d, tau, check):
             continue
         assert int(acc[i]) == acc_o, (d, tau, check, i)
         assert np.linalg.norm(Wg[i].cpu().numpy() - ref) <= 2e-7 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("d,bf16", [(8200, True), (12000, True), (16384, True), (16388, False), (24001, False), (33000, False), (65536, False)])
+@pytest.mark.parametrize("loss", [wl.HINGE, wl.LOGISTIC])
+def test_column_slices_of_either_workgroup_size(d, bf16, loss):
+    rng = np.random.default_rng(d + loss)
+    m = 70
+    X = (rng.standard_normal((m, d)) / math.sqrt(d)).astype(np.float32)
+    y = np.where(rng.random(m) < 0.5, 1.0, -1.0).astype(np.float32)
+    if bf16:
+        X = wl.f32_to_bf16_bits(X)
+        dev = torch.from_numpy(X.view(np.int16)).cuda().view(torch.bfloat16)
+    else:
+        dev = torch.from_numpy(X).cuda()
+    Xg = api.Matrix(m, d, dense=dev)
+    assert "slices=" in api.wpsgd_describe_plan(Xg, len(K_STEPS), loss)
+    W = api.wpsgd_run_chains(Xg, torch.from_numpy(y).cuda(), K_STEPS, 0.5, 1e-3, loss, 9)
+    ref = orc.run_chains(orc.Dense(X), y, K_STEPS, 0.5, 1e-3, loss, 9)[0]
+    for i in range(len(K_STEPS)):
+        assert np.linalg.norm(W[i].cpu().numpy() - ref[i]) <= 1e-4 * max(np.linalg.norm(ref[i]), 1e-30), (d, i)
