@@ -15,11 +15,12 @@
 // The worker takes a group in turn step by step, reading every value when its step comes.  The steps after a long
 // row re-read their values, since its columns leave no stamps.
 //
-// What bounds it: some 510 cycles a group, much the same with fp64 and with fp32 state: the scouts' LDS and load
-// traffic beside the worker's dependent chain (LDS read, product, four levels of a sum over 16 lanes, slope, LDS write);
-// groups that re-read or run in turn add an eighth.  Ten chains of up to 100000 steps, rows of 5 to 10 entries, d = 100000:
-// 0.213 us per step one at a time, 0.060 this way (21.3 -> 6.0 ms).  Requests six groups ahead instead of four: 0.077
-// against 0.076 in an earlier form.
+// What bounds it: some 480 cycles a group, much the same with fp64 and with fp32 state: the stamp scout's tables beside
+// the worker's dependent chain (LDS read, product, four levels of a sum over 16 lanes, slope, LDS write): without the
+// tables, for timing only, 0.033 us per step; a fourth wave for the shared columns gained 2 % here and lost half a per
+// cent on long rows; groups that re-read or run in turn cost an eighth.  Ten chains of up to 100000 steps, rows of 5 to 10
+// entries, d = 100000: 0.213 us per step one at a time, 0.057 this way (21.3 -> 5.7 ms).  Requests three or six groups
+// ahead instead of four: the same within 2 %.
 #pragma once
 
 namespace wpsgd {
@@ -131,13 +132,13 @@ __device__ inline void short_scout(const ChainArgs &a, char *lds, int chain, int
         for (int u = 0; u < kShortLead; ++u) request(u, rows[kShortRows * u + r]);
         __builtin_amdgcn_s_waitcnt(0x0F70);      // enter the loop with an empty queue
         StepScalars<TV> sc_tab;
-        int64_t redo_until = -1;                 // (marks) groups up to this one re-read their values: they follow a long row
-        struct { bool tail, real, forced; uint16_t now, sa, sb; uint8_t who; bool in_turn; char *pad; } prev;
-        prev.pad = nullptr;
-        auto settle = [&]() {                    // the verdict on a group, when its table reads have arrived
-            const bool stale = __any(prev.tail & ((uint16_t)(prev.now - prev.sa) < kShortRecent) & ((uint16_t)(prev.now - prev.sb) < kShortRecent)) | prev.forced;
-            const bool shared = __any(prev.real & ((int)prev.who / kShortLen != r)) | prev.in_turn;
-            if (lane == 0) *reinterpret_cast<int32_t *>(prev.pad) = (stale ? kStale : 0) | (shared ? kInTurn : 0);
+        int redo = 0;                            // (marks) groups still to re-read their values because they follow a long row
+        struct { bool tail, real; uint16_t now, sa, sb; uint8_t who; } prev;
+        uint32_t stale_bits = 0, turn_bits = 0;  // (marks) the verdicts on this section's groups
+        auto settle = [&](int u) {               // the verdict on group u, when its table reads have arrived
+            const bool recent = ((uint16_t)(prev.now - prev.sa) < kShortRecent) & ((uint16_t)(prev.now - prev.sb) < kShortRecent);
+            if (__builtin_amdgcn_ballot_w64(prev.tail & recent) != 0) stale_bits |= 1u << u;
+            if (__builtin_amdgcn_ballot_w64(prev.real & ((int)prev.who / kShortLen != r)) != 0) turn_bits |= 1u << u;
         };
 
         // one section: groups kG*i .. kG*i + kG-1, HALF = i & 1 of the window
@@ -186,8 +187,7 @@ __device__ inline void short_scout(const ChainArgs &a, char *lds, int chain, int
                 const uint32_t col = er_col[slot];
                 const bool in = e < len, tail = in && col >= (uint32_t)kPHead;
                 if constexpr (MARKS) {
-                    const int64_t grp = i * kG + u;
-                    const uint16_t now = (uint16_t)grp;
+                    const uint16_t now = (uint16_t)(i * kG + u);
                     uint16_t *const pa = reinterpret_cast<uint16_t *>(lds + L::stamp_a) + (tail ? stamp_slot_a(col) : (uint32_t)(kPStamps + lane));
                     uint16_t *const pb = reinterpret_cast<uint16_t *>(lds + L::stamp_b) + (tail ? stamp_slot_b(col) : (uint32_t)(kPStamps + lane));
                     uint8_t *const po = reinterpret_cast<uint8_t *>(lds + L::owner) + (in ? col & (kOwners - 1) : (uint32_t)(kOwners + lane));
@@ -197,14 +197,23 @@ __device__ inline void short_scout(const ChainArgs &a, char *lds, int chain, int
                     *po = (uint8_t)lane;
                     asm volatile("" ::: "memory");          // the slot is read back after all lanes have written (one wave's LDS accesses keep their order)
                     const uint8_t who = *po;
-                    const bool has_long = __any(len > kShortLen);
-                    if (has_long) redo_until = grp + kShortRecent - 1;
-                    const bool forced = grp <= redo_until;
-                    if (u > 0) settle();         // (a section's last group is settled before its barrier)
-                    prev.tail = tail; prev.real = in; prev.forced = forced; prev.now = now; prev.sa = sa; prev.sb = sb; prev.who = who;
-                    prev.in_turn = has_long;
-                    prev.pad = sec + u * kGroupBytes + kWave * 16 + 16 + offsetof(StepRow, pad);
-                    if (u == kG - 1) settle();
+                    if (u > 0) settle(u - 1);
+                    else stale_bits = turn_bits = 0;
+                    if (__builtin_amdgcn_ballot_w64(len > kShortLen) != 0) {
+                        redo = kShortRecent;
+                        turn_bits |= 1u << u;
+                    }
+                    if (redo > 0) {
+                        stale_bits |= 1u << u;
+                        --redo;
+                    }
+                    prev.tail = tail; prev.real = in; prev.now = now; prev.sa = sa; prev.sb = sb; prev.who = who;
+                    if (u == kG - 1) {           // the section's marks go out together, before its barrier
+                        settle(u);
+                        if (lane < kG)
+                            reinterpret_cast<StepRow *>(sec + lane * kGroupBytes + kWave * 16 + 16)->pad =
+                                (int32_t)(((stale_bits >> lane) & 1u) * kStale + ((turn_bits >> lane) & 1u) * kInTurn);
+                    }
                 } else {
                     pu32x4 rec;
                     rec[0] = in ? __float_as_uint(er_val[slot]) : 0u;
