@@ -580,7 +580,7 @@ __global__ __launch_bounds__(NT) void chain_dense_reg_kernel(ChainArgs a)
 
 #define WPSGD_ALL_VARIANTS(V) WPSGD_VARIANTS_VEC(V) WPSGD_VARIANTS_ANY(V) WPSGD_VARIANTS_WIDE(V)
 
-// Which variants also exist as a kernel for column slices: four waves, vector loads, rows in
+// Which variants also exist as a kernel for column slices: four or eight waves, vector loads, rows in
 // registers, and sums that fit the slices' records (twelve 32-bit words).
 constexpr bool can_slice(int nt, int vec, int bb, int pp)
 {
