@@ -53,3 +53,19 @@ def test_sparse_rows(m, d, loss):
     out = api.wpsgd_objective(X, torch.from_numpy(y).cuda(), torch.from_numpy(w).cuda(), 0.01, loss).cpu().numpy()
     z = y * np.bincount(np.repeat(np.arange(m), lens), weights=w.astype(np.float64)[cols] * vals.astype(np.float64), minlength=m)
     _check(out, z, w.astype(np.float64), 0.01, loss)
+
+
+@pytest.mark.parametrize("d", [4, 5, 18, 31, 63, 99, 127])
+def test_an_infinite_element_counts_once(d):
+    """z = +inf costs nothing, z = -inf is wrong and costs infinitely much; no lane may meet the element with a weight of zero."""
+    X = torch.ones((70, d), device="cuda")
+    X[3, d - 1] = math.inf
+    X[65, d - 1] = math.inf
+    y = torch.ones(70, device="cuda")
+    w = torch.full((d,), 0.25, device="cuda")
+    out = api.wpsgd_objective(api.Matrix(70, d, dense=X), y, w, 0.0, wl.HINGE).cpu().numpy()
+    assert abs(out[0] - max(0.0, 1.0 - 0.25 * d) * 68 / 70) < 1e-12
+    assert out[1] == 0.0
+    y[65] = -1.0
+    out = api.wpsgd_objective(api.Matrix(70, d, dense=X), y, w, 0.0, wl.HINGE).cpu().numpy()
+    assert out[0] == math.inf and abs(out[1] - 1.0 / 70) < 1e-15
