@@ -252,7 +252,9 @@ __global__ __launch_bounds__(kPairThreads) void chain_csr_pair_kernel(ChainArgs 
             // (The sampler is written out here rather than called: after a call the compiler no longer knows
             // which loads are outstanding and drains the whole queue at the top of every iteration of the loop
             // below, rows requested kLead steps ahead included.)
-            const uint64_t step = (uint64_t)(step0 + w * kWave + lane);
+            // (past the chain's end the row of its last step once more, see chain_csr_short.h)
+            const int64_t at = w * kWave + lane;
+            const uint64_t step = (uint64_t)(step0 + (at < n ? at : n - 1));
             const uint32_t row = a.perm ? a.perm[shard_position((uint32_t)chain, (uint32_t)a.k, step, m32)]
                                         : sample_row(seed_lo, seed_hi, (uint32_t)chain, step, m32);
             lo = a.row_ptr[row];

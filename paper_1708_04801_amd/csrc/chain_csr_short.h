@@ -93,8 +93,11 @@ __device__ inline void short_scout(const ChainArgs &a, char *lds, int chain, int
     // per lane: the row of step (window start + lane), for the window being written (A), the next (B) and the one after (C)
     // (as loaded: a difference taken here would wait for the loads, and with them for every row on its way)
     struct Window { int64_t lo, end; float y; };
+    // (past the chain's end the row of its last step once more: such a step adds 0 times its row, which must be a row
+    // the chain has visited, since 0 times a NaN is one)
     auto load_window = [&](int64_t w) {
-        const uint64_t step = (uint64_t)(step0 + w * kWave + lane);
+        const int64_t at = w * kWave + lane;
+        const uint64_t step = (uint64_t)(step0 + (at < n ? at : n - 1));
         const uint32_t row = a.perm ? a.perm[shard_position((uint32_t)chain, (uint32_t)a.k, step, (uint32_t)a.m)]
                                     : sample_row(a.seed_lo, a.seed_hi, (uint32_t)chain, step, (uint32_t)a.m);
         Window t;

@@ -18,8 +18,9 @@
 // visited rows (Philox) and the two per-step scalars of the recursion, s_l and eta/s_{l+1} with
 // s_l = s_window * (1-eta*lambda)^l in fp64.  Inside a window a step fetches them with a lane
 // read, so its dependent path holds no integer hashing and no fp64 scale arithmetic.  Steps
-// past the end of the chain have eta/s = 0 in their lane and therefore change nothing: the loop
-// always runs whole groups of P rounds and needs no tail code.
+// past the end of the chain have eta/s = 0 in their lane and name the row of its last step again, so
+// that they change nothing whatever the rows behind hold (0 times a NaN is one): the loop always
+// runs whole groups of P rounds and needs no tail code.
 //
 // Rows are fetched with raw buffer loads: the row's address sits in a scalar descriptor, each
 // lane adds a fixed 32-bit offset, and lanes past the end of the row read zeros.
@@ -136,24 +137,26 @@ __global__ __launch_bounds__(NT) void chain_dense_reg_kernel(ChainArgs a)
         // Partition-and-shuffle sampling reads the tabulated shuffled order; the lane's position in
         // its chain's share advances by 64 (mod the share size) from window to window, so no
         // division sits in the loop.  Windows are asked for in order: 0, 1, 2, ...
-        uint32_t shard_lo = 0, shard_len = 1, shard_inc = 0, shard_pos = 0;
+        uint32_t shard_lo = 0, shard_len = 1, shard_inc = 0, shard_pos = 0, shard_last = 0;
         if (a.perm) {
             shard_lo = a.shard[cb];
             shard_len = a.shard[a.k + cb];
             const uint32_t pos0 = (uint32_t)((uint64_t)step0 % shard_len), room = shard_len - pos0;
             shard_inc = (uint32_t)kWave % shard_len;
+            shard_last = (uint32_t)((uint64_t)(step0 + n - 1) % shard_len);
             shard_pos = (uint32_t)lane < room ? pos0 + (uint32_t)lane : ((uint32_t)lane - room) % shard_len;
         }
         auto window_rows = [&](int64_t w) {
+            const int64_t step = w * kWave + lane;
             if (a.perm) {
-                const uint32_t *p = a.perm + ((uint64_t)shard_lo + shard_pos);
+                const uint32_t *p = a.perm + ((uint64_t)shard_lo + (step < n ? shard_pos : shard_last));
                 uint32_t r;   // a load the compiler does not count: nothing outside this branch may wait for it
                 asm volatile("global_load_dword %0, %1, off\n\ts_waitcnt vmcnt(0)" : "=v"(r) : "v"(p) : "memory");
                 const uint32_t t = shard_pos + shard_inc;                 // may wrap past 2^32: then it is past the share too
                 shard_pos = (t < shard_pos || t >= shard_len) ? t - shard_len : t;
                 return r;
             }
-            return sample_row(seed_lo, seed_hi, (uint32_t)chain, (uint64_t)(step0 + w * kWave + lane), m32);
+            return sample_row(seed_lo, seed_hi, (uint32_t)chain, (uint64_t)(step0 + (step < n ? step : n - 1)), m32);
         };
         uint32_t rows_a = window_rows(0), rows_b = window_rows(1);   // this window and the next
         TV zs_tab = (TV)0, cs_tab = (TV)0;   // per lane: s_l (times log2(e) for logistic), eta/s_{l+1}
