@@ -90,6 +90,9 @@ __global__ __launch_bounds__(kBlockThreads) void chain_dense_block_kernel(ChainA
     };
     __shared__ __attribute__((aligned(16))) Section section[2];
     __shared__ __attribute__((aligned(16))) TV model[C];
+    // does block b (in word b mod 4) hold an element whose products with others may not be finite?
+    __shared__ uint32_t excess[4];
+    constexpr float kProbe = LOSS == kLossHinge ? 0.0f : 0x1p70f;        // (fp64 products of fp32 numbers do not overflow; 256 fp32 squares of less than 2^58 do not)
 
     const int lane = (int)(threadIdx.x & (kWave - 1));
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
@@ -118,8 +121,10 @@ __global__ __launch_bounds__(kBlockThreads) void chain_dense_block_kernel(ChainA
         double s_w = 1.0;
 #pragma unroll 1
         for (int q = 0; q < kScouts; ++q) section_barrier();
+        int64_t b = 0;
+        uint32_t odd = excess[0];
 #pragma unroll 1
-        for (int64_t b = 0; b < nblk; ++b) {
+        for (int64_t end = odd ? 0 : nblk; b < end; ++b) {
             if ((b % kBlocksPerWindow) == 0 && b > 0) {
                 s_w *= rho64;
                 if (s_w < 0x1p-30) {          // fold the scale into v; the scouts do the same to theirs
@@ -143,6 +148,7 @@ __global__ __launch_bounds__(kBlockThreads) void chain_dense_block_kernel(ChainA
 #pragma unroll
             for (int t = 0; t < kBlock; ++t) gram[t] = sec.gram[t][j];
             const TV zs = sec.zs[j], cs = sec.cs[j];
+            odd = excess[(b + 1) & 3];        // (the next block's, there for a block time; read here, it has arrived when the loop asks)
             TV p = (acc[0] + acc[1]) + (acc[2] + acc[3]);
             p = merge_values<false>(p, p);    // the four quarters of the columns: every lane ends with the whole sum
             p = merge_values<true>(p, p);
@@ -172,6 +178,39 @@ __global__ __launch_bounds__(kBlockThreads) void chain_dense_block_kernel(ChainA
                 for (int e = 0; e < CE; ++e) v[e] += c[t] * (TV)sec.tile[t][lane * CE + e];
 #pragma unroll
             for (int e = 0; e < CE; ++e) model[lane * CE + e] = v[e];
+            if (__builtin_amdgcn_readfirstlane((int)odd) != 0) end = b + 1;
+            section_barrier();
+        }
+        // The block has a row that is not finite (or too large for fp32 products).  Two terms of an infinite product may
+        // have different signs, and a step that is not taken still adds 0 times its row, so products must not be split
+        // into v.x and Gram terms: from here on, on data no model is learnt from, one step is taken after the other.
+        // (The look-out for such rows, us per step at eight chains: hinge none to 2 %, logistic none up to d = 128 and 0.088 ->
+        // 0.094 at d = 256.)
+        for (; b < nblk; ++b) {
+            if ((b % kBlocksPerWindow) == 0 && b > 0) {
+                s_w *= rho64;
+                if (s_w < 0x1p-30) {
+#pragma unroll
+                    for (int e = 0; e < CE; ++e) v[e] *= (TV)s_w;
+                    s_w = 1.0;
+                }
+            }
+            const Section &sec = section[b & 1];
+#pragma unroll 1
+            for (int t = 0; t < kBlock; ++t) {
+                TV x[CE], dot = (TV)0;
+#pragma unroll
+                for (int e = 0; e < CE; ++e) {
+                    x[e] = (TV)sec.tile[t][lane * CE + e];
+                    dot += v[e] * x[e];
+                }
+                const TV q = sec.zs[t] * wave_sum(dot), cs = sec.cs[t];
+                TV ct;
+                if constexpr (LOSS == kLossHinge) ct = q < 1.0 ? cs : 0.0;
+                else ct = cs * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(q));
+#pragma unroll
+                for (int e = 0; e < CE; ++e) v[e] += ct * x[e];
+            }
             section_barrier();
         }
         const int rem = (int)(n - (n - 1) / kWave * kWave);                  // 1..64 steps in the last window
@@ -267,6 +306,16 @@ __global__ __launch_bounds__(kBlockThreads) void chain_dense_block_kernel(ChainA
         if (++beat == beats) break;
 
         add(std::integral_constant<int, K / kScouts>{}, std::integral_constant<int, 2 * K / kScouts>{});
+        // (behind the matrix products: mixed in with them it cost the scouts of bf16 rows of 256 elements 18 % of a block)
+        __builtin_amdgcn_sched_barrier(0);
+        float probe[4] = {0.0f, 0.0f, 0.0f, 0.0f};       // infinite or NaN once an element is, or is too large for products
+#pragma unroll
+        for (int kk = 0; kk < K; ++kk)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) probe[e] = fmaf(x[kk][e], kProbe, probe[e]);
+        const float probed = (probe[0] + probe[1]) + (probe[2] + probe[3]);
+        const uint64_t odd = __builtin_amdgcn_ballot_w64(!(probed - probed == 0.0f));
+        if (lane == 0) excess[b & 3] = odd != 0 ? 1u : 0u;
         section_barrier();
         if (++beat == beats) break;
 

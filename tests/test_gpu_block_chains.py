@@ -74,3 +74,28 @@ def test_scale_is_folded_and_many_chains_run(loss):
     ref = orc.run_chains(orc.Dense(host), y, n, 0.8, 0.5, loss, 4, chain_ids=np.arange(24))[0]
     _compare(W[:24], ref, TOL[loss])
     _compare(W[-12:], orc.run_chains(orc.Dense(host), y, n, 0.8, 0.5, loss, 4, chain_ids=np.arange(k - 12, k))[0], TOL[loss])
+
+
+@pytest.mark.parametrize("d", [33, 128, 200])
+@pytest.mark.parametrize("loss", [wl.HINGE, wl.LOGISTIC])
+def test_rows_that_are_not_finite(d, loss):
+    """From the step that meets an infinity on, the model holds infinities or NaN; which ones, and where the rest of it
+    stands still, is as with one step at a time."""
+    m, k = 300, 40
+    rng = np.random.default_rng(d)
+    host = (rng.standard_normal((m, d)) / math.sqrt(d)).astype(np.float32)
+    bad = rng.choice(m, 12, replace=False)
+    host[bad, rng.integers(0, d, 12)] = np.resize(np.array([math.inf, -math.inf, math.nan], dtype=np.float32), 12)
+    y = np.where(rng.random(m) < 0.5, 1.0, -1.0).astype(np.float32)
+    w0 = rng.standard_normal(d).astype(np.float32)
+    n = np.full(k, 45, dtype=np.int64)
+    W = api.wpsgd_run_chains_from(api.Matrix(m, d, dense=torch.from_numpy(host).cuda()), torch.from_numpy(y).cuda(), n, 0.5, 1e-3, loss, 9,
+                                  w_start=torch.from_numpy(w0).cuda(), plan=BLOCK).cpu().numpy()
+    spoiled = 0
+    with np.errstate(invalid="ignore"):
+        for i in range(k):
+            ref, _ = orc.sgd(orc.Dense(host), y, orc.sample_indices(9, i, 0, 45, m), 0.5, 1e-3, loss, w0=w0.astype(np.float64))
+            spoiled += not np.isfinite(ref).all()
+            # elementwise: a few dozen fp32 roundings of the model's entries, whose size is 1 (logistic); one (hinge)
+            np.testing.assert_allclose(W[i], ref, rtol=1e-5, atol=1e-5 if loss == wl.LOGISTIC else 2e-7, equal_nan=True)
+    assert 10 <= spoiled < k
