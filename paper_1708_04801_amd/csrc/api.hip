@@ -610,6 +610,7 @@ static int run_chains_from(const wpsgd_matrix *X, const float *y, int k, const i
     a.status = reinterpret_cast<uint32_t *>(ws);
     a.order = reinterpret_cast<const int32_t *>(ws + h.order);
     a.nsteps = reinterpret_cast<const int64_t *>(ws + h.steps);
+    a.longest = max_steps;
     a.step0 = reinterpret_cast<const int64_t *>(ws + h.offsets);
     a.w_start = w_start;
     a.pow_tab = reinterpret_cast<const double *>(ws + h.pow_tab);

@@ -200,13 +200,15 @@ __global__ __launch_bounds__(kPairThreads) void chain_csr_pair_kernel(ChainArgs 
     // only what its rows touch.  A chain without steps, or a matrix without entries (every step
     // then only shrinks the vector), has nothing to do here.
     if (nnz == 0 || n == 0) return;
-    const RowLook look(a);
+    const uint32_t rows_are_short = a.status[1];
     TV *head = reinterpret_cast<TV *>(lds + L::head);
     using S = ShortLds<TV>;
     static_assert(S::head == L::head && kWave <= kSlots, "both forms keep the same columns at the same place");
     for (int c = tid; c < kPHead + kSlots; c += kPairThreads)                             // values and scratch slots
         head[c] = (a.w_start && c < kPHead && c < d) ? (TV)a.w_start[c] : (TV)0;
-    if (look.rows_are_short()) {                     // four steps at a time: chain_csr_short.h
+    if (rows_are_short != 0 && n >= (rows_are_short == kShortAlways ? kShortWorth : kShortWorthInTurn)) {        // four steps at a time: chain_csr_short.h
+        // (the head's values must be written before the stamps that overlap their scratch slots)
+        __syncthreads();
         for (int c = tid; c < 2 * (kPStamps + kWave); c += kPairThreads) reinterpret_cast<uint16_t *>(lds + S::stamp_a)[c] = 0;
         __syncthreads();
         constexpr int kSteps = kG * kShortRows;      // steps per section
@@ -566,13 +568,19 @@ __global__ __launch_bounds__(kPairThreads) void chain_csr_pair_kernel(ChainArgs 
 }
 
 // Before the chains: every chain's vector in the workspace starts as the common start vector (or
-// zero).  Grid row y is chain row0 + y; the workgroups of a row share its columns.
+// zero).  Grid row y is chain row0 + y; the workgroups of a row share its columns.  The first workgroup also looks
+// at the matrix for them.
 template <typename TV>
-__global__ __launch_bounds__(256) void csr_state_start_kernel(TV *state, const float *w_start, int64_t d, int row0)
+__global__ __launch_bounds__(kLookThreads) void csr_state_start_kernel(TV *state, const float *w_start, int64_t d, int row0,
+                                                                       int64_t longest, const int64_t *row_ptr, const int32_t *col_idx, int64_t m,
+                                                                       uint32_t *answer)
 {
+    __shared__ uint8_t owner[kOwners + kWave];
     TV *v = state + (int64_t)(row0 + (int)blockIdx.y) * d;
-    for (int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x; c < d; c += (int64_t)gridDim.x * 256)
+    for (int64_t c = (int64_t)blockIdx.x * kLookThreads + threadIdx.x; c < d; c += (int64_t)gridDim.x * kLookThreads)
         v[c] = w_start ? (TV)w_start[c] : (TV)0;
+    if (row0 == 0 && blockIdx.x == 0 && blockIdx.y == 0 && longest >= kShortWorth)       // (for shorter chains the word stays zero)
+        look_for_short_rows(row_ptr, col_idx, m, owner, answer);
 }
 
 // After the chains: W[chain,:] = (1-eta*lambda)^n * v, the lazy scale applied once, in fp64.  Grid row
@@ -604,7 +612,8 @@ static hipError_t launch_pair(const ChainArgs &a, hipStream_t s)
     const unsigned across = (unsigned)std::max<int64_t>(1, std::min<int64_t>((a.d + 255) / 256, (4096 + rows_at_once - 1) / rows_at_once));
     for (int row0 = 0; row0 < a.k; row0 += kRows) {
         const unsigned rows = (unsigned)std::min(kRows, a.k - row0);
-        hipLaunchKernelGGL((csr_state_start_kernel<TV>), dim3(across, rows), dim3(256), 0, s, state, a.w_start, a.d, row0);
+        hipLaunchKernelGGL((csr_state_start_kernel<TV>), dim3(across, rows), dim3(kLookThreads), 0, s, state, a.w_start, a.d, row0, a.longest,
+                           a.row_ptr, a.col_idx, a.m, a.status + 1);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

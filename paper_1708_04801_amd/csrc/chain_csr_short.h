@@ -1,5 +1,5 @@
-// Sparse chains whose rows are short (at most 16 entries, nearly all of them): four steps at a time, one row of
-// 16 lanes each.
+// Sparse chains whose rows are short (at most 16 entries, nearly all of them) and seldom share columns: four steps at a
+// time, one row of 16 lanes each.
 //
 // A short row leaves most of a wave idle, and two short rows of a wide matrix seldom share a column.  Steps
 // whose rows share none are independent of each other but for the shrink, which the per-step scalars carry:
@@ -56,30 +56,67 @@ struct ShortLds {
     static constexpr uint32_t bytes = ring + kSections * kShortSectionBytes;
 };
 
-// Are the matrix's rows short?  768 rows spread over it are looked at (the same ones by every workgroup); if hardly any
-// is longer than 16 entries the answer is yes.  Either answer gives correct results.  Loaded first and asked for
-// later, so that the loads are on their way while the workgroup clears its LDS.
-struct RowLook {
-    static constexpr int kEach = 4;          // per thread
-    int64_t lo[kEach], hi[kEach];
-    __device__ RowLook(const ChainArgs &a)
-    {
+// Do a matrix's chains run faster four steps at a time?  One workgroup of the launch in front of the chains looks at 768
+// rows spread over the matrix and leaves the answer in the workspace; either answer gives correct results.
+//   Rows: hardly any may be longer than 16 entries.
+//   Shared columns: 192 of the rows, also spread over all of it, are put into 48 groups of four and marked as the stamp
+//   scout would.  us per step (ten chains, 5 to 10 entries, fp64), one at a time | a group in turn | side by side:
+//   0.22 | 0.45 | 0.06 if the group has HBM-resident columns, which it then reads and writes four times over, and
+//   0.22 | 0.20 | 0.06 if all its columns are in LDS.  The first costs more than it gains from two groups in five on (a
+//   column that all rows share, such as a constant term, at d = 100000: 0.22 one at a time, 0.46 in groups).  The second
+//   has to earn back the start of the scouts' deeper pipeline.
+constexpr uint32_t kShortAlways = 1, kShortLongChains = 2;       // answers, in the word behind the status word
+constexpr int kLookThreads = 256, kLookEach = 3, kLookGroups = 48, kLookMost = 19;
+// Chains of less than 128 steps do not earn back that start (8 steps of rows without a shared column: 24 us one at a
+// time, 30 in groups; 100 steps, d = 100000: 52.6 and 52.5), nor ones of less than 512 if most groups run in turn.
+constexpr int64_t kShortWorth = 128, kShortWorthInTurn = 512;
+
+__device__ inline void look_for_short_rows(const int64_t *row_ptr, const int32_t *col_idx, int64_t m, uint8_t *owner, uint32_t *answer)
+{
+    constexpr int kRows = kLookThreads * kLookEach;
+    auto row_of = [&](int i) { return (int64_t)((uint64_t)i * (uint64_t)m / kRows); };
+    int too_long = 0;
 #pragma unroll
-        for (int q = 0; q < kEach; ++q) {
-            const uint64_t i = (uint64_t)threadIdx.x * kEach + q;
-            const int64_t row = (int64_t)(i * (uint64_t)a.m / (kEach * kPairThreads));
-            lo[q] = a.row_ptr[row];
-            hi[q] = a.row_ptr[row + 1];
+    for (int q = 0; q < kLookEach; ++q) {
+        const int64_t row = row_of((int)threadIdx.x * kLookEach + q);
+        too_long |= row_ptr[row + 1] - row_ptr[row] > kShortLen;
+    }
+    const bool rows_are_short = __syncthreads_count(too_long) <= 1 && row_ptr[m] > 0;
+    if (!rows_are_short) {
+        if (threadIdx.x == 0) *answer = 0u;
+        return;
+    }
+    if (threadIdx.x >= kWave) return;
+    const int lane = (int)threadIdx.x, r = lane / kShortLen, e = lane % kShortLen;
+    int in_turn = 0, in_turn_far = 0;
+    for (int g0 = 0; g0 < kLookGroups; g0 += kShortLen) {
+        // lane 16*r + g holds row r of group g0 + g: the four rows of a group lie a quarter of the matrix apart
+        const int64_t row = row_of((r * kLookGroups + g0 + e) * (kRows / (kShortRows * kLookGroups)));
+        const int64_t lo = row_ptr[row], len = row_ptr[row + 1] - lo;
+        uint32_t col[kShortLen], real = 0;
+#pragma unroll
+        for (int g = 0; g < kShortLen; ++g) {
+            const int from = r * kShortLen + g;
+            const int64_t p = (int64_t)(((uint64_t)(uint32_t)__shfl((int)(lo >> 32), from) << 32) | (uint32_t)__shfl((int)(uint32_t)lo, from));
+            const bool in = e < __shfl((int)len, from);
+            real |= in ? 1u << g : 0u;
+            col[g] = (uint32_t)col_idx[in ? p + e : 0];         // (the matrix has an entry 0)
+        }
+#pragma unroll
+        for (int g = 0; g < kShortLen; ++g) {
+            const bool in = (real >> g) & 1u;
+            uint8_t *const slot = owner + (in ? col[g] & (kOwners - 1) : (uint32_t)(kOwners + lane));
+            *slot = (uint8_t)lane;
+            asm volatile("" ::: "memory");      // the slot is read back after all lanes have written (one wave's LDS accesses keep their order)
+            const int who = *slot;
+            asm volatile("" ::: "memory");
+            const bool turn = __builtin_amdgcn_ballot_w64(in & (who / kShortLen != r)) != 0;
+            in_turn += turn;
+            in_turn_far += turn && __builtin_amdgcn_ballot_w64(in & (col[g] >= (uint32_t)kPHead)) != 0;
         }
     }
-    __device__ bool rows_are_short() const   // (a barrier)
-    {
-        int too_long = 0;
-#pragma unroll
-        for (int q = 0; q < kEach; ++q) too_long |= hi[q] - lo[q] > kShortLen;
-        return __syncthreads_count(too_long) <= 1;
-    }
-};
+    if (lane == 0) *answer = in_turn_far > kLookMost ? 0u : (in_turn > kLookMost ? kShortLongChains : kShortAlways);
+}
 
 template <int LOSS, typename TV>
 __device__ inline void short_scout(const ChainArgs &a, char *lds, int chain, int64_t n, int64_t step0, int64_t nsections, bool marks)

@@ -25,6 +25,7 @@ struct ChainArgs {
     int k;
     const int32_t *order;     // DEVICE, k entries: chain id run by workgroup b
     const int64_t *nsteps;    // DEVICE, k entries: steps of that chain
+    int64_t longest;          // the most steps a chain has
     const int64_t *step0;     // DEVICE, k entries: position in that chain's sample stream of its first step in span 0
     int64_t span;             // how many spans of nsteps steps each chain has behind it (0 outside periodic averaging)
     const double *pow_tab;    // DEVICE, 128 entries: (1-eta*lambda)^l for l = 0..63, then (1-eta*lambda)^-(l+1)
@@ -48,7 +49,8 @@ struct ChainArgs {
     void *xchg;               // DEVICE, k * 8 * 2 slots of 128 bytes, then k * 8 words (the slices' XCD numbers)
     uint32_t slice_max_polls; // how often a slice polls for the others' sums before it gives up (a poll takes
                               // 600 to 1200 cycles); 0: it does not poll at all
-    uint32_t *status;         // DEVICE, first word of the workspace: bit 0 is set by a slice that gave up
+    uint32_t *status;         // DEVICE, first word of the workspace: bit 0 is set by a slice that gave up; the word behind it:
+                              // whether the sparse chains run four steps at a time (chain_csr_short.h)
     // outputs / scratch
     float *W;                 // k x d
     void *state;              // k x d model vectors in HBM (state_in_hbm plans), else unused

@@ -11,7 +11,8 @@ from paper_1708_04801_amd import workloads as wl
 
 pytestmark = pytest.mark.gpu
 
-STEPS = np.array([0, 1, 3, 4, 5, 31, 32, 33, 64, 127, 700], dtype=np.int64)
+# (groups of four from 128 steps on; the others run one step at a time)
+STEPS = np.array([0, 1, 3, 4, 5, 31, 32, 33, 64, 127, 128, 129, 130, 131, 159, 160, 161, 191, 193, 255, 514, 700], dtype=np.int64)
 # fp64 state leaves the rounding of the result (6e-8 an element); fp32 state some 700 roundings of it
 TOL = {wl.HINGE: 2e-7, wl.LOGISTIC: 2e-5}
 
