@@ -11,6 +11,7 @@
 // the cache hierarchy (it is at most a few MiB).
 #include <algorithm>
 #include <atomic>
+#include <type_traits>
 
 #include "device_utils.h"
 #include "internal.h"
@@ -220,12 +221,18 @@ __global__ __launch_bounds__(kObjThreads) void objective_short_rows_kernel(const
 }
 
 // Sparse rows: 16 lanes per row, four rows at a time; 4*turns <= 64 consecutive rows make a batch, whose offsets are
-// loaded at once (fewer turns where the rows would not keep all waves busy).  Bound by the gathers of the model: from the caches a compute unit serves a third to half a lane per cycle, from
-// LDS many.  HEAD > 0: the model's first HEAD columns are copied to LDS, and only the others are gathered from
-// memory (lanes that need none ask for an offset past the end, which is no access).  A million rows of 80 entries, 2^20 columns
-// (Zipf): 0.41 -> 0.31 ms (2.1 TB/s), the same without the copy 0.41; half a million rows of 40, logistic: 225 -> 70 us.
+// loaded at once.  Bound by the gathers of the model: from the caches a compute unit serves a third to half a lane per
+// cycle, from LDS many.  HEAD > 0: the model's first HEAD columns are copied to LDS and only the others are gathered from
+// memory (lanes that need none ask for an offset past the end, which is no access), if at least a quarter of the sampled
+// entries, one per thread, lie there.  A million rows of 80 entries, 2^20 columns (Zipf): 0.41 -> 0.31 ms (2.1 TB/s), the
+// same without the copy 0.41; half a million rows of 40, logistic: 225 -> 70 us.
+// Long rows take the whole wave, since with 16 lanes a row keeps a quarter as much on its way: one by one inside a batch
+// (one row of 100000 entries among 200000 of 20: 1530 us with 16 lanes, 322 with 64), and one row per wave throughout where
+// the average row is long, where rows are so few that each may have a wave, or where no head is used (1000 rows of
+// 3000: 63 -> 29 us; 1000000 rows of 80 uniform columns: 632 -> 605).
+constexpr int kLongRow = 256;                 // entries
 template <int THREADS, int HEAD>
-__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(HEAD > 0 ? 8 : 1)))
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(HEAD > 0 ? THREADS / 128 : 1)))
 void objective_csr_kernel(const int64_t *row_ptr, const int32_t *col_idx,
                                                                    const float *vals, int64_t m, int64_t d, const float *y,
                                                                    const float *w, int loss, int turns, double *partials)
@@ -234,60 +241,145 @@ void objective_csr_kernel(const int64_t *row_ptr, const int32_t *col_idx,
     constexpr int kAtOnce = 4;                // entries in flight per lane
     __shared__ float head[HEAD > 0 ? HEAD : 1];
     const int lane = threadIdx.x & (kWave - 1), c = lane % LPR, r = lane / LPR;
-    const int64_t wave_id = (int64_t)blockIdx.x * WAVES + threadIdx.x / kWave;
+    const int64_t wave_id = (int64_t)blockIdx.x * WAVES + __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
     const int64_t nwaves = (int64_t)gridDim.x * WAVES;
-    const bool any_entries = row_ptr[m] > 0;
+    const int batch = ROWS * turns;
+    // (The first offsets of either form are asked for beside the ones that choose it, each later batch's beside the batch
+    // before; many batches of a copied head have other waves to wait on, and no registers to spare.)
+    constexpr bool AHEAD = HEAD == 0;
+    auto row_at = [&](int64_t row) { return row < m ? row : m - 1; };
+    int64_t lo_wave = 0, hi_wave = 0, lo_lane = 0, hi_lane = 0;
+    auto ask_wave = [&](int64_t row) {
+        lo_wave = row_ptr[row_at(row)];
+        hi_wave = row_ptr[row_at(row) + 1];
+    };
+    auto ask_lane = [&](int64_t row0) {
+        lo_lane = row_ptr[row_at(row0 + lane)];
+        hi_lane = row_ptr[row_at(row0 + lane) + 1];
+    };
+    if constexpr (AHEAD) {
+        ask_wave(wave_id);
+        ask_lane(wave_id * batch);
+    }
+    const int64_t first = row_ptr[0], entries = row_ptr[m] - first;
     const __amdgpu_buffer_rsrc_t wres =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(w), 0, (int)(uint32_t)(d * 4), 0x00020000);
-    if constexpr (HEAD > 0) {
-        for (int i = (int)threadIdx.x; i < HEAD; i += THREADS) head[i] = i < d ? w[i] : 0.0f;
-        __syncthreads();
-    }
     LossTotals totals;
-    const int batch = ROWS * turns;
-    for (int64_t row0 = wave_id * batch; row0 < m; row0 += nwaves * batch) {
-        const int64_t mine = row0 + lane < m ? row0 + lane : m - 1;
-        const int64_t lo = row_ptr[mine];
-        const int len = (int)(row_ptr[mine + 1] - lo);
+
+    // a whole row by the whole wave (n > 0)
+    auto whole_row = [&](int64_t p0, int n) {
+        double acc = 0.0;
+        int e0 = 0;
+        for (; AHEAD && e0 + kAtOnce * kWave <= n; e0 += kAtOnce * kWave) {
+            uint32_t col[kAtOnce];
+            float val[kAtOnce], wv[kAtOnce];
+#pragma unroll
+            for (int i = 0; i < kAtOnce; ++i) {
+                col[i] = (uint32_t)col_idx[p0 + e0 + i * kWave + lane];
+                val[i] = vals[p0 + e0 + i * kWave + lane];
+            }
+#pragma unroll
+            for (int i = 0; i < kAtOnce; ++i) wv[i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(wres, col[i] * 4u, 0, 0));
+#pragma unroll
+            for (int i = 0; i < kAtOnce; ++i) acc += (double)wv[i] * (double)val[i];
+        }
+        for (int e = e0 + lane; e < n; e += kWave) acc += (double)w[col_idx[p0 + e]] * (double)vals[p0 + e];
+        return wave_sum(acc);
+    };
+    bool whole_waves = entries > m * (m <= 2 * 8192 ? 24 : kLongRow / 2), copied = false;
+    if constexpr (HEAD > 0) {                 // (copied whether it is used or not: meanwhile the sampled entry arrives)
+        if (!whole_waves) {
+            const uint32_t sampled = entries > 0 ? (uint32_t)col_idx[first + (int64_t)((uint64_t)threadIdx.x * (uint64_t)entries / THREADS)] : ~0u;
+            for (int i = (int)threadIdx.x; i < HEAD; i += THREADS) head[i] = i < d ? w[i] : 0.0f;
+            copied = __syncthreads_count(sampled < (uint32_t)HEAD) >= THREADS / 4;
+            whole_waves = !copied && entries > m * (kLongRow / 4);
+        }
+    }
+    if (whole_waves) {
         double held = 0.0;
-        if (any_entries) {
-            for (int it = 0; it < turns; ++it) {
-                const int from = it * ROWS + r;
-                const int64_t p0 = (int64_t)(((uint64_t)(uint32_t)__shfl((int)(lo >> 32), from) << 32) | (uint32_t)__shfl((int)(uint32_t)lo, from));
-                const int n = __shfl(len, from);
-                double acc = 0.0;
-                for (int e0 = 0; __any(e0 < n); e0 += kAtOnce * LPR) {
-                    uint32_t col[kAtOnce];
-                    float val[kAtOnce], wv[kAtOnce];
-#pragma unroll
-                    for (int i = 0; i < kAtOnce; ++i) {
-                        const int e = e0 + i * LPR + c;
-                        const int64_t p = e < n ? p0 + e : 0;    // (entry 0 exists)
-                        col[i] = (uint32_t)col_idx[p];
-                        val[i] = vals[p];
-                    }
-#pragma unroll
-                    for (int i = 0; i < kAtOnce; ++i) {
-                        const bool in = e0 + i * LPR + c < n;
-                        if constexpr (HEAD > 0) {
-                            const bool near = col[i] < (uint32_t)HEAD;
-                            const float far = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(wres, in && !near ? col[i] * 4u : 0xFFFFFFF0u, 0, 0));
-                            wv[i] = near ? head[near ? col[i] : 0u] : far;
-                        } else {
-                            wv[i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(wres, in ? col[i] * 4u : 0xFFFFFFF0u, 0, 0));
-                        }
-                    }
-#pragma unroll
-                    for (int i = 0; i < kAtOnce; ++i) acc += e0 + i * LPR + c < n ? (double)wv[i] * (double)val[i] : 0.0;
-                }
-                acc += dpp_move<0xB1, 0xF>(acc);
-                acc += dpp_move<0x4E, 0xF>(acc);
-                acc += dpp_move<0x141, 0xF>(acc);
-                acc += dpp_move<0x140, 0xF>(acc);
-                held = c == it ? acc : held;
+        int64_t held_row = m;                 // (m: none)
+        int turn = 0;
+        for (int64_t row = wave_id; row < m; row += nwaves) {
+            if constexpr (!AHEAD) ask_wave(row);
+            const int64_t lo = lo_wave;
+            const int n = (int)(hi_wave - lo);
+            if constexpr (AHEAD) ask_wave(row + nwaves);
+            const double yhat = n > 0 ? whole_row(lo, n) : 0.0;
+            if (lane == turn) {
+                held = yhat;
+                held_row = row;
+            }
+            if (++turn == kWave) {
+                totals.add(loss, y, held_row, m, held);
+                held_row = m;
+                turn = 0;
             }
         }
-        if (c < turns) totals.add(loss, y, row0 + c * ROWS + r, m, held);
+        totals.add(loss, y, held_row, m, held);
+        totals.store(partials, wave_id, lane, squares_of_my_share(w, d, wave_id, nwaves, lane));
+        return;
+    }
+
+    auto rows_in_batches = [&](auto copied_tag) {
+        constexpr bool COPIED = decltype(copied_tag)::value;
+        for (int64_t row0 = wave_id * batch; row0 < m; row0 += nwaves * batch) {
+            if constexpr (!AHEAD) ask_lane(row0);
+            const int64_t lo = lo_lane;
+            const int len = (int)(hi_lane - lo);
+            if constexpr (AHEAD) ask_lane(row0 + nwaves * batch);
+            double held = 0.0;
+            if (entries > 0) {
+                for (int it = 0; it < turns; ++it) {
+                    const int from = it * ROWS + r;
+                    const int64_t p0 = (int64_t)(((uint64_t)(uint32_t)__shfl((int)(lo >> 32), from) << 32) | (uint32_t)__shfl((int)(uint32_t)lo, from));
+                    const int whole = __shfl(len, from), n = whole > kLongRow ? 0 : whole;
+                    double acc = 0.0;
+                    for (int e0 = 0; __any(e0 < n); e0 += kAtOnce * LPR) {
+                        uint32_t col[kAtOnce];
+                        float val[kAtOnce], wv[kAtOnce];
+#pragma unroll
+                        for (int i = 0; i < kAtOnce; ++i) {
+                            const int e = e0 + i * LPR + c;
+                            const int64_t p = e < n ? p0 + e : first;          // (that entry exists)
+                            col[i] = (uint32_t)col_idx[p];
+                            val[i] = vals[p];
+                        }
+#pragma unroll
+                        for (int i = 0; i < kAtOnce; ++i) {
+                            const bool in = e0 + i * LPR + c < n;
+                            if constexpr (COPIED) {
+                                const bool near = col[i] < (uint32_t)HEAD;
+                                const float far = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(wres, in && !near ? col[i] * 4u : 0xFFFFFFF0u, 0, 0));
+                                wv[i] = near ? head[near ? col[i] : 0u] : far;
+                            } else {
+                                wv[i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(wres, in ? col[i] * 4u : 0xFFFFFFF0u, 0, 0));
+                            }
+                        }
+#pragma unroll
+                        for (int i = 0; i < kAtOnce; ++i) acc += e0 + i * LPR + c < n ? (double)wv[i] * (double)val[i] : 0.0;
+                    }
+                    acc += dpp_move<0xB1, 0xF>(acc);
+                    acc += dpp_move<0x4E, 0xF>(acc);
+                    acc += dpp_move<0x141, 0xF>(acc);
+                    acc += dpp_move<0x140, 0xF>(acc);
+                    held = c == it ? acc : held;
+                    uint64_t longer = __builtin_amdgcn_ballot_w64(whole > kLongRow && c == 0);
+                    while (__builtin_expect(longer != 0, 0)) {                // (one bit per such row, at its first lane)
+                        const int at = __builtin_ctzll(longer);
+                        longer &= longer - 1;
+                        const double yhat = whole_row(lane_read_i64(p0, at), __builtin_amdgcn_readlane(whole, at));
+                        held = c == it && r == at / LPR ? yhat : held;
+                    }
+                }
+            }
+            if (c < turns) totals.add(loss, y, row0 + c * ROWS + r, m, held);
+        }
+    };
+    if constexpr (HEAD > 0) {
+        if (copied) rows_in_batches(std::true_type{});
+        else rows_in_batches(std::false_type{});
+    } else {
+        rows_in_batches(std::false_type{});
     }
     totals.store(partials, wave_id, lane, squares_of_my_share(w, d, wave_id, nwaves, lane));
 }
@@ -443,19 +535,23 @@ hipError_t launch_objective(const ChainArgs &a, int dtype, int vec, int loss, co
             else grid = launch_dense_rows<float, 1>(rb, most, s, X, stride, a.m, a.d, a.y, w, loss, partials);
         }
     } else {
-        // As many rows per batch as leave every wave of the device one (8192 waves).  A copy of the model's head per
-        // workgroup pays when a wave has several batches' worth of rows to use it on; two workgroups of 1024 threads fill
-        // a compute unit's waves, with 64 KiB of LDS each.
-        const int turns = (int)std::max<int64_t>(1, std::min<int64_t>(a.m / (4 * 8192), 16));
-        const int64_t batches = (a.m + 4 * turns - 1) / (4 * turns);
+        // Batches that fill whole rounds of the waves that run at once, as long as 64 rows allow (300000 rows of 80, Zipf: one
+        // batch for most waves and two for some 90 us, one round 70).  A copy of the model's head per workgroup pays when a
+        // wave has some fifty rows to use it on (half a million rows of 80 uniform columns, which do not use it, lose 6 %); two
+        // workgroups of 1024 threads fill a compute unit's waves, with 64 KiB of LDS each.
         constexpr int kHeadThreads = 1024, kHeadWaves = kHeadThreads / kWave, kHead = 16384;
-        if (a.m >= 131072) {
+        const bool head = a.m >= 400000;
+        if (!head) grid = resident_grid<objective_csr_kernel<kObjThreads, 0>>(most);
+        const int64_t at_once = head ? 512 * kHeadWaves : std::max<int64_t>((int64_t)grid * kObjWaves, 1);
+        const int64_t rounds = (a.m + 64 * at_once - 1) / (64 * at_once);
+        const int turns = (int)((a.m + 4 * at_once * rounds - 1) / (4 * at_once * rounds));
+        if (head) {
+            const int64_t batches = (a.m + 4 * turns - 1) / (4 * turns);
             grid = (unsigned)std::min<int64_t>((batches + kHeadWaves - 1) / kHeadWaves, 512);
             hipLaunchKernelGGL((objective_csr_kernel<kHeadThreads, kHead>), dim3(grid), dim3(kHeadThreads), 0, s, a.row_ptr, a.col_idx, a.vals,
                                a.m, a.d, a.y, w, loss, turns, partials);
             grid *= kHeadWaves / kObjWaves;              // (what the finish kernel counts in)
-        } else {
-            grid = most;                                 // (waves without rows still add up their share of the model's squares)
+        } else {                                         // (waves without rows still add up their share of the model's squares)
             hipLaunchKernelGGL((objective_csr_kernel<kObjThreads, 0>), dim3(grid), dim3(kObjThreads), 0, s, a.row_ptr, a.col_idx, a.vals,
                                a.m, a.d, a.y, w, loss, turns, partials);
         }
