@@ -139,7 +139,8 @@ struct RowWindow {
         return (uint32_t)__builtin_amdgcn_readlane((int)rows, (int)(step & (kWave - 1)));
     }
     // the with-replacement stream, its sampler in line: a call in a loop keeps the caller's registers
-    // where the calling convention wants them, which costs moves all around it
+    // where the calling convention wants them, which costs moves all around it (where there is one request per
+    // sample and few registers to move the call is the shorter one: delay_server_reg_kernel)
     __device__ uint32_t get_stream(int64_t step)
     {
         const int64_t b = step & ~(int64_t)(kWave - 1);
