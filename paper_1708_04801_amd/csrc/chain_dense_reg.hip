@@ -550,6 +550,14 @@ __global__ __launch_bounds__(NT) void chain_dense_reg_kernel(ChainArgs a)
 #define WPSGD_WIDEST_LDS(V, VEC)
 #endif
 
+// 64 bf16 elements per thread: with fp64 state two steps per round do not fit the registers (157 to 263 of them go through
+// memory; 256 chains of 2000 steps at d = 16384: 3.9 to 4.1 ms, one step at a time 2.4); sliced plans ask for two.
+#if WPSGD_LOSS == 1
+#define WPSGD_BF16_WIDE(V) V(256, 64, 8, 2, 2) V(256, 64, 8, 1, 4)
+#else
+#define WPSGD_BF16_WIDE(V) V(256, 64, 8, 1, 4) V(256, 64, 8, 2, 2)
+#endif
+
 #define WPSGD_VARIANTS_ANY(V)                                                                  \
     V(64, 1, 1, 1, 8) V(64, 2, 1, 1, 8) V(64, 4, 1, 1, 8)                                      \
     V(64, 1, 1, 4, 2) V(64, 4, 1, 2, 4) V(64, 8, 1, 1, 8)                                     \
@@ -563,7 +571,7 @@ __global__ __launch_bounds__(NT) void chain_dense_reg_kernel(ChainArgs a)
     V(64, 8, 8, 1, 8) V(64, 8, 8, 4, 2) V(64, 16, 8, 1, 8) V(128, 8, 8, 2, 4)                   \
     V(256, 8, 8, 1, 8) V(256, 16, 8, 1, 8) V(256, 32, 8, 1, 4) V(256, 32, 8, 4, 2)             \
     V(256, 8, 8, 4, 2) V(256, 16, 8, 4, 2)                                                     \
-    V(256, 8, 8, 2, 4) V(256, 16, 8, 2, 4) V(256, 32, 8, 2, 4) V(256, 64, 8, 2, 2) V(256, 64, 8, 1, 4) \
+    V(256, 8, 8, 2, 4) V(256, 16, 8, 2, 4) V(256, 32, 8, 2, 4) WPSGD_BF16_WIDE(V) \
     V(256, 64, 8, 4, 2)                                                                        \
     V(1024, 16, 8, 1, -1) V(1024, 32, 8, 1, -1) WPSGD_WIDEST_LDS(V, 8)                          \
     V(1024, 16, 8, 1, 0) V(1024, 32, 8, 1, 0) WPSGD_WIDEST(V, 8)
