@@ -139,6 +139,9 @@ static int resolve_plan(const wpsgd_matrix *X, int k, wpsgd_loss loss, const wps
 
     const int aligned = dense_vec(X), wide = buffer_vec(X);
     p.vec = p.align = aligned;
+    // Chains of at most sixteen steps (unknown: long) are bound by their start: kernels that fill a deeper pipeline of rows, or
+    // round the steps up to more, do not pay there.
+    const bool brief = max_steps > 0 && max_steps <= 16;
     // The register kernel folds its lazy scale once per 64 steps, which needs
     // (1-eta*lambda)^64 to stay far inside fp32 range; a harsher shrink takes the HBM kernel,
     // which checks every step.
@@ -161,9 +164,9 @@ static int resolve_plan(const wpsgd_matrix *X, int k, wpsgd_loss loss, const wps
                 if (nt == 64 && ept == 16 && !f.threads && k <= compute_units()) continue;
                 // fp32 column slices of more than 4096 elements: two waves per SIMD with half the columns each keep four
                 // rounds of rows on their way where one wave has registers for two (us per step, 8 slices of 8192
-                // columns, four chains, one wave | two: logistic 1.24 | 0.92, hinge 1.43 | 1.11).  Slices of up to 4096
-                // have the registers (logistic 0.69 | 0.73, hinge 0.80 | 0.93).
-                if (slices > 1 && !f.threads && p.dtype == WPSGD_F32 && nt == 256 && ept == 32 && !f.block_steps && !f.prefetch) continue;
+                // columns, four chains, one wave | two: logistic 1.24 | 0.92, hinge 1.43 | 1.11; calls of four steps 25 | 32 us).
+                // Slices of up to 4096 have the registers (logistic 0.69 | 0.73, hinge 0.80 | 0.93).
+                if (slices > 1 && !f.threads && p.dtype == WPSGD_F32 && nt == 256 && ept == 32 && !f.block_steps && !f.prefetch && !brief) continue;
                 int vec = wide;
                 if (wide > 1 && ept * 4 <= wide) vec = 1;
                 if (ept % vec != 0) continue;
@@ -198,7 +201,8 @@ static int resolve_plan(const wpsgd_matrix *X, int k, wpsgd_loss loss, const wps
                 // two are within 2 %; with more the extra Gram products only cost throughput.  Rows of
                 // 8192 elements (32 per thread) gained nothing.
                 const bool few = k <= 2 * compute_units() && slices == 1 && nt <= 256;
-                const bool few_sliced = slices > 1 && p.dtype == WPSGD_F32 && ept == 16;      // (hinge: four rounds on their way 0.80, two 1.09)
+                // (sliced hinge: four rounds on their way 0.80, two 1.09; calls of four steps 40 us and 30)
+                const bool few_sliced = slices > 1 && p.dtype == WPSGD_F32 && ept == 16 && !(brief && p.loss == WPSGD_HINGE);
                 if (!f.block_steps && !f.prefetch && !f.rows && nt >= 128 && ept <= 16 && (few || few_sliced)) {
                     Plan two = q;
                     two.block_steps = 2;
@@ -226,8 +230,9 @@ static int resolve_plan(const wpsgd_matrix *X, int k, wpsgd_loss loss, const wps
         // units for (the widest workload: 8 slices of 8192 columns run 3 times as fast as one
         // workgroup of 1024; with fp64 state that row length has no one-workgroup shape at all).
         // bf16 rows of 8193 to 16384 elements fit 256 threads, but with 64 elements each: six slices take 0.72 us per step
-        // instead of 1.48 (hinge) and 0.61 instead of 0.74 (logistic, which two slices would slow down to 0.77).
-        const bool crowded = have && found.threads == 256 && found.ept >= 64;
+        // instead of 1.48 (hinge) and 0.61 instead of 0.74 (logistic, which two slices would slow down to 0.77, and which has
+        // to earn back the start of the slices: 50 steps 47 us in one piece, 53 in six).
+        const bool crowded = have && found.threads == 256 && found.ept >= 64 && !(loss == WPSGD_LOGISTIC && max_steps > 0 && max_steps < 128);
         if (f.slices == 0 && !f.threads && !f.block_steps && !f.prefetch && !f.rows && (!have || found.threads == 1024 || crowded)) {
             for (int c = 8; c >= (crowded && loss == WPSGD_LOGISTIC ? 3 : 2); --c) {
                 Plan cut;
@@ -246,9 +251,16 @@ static int resolve_plan(const wpsgd_matrix *X, int k, wpsgd_loss loss, const wps
         const int64_t block_chains = X->d <= 64 ? 4 * compute_units()
                                      : X->d <= 128 ? (loss == WPSGD_LOGISTIC ? 4 : 2) * compute_units()
                                      : (loss == WPSGD_LOGISTIC || X->dtype == WPSGD_BF16) ? compute_units() : 0;
+        // A block kernel starts later (three beats of its scouts, more code to fetch) and rounds up to sixteen steps, so chains
+        // have to be long enough (us, one wave | blocks: d = 64, 1024 chains of 100 steps 35 | 40, of 300 57 | 57; d = 128, 64
+        // chains of 50 steps 15.6 | 16.7; d = 128 logistic, 1024 chains of 300 56 | 61; bf16 d = 256 hinge, 64 chains of 50 17.7 | 24).
+        const int64_t block_worth = X->d <= 64 ? (k <= compute_units() ? 1 : k <= 2 * compute_units() ? 64 : 256)
+                                    : X->d <= 128 ? (k <= compute_units() ? 100 : k <= 2 * compute_units() ? 256 : 768)
+                                    : 512;
         const bool block_shape = X->d >= kBlockMinColumns && X->d <= kBlockMaxColumns && (uintptr_t)X->dense % (X->dtype == WPSGD_BF16 ? 2 : 4) == 0;
         const bool asked_block = f.block_steps == 16 && (!f.threads || f.threads == kWave) && !f.prefetch && !f.rows && f.slices <= 1;
-        if (block_shape && (asked_block || (have && !f.threads && !f.block_steps && !f.prefetch && !f.rows && f.slices <= 1 && k <= block_chains))) {
+        if (block_shape && (asked_block || (have && !f.threads && !f.block_steps && !f.prefetch && !f.rows && f.slices <= 1 && k <= block_chains &&
+                                            (max_steps == 0 || max_steps >= block_worth)))) {
             if (!have) found = p;
             found.family = Family::DenseReg;
             found.threads = kWave;
