@@ -90,7 +90,7 @@ typedef struct wpsgd_plan {
                             chain's compute unit shares.  0: choose (2 when compute units are to spare
                             and rows are 8 KiB or longer); -1: none; 1..3: that many, room permitting  */
     int slices;          /* dense, 256 or 512 threads, rows in registers: compute units per chain.  Each takes a
-                            slice of 256 x (elements per thread) columns of the model vector and of every
+                            slice of threads x (elements per thread) columns of the model vector and of every
                             row; the slices add their partial sums through global memory once per round
                             (logistic: up to 4 steps per round; hinge: up to 2).  k*slices must not exceed
                             the compute units.  0: choose (chains whose rows need more than 256
@@ -293,8 +293,11 @@ int wpsgd_stream_rows(const wpsgd_matrix *X, int groups, int64_t rows_per_group,
 
 const char *wpsgd_strerror(int status);
 int wpsgd_last_hip_error(void);           /* hipError_t of the last failed HIP call on this thread */
-/* Writes a short description of the kernel the given problem would run (for logs and the
- * tuner), e.g. "dense_reg f32 logistic nt=256 ept=16 vec=4 B=4 P=2".  HOST.                */
+/* Writes a short description of the kernel the given problem would run with chains of a thousand steps
+ * or more (for logs and the tuner), e.g. "dense_reg f32 logistic nt=256 ept=16 vec=4 B=4 P=2".  HOST.
+ * nt: threads that own columns of the model; scouts=S: S waves beside them that prepare blocks of steps.
+ * vec: elements per load of rows that are whole 16-byte pieces, else 1; load=L: rows that are not are
+ * fetched L elements at a time all the same.                                                          */
 int wpsgd_describe_plan(const wpsgd_matrix *X, int k, wpsgd_loss loss, const wpsgd_plan *plan,
                         char *buf, size_t buf_bytes);
 

@@ -142,6 +142,13 @@ static int resolve_plan(const wpsgd_matrix *X, int k, wpsgd_loss loss, const wps
     // Chains of at most sixteen steps (unknown: long) are bound by their start: kernels that fill a deeper pipeline of rows, or
     // round the steps up to more, do not pay there.
     const bool brief = max_steps > 0 && max_steps <= 16;
+    // Four dwords at a time from rows that are not aligned: a chain that waits for its own rows is up to a third faster
+    // that way, but where enough chains share a compute unit to keep its memory pipe full a load that touches nine
+    // 128-byte lines instead of eight costs 2 to 8 % (us, single dwords | four: d = 767, 768 chains of 1541 steps 609 | 644;
+    // d = 3001, 256 chains 667 | 723; d = 4093, 5000 chains 1389 | 1465; against 576 | 418 for one chain at d = 1501).  Rows of
+    // 129 to 512 elements have fewer waves or loads that way and gain throughout; shorter ones have twice the elements per lane
+    // (d = 65, 512 chains of 200 steps 48 | 51).
+    const bool wide_pays = wide == aligned || (X->d > 128 && X->d <= 512) || (!brief && X->d > 512 && k <= 2 * compute_units() && (X->d <= 2048 || k < compute_units()));
     // The register kernel folds its lazy scale once per 64 steps, which needs
     // (1-eta*lambda)^64 to stay far inside fp32 range; a harsher shrink takes the HBM kernel,
     // which checks every step.
@@ -221,7 +228,9 @@ static int resolve_plan(const wpsgd_matrix *X, int k, wpsgd_loss loss, const wps
         return false;
         };
         auto search = [&](int slices, Plan *found) -> bool {
-            return search_loads(slices, wide, found) || (wide > aligned && search_loads(slices, aligned, found));
+            if (wide == aligned) return search_loads(slices, wide, found);
+            if (wide_pays) return search_loads(slices, wide, found) || search_loads(slices, aligned, found);
+            return search_loads(slices, aligned, found) || ((slices == 1 || f.slices > 1) && search_loads(slices, wide, found));
         };
         Plan found;
         bool have = search(f.slices > 1 ? f.slices : 1, &found);
@@ -458,9 +467,11 @@ int wpsgd_describe_plan(const wpsgd_matrix *X, int k, wpsgd_loss loss, const wps
     if (hp > 0) std::snprintf(helped, sizeof(helped), " helpers=%d", hp);
     if (p.family == Family::DenseReg && p.slices > 1) std::snprintf(helped, sizeof(helped), " slices=%d", p.slices);
     if (p.scouts > 0) std::snprintf(helped, sizeof(helped), " scouts=%d", p.scouts);
-    std::snprintf(buf, buf_bytes, "%s %s %s nt=%d ept=%d vec=%d B=%d P=%d state=%s%s%s",
+    char load[16] = "";                  // rows of single elements that are fetched several at a time all the same
+    if (p.vec > p.align && p.scouts == 0) std::snprintf(load, sizeof(load), " load=%d", p.vec);
+    std::snprintf(buf, buf_bytes, "%s %s %s nt=%d ept=%d vec=%d%s B=%d P=%d state=%s%s%s",
                   family_name(p.family), p.dtype == WPSGD_BF16 ? "bf16" : "f32",
-                  p.loss == WPSGD_HINGE ? "hinge" : "logistic", p.threads, p.ept, std::min(p.vec, p.align),
+                  p.loss == WPSGD_HINGE ? "hinge" : "logistic", p.threads, p.ept, std::min(p.vec, p.align), load,
                   p.block_steps, p.prefetch,
                   p.state_bytes_per_elem == 0 ? "registers" : (p.state_bytes_per_elem == 8 ? "hbm-f64" : "hbm-f32"),
                   p.family == Family::DenseReg ? kRows[p.rows] : "", helped);

@@ -49,3 +49,13 @@ def test_column_slices_of_bf16_rows():
     assert torch.equal(_run(12000, 3, 127, None, bf16=True), _run(12000, 3, 127, {"threads": 256, "slices": 1}, bf16=True))
     assert torch.equal(_run(12000, 3, 128, None, bf16=True), _run(12000, 3, 128, {"slices": 6}, bf16=True))
 
+
+@pytest.mark.parametrize("d,k,four", [
+    (65, 300, False), (129, 5000, True), (501, 5000, True), (513, 512, True), (513, 513, False), (2047, 512, True), (2049, 255, True),
+    (2049, 256, False), (4093, 5000, False)])
+def test_rows_that_are_not_aligned(d, k, four):
+    """Four dwords at a time, or one where enough chains share the compute units."""
+    flat = torch.zeros(2 * d + 1, device="cuda")
+    X = api.Matrix(2, d, dense=flat[1:1 + 2 * d].view(2, d))
+    plan = api.wpsgd_describe_plan(X, k, wl.HINGE)
+    assert "vec=1 " in plan and ("load=4" in plan) == four, plan
