@@ -559,15 +559,17 @@ __global__ __launch_bounds__(NT) void chain_dense_reg_kernel(ChainArgs a)
 #endif
 
 #define WPSGD_VARIANTS_ANY(V)                                                                  \
-    V(64, 1, 1, 1, 8) V(64, 2, 1, 1, 8) V(64, 4, 1, 1, 8)                                      \
-    V(64, 1, 1, 4, 2) V(64, 4, 1, 2, 4) V(64, 8, 1, 1, 8)                                     \
+    V(64, 1, 1, 1, 8) V(64, 2, 1, 1, 8)                                                        \
+    V(64, 1, 1, 4, 2) V(64, 4, 1, 2, 4)                                                        \
     V(256, 4, 1, 1, 4) V(256, 8, 1, 1, 4) V(256, 16, 1, 1, 4) V(256, 32, 1, 1, 2)              \
     V(256, 4, 1, 4, 2) V(256, 16, 1, 4, 2)                                                     \
     V(256, 4, 1, 2, 4) V(256, 8, 1, 2, 4)                                                      \
     V(1024, 16, 1, 1, 0) V(1024, 32, 1, 1, 0) WPSGD_WIDEST(V, 1)
 
 #if WPSGD_TX_BF16
+// (unaligned fp32 rows of 129 to 512 elements are loaded four dwords at a time on any plan)
 #define WPSGD_VARIANTS_VEC(V)                                                                  \
+    V(64, 4, 1, 1, 8) V(64, 8, 1, 1, 8)                                                        \
     V(64, 8, 8, 1, 8) V(64, 8, 8, 4, 2) V(64, 16, 8, 1, 8) V(128, 8, 8, 2, 4)                   \
     V(256, 8, 8, 1, 8) V(256, 16, 8, 1, 8) V(256, 32, 8, 1, 4) V(256, 32, 8, 4, 2)             \
     V(256, 8, 8, 4, 2) V(256, 16, 8, 4, 2)                                                     \
