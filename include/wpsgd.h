@@ -95,7 +95,7 @@ typedef struct wpsgd_plan {
                             (logistic: up to 4 steps per round; hinge: up to 2).  k*slices must not exceed
                             the compute units.  0: choose (chains whose rows need more than 256
                             threads, compute units permitting); 1: a chain is one workgroup; 2..8: that
-                            many, which must be what some 256-thread shape needs to cover d.
+                            many, which must be what some shape of 256 or 512 threads needs to cover d.
                             The slices of a chain wait for each other, so all k*slices workgroups must
                             be running at once.  The library sees to it where it can: a sliced launch
                             never has more workgroups than the device has compute units, and within one

@@ -498,9 +498,6 @@ struct SlicedLaunchOrder {
 };
 static SlicedLaunchOrder g_sliced;
 
-// keep_status: leave the status word as earlier launches on this workspace left it (later spans of
-// wpsgd_run_spans); otherwise it is cleared along with the header.
-
 static hipError_t launch_whole(Plan p, const ChainArgs &a, hipStream_t s)
 {
     switch (p.family) {
@@ -612,7 +609,7 @@ static int run_chains_from(const wpsgd_matrix *X, const float *y, int k, const i
     char *ws = static_cast<char *>(workspace);
     uint32_t *perm_dev = reinterpret_cast<uint32_t *>(ws + h.total);
     void *state_dev = ws + h.total + perm_bytes(X->m);
-    rc = upload(ws, header.data(), header.size(), s);             // (the status block is zero in `header`)
+    rc = upload(ws, header.data(), header.size(), s);             // (clears the status block, once per call: a span that fails stays reported)
     if (rc != WPSGD_OK) return rc;
 
     if (spans) {

@@ -348,7 +348,7 @@ def test_dense_rows_with_padding_and_misaligned_base():
     flat = torch.zeros(m * d + 1, dtype=torch.float32, device="cuda")
     flat[1:] = torch.from_numpy(X).cuda().reshape(-1)
     Xu = api.Matrix(m, d, dense=flat[1:].view(m, d))               # base only 4-byte aligned
-    assert "vec=1" in api.wpsgd_describe_plan(Xu, 2, wl.LOGISTIC)
+    assert "vec=1 load=4" in api.wpsgd_describe_plan(Xu, 2, wl.LOGISTIC)       # (four dwords at a time all the same)
     check_against_oracle(w, gpu_chains(w, X=Xu), label="misaligned base")
 
 

@@ -13,6 +13,8 @@ from paper_1708_04801_amd import workloads as wl
 pytestmark = pytest.mark.gpu
 
 K_STEPS = np.array([130, 0, 1, 65, 64], dtype=np.int64)
+# fp64 state leaves the rounding of the result to fp32 (6e-8 an element); fp32 state some 130 roundings of the model and of its products
+TOL = {wl.HINGE: 2e-7, wl.LOGISTIC: 1e-5}
 
 
 def _embedded(X, ld, shift):
@@ -42,7 +44,7 @@ def test_rows_at_any_dword(d, ld, shift, loss):
     got = W.cpu().numpy()
     for i in range(len(K_STEPS)):
         scale = max(np.linalg.norm(ref[i]), 1e-30)
-        assert np.linalg.norm(got[i] - ref[i]) <= 1e-4 * scale, (d, ld, shift, i)
+        assert np.linalg.norm(got[i] - ref[i]) <= TOL[loss] * scale, (d, ld, shift, i)
     # the objective reads rows and model with the same kind of load; its sums are fp64 (order of the sum only)
     out = api.wpsgd_objective(Xg, yg, W[0].contiguous(), 1e-3, loss).cpu().numpy()
     w = got[0].astype(np.float64)
@@ -67,7 +69,7 @@ def test_bf16_rows_on_every_workgroup_size(d, k, loss):
     ids = np.array([0, 1, 2, 3, 4, k - 1])
     ref = orc.run_chains(orc.Dense(bits), y, n, 0.5, 1e-3, loss, 9, chain_ids=ids)[0]
     for q, i in enumerate(ids):
-        assert np.linalg.norm(W[i] - ref[q]) <= 1e-4 * max(np.linalg.norm(ref[q]), 1e-30), (d, k, i)
+        assert np.linalg.norm(W[i] - ref[q]) <= TOL[loss] * max(np.linalg.norm(ref[q]), 1e-30), (d, k, i)
 
 
 @pytest.mark.parametrize("d", [50, 333, 542, 1023, 2047, 4095])
@@ -107,4 +109,4 @@ def test_column_slices_of_either_workgroup_size(d, bf16, loss):
     W = api.wpsgd_run_chains(Xg, torch.from_numpy(y).cuda(), K_STEPS, 0.5, 1e-3, loss, 9)
     ref = orc.run_chains(orc.Dense(X), y, K_STEPS, 0.5, 1e-3, loss, 9)[0]
     for i in range(len(K_STEPS)):
-        assert np.linalg.norm(W[i].cpu().numpy() - ref[i]) <= 1e-4 * max(np.linalg.norm(ref[i]), 1e-30), (d, i)
+        assert np.linalg.norm(W[i].cpu().numpy() - ref[i]) <= TOL[loss] * max(np.linalg.norm(ref[i]), 1e-30), (d, i)

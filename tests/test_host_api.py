@@ -128,8 +128,12 @@ def test_planner_picks_registers_when_the_vector_fits_and_hbm_otherwise():
     assert "state=registers" in d(_FakeMatrix(65536, 65536, api.BF16), 32, api.LOGISTIC)
     assert d(_FakeMatrix(100, 1 << 20), 2, api.LOGISTIC).startswith("dense_mem")
     assert "hbm-f64" in d(_FakeMatrix(100, 1 << 20), 2, api.HINGE)
-    assert "vec=1" in d(_FakeMatrix(100, 255), 2, api.HINGE)            # ragged d: scalar loads
-    assert "vec=1" in d(_FakeMatrix(100, 256, base=0x10004), 2, api.HINGE)   # misaligned base
+    assert "vec=1" in d(_FakeMatrix(100, 255), 2, api.HINGE)            # ragged d: rows are not whole 16-byte pieces,
+    assert "load=4" in d(_FakeMatrix(100, 255), 2, api.HINGE)           # but fp32 rows are fetched four dwords at a time,
+    assert "vec=1" in d(_FakeMatrix(100, 255, api.BF16), 2000, api.HINGE)       # bf16 rows element by element
+    assert "load=" not in d(_FakeMatrix(100, 255, api.BF16), 2000, api.HINGE)
+    assert "vec=1" in d(_FakeMatrix(100, 256, base=0x10004), 2, api.HINGE)   # misaligned base: the same
+    assert "load=4" in d(_FakeMatrix(100, 256, base=0x10004), 2, api.HINGE)
     assert d(_FakeMatrix(1000, 1 << 20, csr=True), 2, api.HINGE).startswith("csr")
     assert "dense_mem" in d(_FakeMatrix(100, 256), 2, api.HINGE, plan={"state_in_hbm": 1})
     with pytest.raises(api.WpsgdError) as err:
