@@ -228,25 +228,30 @@ __global__ __launch_bounds__(kBlockThreads) void chain_dense_block_kernel(ChainA
     const TX *X = static_cast<const TX *>(a.dense);
     const int64_t step0 = first_step(a, (int)blockIdx.x);
     const uint32_t m32 = (uint32_t)a.m;
-    uint32_t shard_lo = 0, shard_len = 1, shard_inc = 0, shard_pos = 0, shard_last = 0;
+    uint32_t shard_lo = 0, shard_len = 1, shard_inc = 0, shard_pos = 0;
     if (a.perm) {
         shard_lo = a.shard[blockIdx.x];
         shard_len = a.shard[a.k + blockIdx.x];
         shard_inc = (uint32_t)(kScouts * kBlock) % shard_len;
-        shard_last = (uint32_t)((uint64_t)(step0 + n - 1) % shard_len);
         shard_pos = (uint32_t)(((uint64_t)step0 + (uint32_t)(kBlock * h + j)) % shard_len);
     }
     // row of step 16*b + j, past the chain's end that of its last step once more (such a step adds 0 times its
     // row, which must be a row the chain has visited: 0 times a NaN is one); asked for b = h, h+3, h+6, .. in turn
     auto sample = [&](int64_t b) {
-        const int64_t step = b * kBlock + j;
+        uint32_t r;
         if (a.perm) {
-            const uint32_t r = a.perm[(uint64_t)shard_lo + (step < n ? shard_pos : shard_last)];
+            r = a.perm[(uint64_t)shard_lo + shard_pos];
             const uint32_t t = shard_pos + shard_inc;                 // may wrap past 2^32: then it is past the share too
             shard_pos = (t < shard_pos || t >= shard_len) ? t - shard_len : t;
-            return r;
+        } else {
+            r = sample_row(a.seed_lo, a.seed_hi, (uint32_t)chain, (uint64_t)(step0 + b * kBlock + j), m32);
         }
-        return sample_row(a.seed_lo, a.seed_hi, (uint32_t)chain, (uint64_t)(step0 + (step < n ? step : n - 1)), m32);
+        if (b == nblk - 1) {                  // (blocks behind the last are asked for, but not run)
+            const int last = (int)((n - 1) % kBlock);
+            const uint32_t row = (uint32_t)__builtin_amdgcn_readlane((int)r, last);
+            r = j < last ? r : row;
+        }
+        return r;
     };
     // Lane (j, g) takes columns 16*kk + 4*g .. +3 of row j.  A piece that reaches past the row's end is read from
     // d-4 on instead and shifted; columns from d on are zero.
