@@ -146,18 +146,19 @@ __global__ __launch_bounds__(NT) void chain_dense_reg_kernel(ChainArgs a)
             shard_last = (uint32_t)((uint64_t)(step0 + n - 1) % shard_len);
             shard_pos = (uint32_t)lane < room ? pos0 + (uint32_t)lane : ((uint32_t)lane - room) % shard_len;
         }
+        int64_t left = n - lane;             // steps from the lane's in the window asked for next to the end
         auto window_rows = [&](int64_t w) {
-            const int64_t left = n - w * kWave;                           // (a window behind the end: negative, more than -128)
-            const int last = (int)(left < kWave ? left : kWave) - 1;
+            const int64_t behind = left > 0 ? 0 : left - 1;              // from the lane's step back to the chain's last
+            left -= kWave;
             if (a.perm) {
-                const uint32_t *p = a.perm + ((uint64_t)shard_lo + (lane <= last ? shard_pos : shard_last));
+                const uint32_t *p = a.perm + ((uint64_t)shard_lo + (behind == 0 ? shard_pos : shard_last));
                 uint32_t r;   // a load the compiler does not count: nothing outside this branch may wait for it
                 asm volatile("global_load_dword %0, %1, off\n\ts_waitcnt vmcnt(0)" : "=v"(r) : "v"(p) : "memory");
                 const uint32_t t = shard_pos + shard_inc;                 // may wrap past 2^32: then it is past the share too
                 shard_pos = (t < shard_pos || t >= shard_len) ? t - shard_len : t;
                 return r;
             }
-            return sample_row(seed_lo, seed_hi, (uint32_t)chain, (uint64_t)(step0 + w * kWave + (lane < last ? lane : last)), m32);
+            return sample_row(seed_lo, seed_hi, (uint32_t)chain, (uint64_t)(step0 + w * kWave + lane + behind), m32);
         };
         uint32_t rows_a = window_rows(0), rows_b = window_rows(1);   // this window and the next
         TV zs_tab = (TV)0, cs_tab = (TV)0;   // per lane: s_l (times log2(e) for logistic), eta/s_{l+1}
