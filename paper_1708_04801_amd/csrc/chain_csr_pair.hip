@@ -254,7 +254,8 @@ __global__ __launch_bounds__(kPairThreads) void chain_csr_pair_kernel(ChainArgs 
             // (The sampler is written out here rather than called: after a call the compiler no longer knows
             // which loads are outstanding and drains the whole queue at the top of every iteration of the loop
             // below, rows requested kLead steps ahead included.)
-            // (past the chain's end the row of its last step once more, see chain_csr_short.h)
+            // (past the chain's end the row of its last step once more: such a step adds 0 times its row, which must be a
+            // row the chain has visited, since 0 times a NaN is one)
             const int64_t at = w * kWave + lane;
             const uint64_t step = (uint64_t)(step0 + (at < n ? at : n - 1));
             const uint32_t row = a.perm ? a.perm[shard_position((uint32_t)chain, (uint32_t)a.k, step, m32)]
@@ -575,12 +576,12 @@ __global__ __launch_bounds__(kLookThreads) void csr_state_start_kernel(TV *state
                                                                        int64_t longest, const int64_t *row_ptr, const int32_t *col_idx, int64_t m,
                                                                        uint32_t *answer)
 {
-    __shared__ uint8_t owner[kOwners + kWave];
+    __shared__ uint8_t owner[kLookThreads / kWave][kLookSlots + kWave];
     TV *v = state + (int64_t)(row0 + (int)blockIdx.y) * d;
+    if (row0 == 0 && blockIdx.x == 0 && blockIdx.y == 0 && longest >= kShortWorth)       // (for shorter chains the word stays zero)
+        look_for_short_rows(row_ptr, col_idx, m, owner[threadIdx.x / kWave], answer);
     for (int64_t c = (int64_t)blockIdx.x * kLookThreads + threadIdx.x; c < d; c += (int64_t)gridDim.x * kLookThreads)
         v[c] = w_start ? (TV)w_start[c] : (TV)0;
-    if (row0 == 0 && blockIdx.x == 0 && blockIdx.y == 0 && longest >= kShortWorth)       // (for shorter chains the word stays zero)
-        look_for_short_rows(row_ptr, col_idx, m, owner, answer);
 }
 
 // After the chains: W[chain,:] = (1-eta*lambda)^n * v, the lazy scale applied once, in fp64.  Grid row

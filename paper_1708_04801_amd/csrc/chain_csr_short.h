@@ -12,7 +12,8 @@
 //   in turn    groups in which two rows share a column (or a slot of the table that finds them: every lane
 //              writes its number to the slot of its column and reads the slot back; of two lanes with one
 //              column at most one finds its own number), or in which a row is longer than 16 entries.
-// The worker takes a group in turn step by step, reading every value when its step comes.  The steps after a long
+// The worker takes a group in turn step by step, reading every value when its step comes; so it takes the group in which
+// the chain ends, and leaves out the steps behind the end.  The steps after a long
 // row re-read their values, since its columns leave no stamps.
 //
 // What bounds it: some 480 cycles a group, much the same with fp64 and with fp32 state: the stamp scout's tables beside
@@ -59,63 +60,63 @@ struct ShortLds {
 // Do a matrix's chains run faster four steps at a time?  One workgroup of the launch in front of the chains looks at 768
 // rows spread over the matrix and leaves the answer in the workspace; either answer gives correct results.
 //   Rows: hardly any may be longer than 16 entries.
-//   Shared columns: 192 of the rows, also spread over all of it, are put into 48 groups of four and marked as the stamp
-//   scout would.  us per step (ten chains, 5 to 10 entries, fp64), one at a time | a group in turn | side by side:
+//   Shared columns: 192 of the rows, also spread over all of it, are put into 48 groups of four, and the groups that share a
+//   column counted.  us per step (ten chains, 5 to 10 entries, fp64), one at a time | a group in turn | side by side:
 //   0.22 | 0.45 | 0.06 if the group has HBM-resident columns, which it then reads and writes four times over, and
 //   0.22 | 0.20 | 0.06 if all its columns are in LDS.  The first costs more than it gains from two groups in five on (a
 //   column that all rows share, such as a constant term, at d = 100000: 0.22 one at a time, 0.46 in groups).  The second
 //   has to earn back the start of the scouts' deeper pipeline.
 constexpr uint32_t kShortAlways = 1, kShortLongChains = 2;       // answers, in the word behind the status word
-constexpr int kLookThreads = 256, kLookEach = 3, kLookGroups = 48, kLookMost = 19;
+constexpr int kLookThreads = 256, kLookEach = 3, kLookGroups = 48, kLookMost = 19, kLookSlots = 4096;
 // Chains of less than 128 steps do not earn back that start (8 steps of rows without a shared column: 24 us one at a
 // time, 30 in groups; 100 steps, d = 100000: 52.6 and 52.5), nor ones of less than 512 if most groups run in turn.
 constexpr int64_t kShortWorth = 128, kShortWorthInTurn = 512;
 
+// owner: this wave's table.  (All loads of the look go out at once, a quarter of the groups per wave: two trips to memory.)
 __device__ inline void look_for_short_rows(const int64_t *row_ptr, const int32_t *col_idx, int64_t m, uint8_t *owner, uint32_t *answer)
 {
-    constexpr int kRows = kLookThreads * kLookEach;
+    constexpr int kRows = kLookThreads * kLookEach, kMine = kLookGroups / (kLookThreads / kWave);        // groups of a wave
+    static_assert(kMine <= kShortLen, "lane 16*r + g holds row r of the wave's group g");
+    const int lane = (int)(threadIdx.x & (kWave - 1)), wave = (int)threadIdx.x / kWave, r = lane / kShortLen, e = lane % kShortLen;
     auto row_of = [&](int i) { return (int64_t)((uint64_t)i * (uint64_t)m / kRows); };
+    const int64_t entries = row_ptr[m];
     int too_long = 0;
 #pragma unroll
     for (int q = 0; q < kLookEach; ++q) {
         const int64_t row = row_of((int)threadIdx.x * kLookEach + q);
         too_long |= row_ptr[row + 1] - row_ptr[row] > kShortLen;
     }
-    const bool rows_are_short = __syncthreads_count(too_long) <= 1 && row_ptr[m] > 0;
-    if (!rows_are_short) {
-        if (threadIdx.x == 0) *answer = 0u;
-        return;
-    }
-    if (threadIdx.x >= kWave) return;
-    const int lane = (int)threadIdx.x, r = lane / kShortLen, e = lane % kShortLen;
-    int in_turn = 0, in_turn_far = 0;
-    for (int g0 = 0; g0 < kLookGroups; g0 += kShortLen) {
-        // lane 16*r + g holds row r of group g0 + g: the four rows of a group lie a quarter of the matrix apart
-        const int64_t row = row_of((r * kLookGroups + g0 + e) * (kRows / (kShortRows * kLookGroups)));
-        const int64_t lo = row_ptr[row], len = row_ptr[row + 1] - lo;
-        uint32_t col[kShortLen], real = 0;
+    // (the four rows of a group lie a quarter of the matrix apart)
+    const int64_t row = row_of((r * kLookGroups + wave * kMine + (e < kMine ? e : 0)) * (kRows / (kShortRows * kLookGroups)));
+    const int64_t lo = row_ptr[row], len = row_ptr[row + 1] - lo;
+    uint32_t col[kMine], real = 0;
 #pragma unroll
-        for (int g = 0; g < kShortLen; ++g) {
-            const int from = r * kShortLen + g;
-            const int64_t p = (int64_t)(((uint64_t)(uint32_t)__shfl((int)(lo >> 32), from) << 32) | (uint32_t)__shfl((int)(uint32_t)lo, from));
-            const bool in = e < __shfl((int)len, from);
-            real |= in ? 1u << g : 0u;
-            col[g] = (uint32_t)col_idx[in ? p + e : 0];         // (the matrix has an entry 0)
-        }
-#pragma unroll
-        for (int g = 0; g < kShortLen; ++g) {
-            const bool in = (real >> g) & 1u;
-            uint8_t *const slot = owner + (in ? col[g] & (kOwners - 1) : (uint32_t)(kOwners + lane));
-            *slot = (uint8_t)lane;
-            asm volatile("" ::: "memory");      // the slot is read back after all lanes have written (one wave's LDS accesses keep their order)
-            const int who = *slot;
-            asm volatile("" ::: "memory");
-            const bool turn = __builtin_amdgcn_ballot_w64(in & (who / kShortLen != r)) != 0;
-            in_turn += turn;
-            in_turn_far += turn && __builtin_amdgcn_ballot_w64(in & (col[g] >= (uint32_t)kPHead)) != 0;
-        }
+    for (int g = 0; g < kMine; ++g) {
+        const int from = r * kShortLen + g;
+        const int64_t p = (int64_t)(((uint64_t)(uint32_t)__shfl((int)(lo >> 32), from) << 32) | (uint32_t)__shfl((int)(uint32_t)lo, from));
+        const bool in = e < __shfl((int)len, from);
+        real |= in ? 1u << g : 0u;
+        col[g] = 0;
+        if (entries > 0) col[g] = (uint32_t)col_idx[in ? p + e : 0];         // (the matrix has an entry 0)
     }
-    if (lane == 0) *answer = in_turn_far > kLookMost ? 0u : (in_turn > kLookMost ? kShortLongChains : kShortAlways);
+    uint32_t in_turn = 0, far = 0;            // a bit per group
+#pragma unroll
+    for (int g = 0; g < kMine; ++g) {
+        const bool in = (real >> g) & 1u;
+        uint8_t *const slot = owner + (in ? col[g] & (kLookSlots - 1) : (uint32_t)(kLookSlots + lane));
+        *slot = (uint8_t)lane;
+        asm volatile("" ::: "memory");          // the slot is read back after all lanes have written (one wave's LDS accesses keep their order)
+        const int who = *slot;
+        asm volatile("" ::: "memory");
+        // (the table is small: its owner's column is compared)
+        const bool shared = in & (who / kShortLen != r) & ((uint32_t)__shfl((int)col[g], who) == col[g]);
+        if (__builtin_amdgcn_ballot_w64(shared) != 0) in_turn |= 1u << g;
+        if (__builtin_amdgcn_ballot_w64(in & (col[g] >= (uint32_t)kPHead)) != 0) far |= 1u << g;
+    }
+    const bool rows_are_short = __syncthreads_count(too_long) <= 1 && entries > 0;
+    const int nturn = __syncthreads_count(lane < kMine && (in_turn >> lane & 1u));
+    const int nfar = __syncthreads_count(lane < kMine && ((in_turn & far) >> lane & 1u));
+    if (threadIdx.x == 0) *answer = !rows_are_short || nfar > kLookMost ? 0u : (nturn > kLookMost ? kShortLongChains : kShortAlways);
 }
 
 template <int LOSS, typename TV>
@@ -130,11 +131,8 @@ __device__ inline void short_scout(const ChainArgs &a, char *lds, int chain, int
     // per lane: the row of step (window start + lane), for the window being written (A), the next (B) and the one after (C)
     // (as loaded: a difference taken here would wait for the loads, and with them for every row on its way)
     struct Window { int64_t lo, end; float y; };
-    // (past the chain's end the row of its last step once more: such a step adds 0 times its row, which must be a row
-    // the chain has visited, since 0 times a NaN is one)
     auto load_window = [&](int64_t w) {
-        const int64_t at = w * kWave + lane;
-        const uint64_t step = (uint64_t)(step0 + (at < n ? at : n - 1));
+        const uint64_t step = (uint64_t)(step0 + w * kWave + lane);
         const uint32_t row = a.perm ? a.perm[shard_position((uint32_t)chain, (uint32_t)a.k, step, (uint32_t)a.m)]
                                     : sample_row(a.seed_lo, a.seed_hi, (uint32_t)chain, step, (uint32_t)a.m);
         Window t;
@@ -250,6 +248,9 @@ __device__ inline void short_scout(const ChainArgs &a, char *lds, int chain, int
                     prev.tail = tail; prev.real = in; prev.now = now; prev.sa = sa; prev.sb = sb; prev.who = who;
                     if (u == kG - 1) {           // the section's marks go out together, before its barrier
                         settle(u);
+                        // The chain ends in this section: its last group and those behind it go step by step, and a step behind the
+                        // end is left out, whatever its row holds (0 times a NaN is one).
+                        if (i == nsections - 1) turn_bits |= ~0u << (int)((a.nsteps[blockIdx.x] - i * (kG * kShortRows)) / kShortRows);
                         if (lane < kG)
                             reinterpret_cast<StepRow *>(sec + lane * kGroupBytes + kWave * 16 + 16)->pad =
                                 (int32_t)(((stale_bits >> lane) & 1u) * kStale + ((turn_bits >> lane) & 1u) * kInTurn);
@@ -351,6 +352,7 @@ __device__ inline void short_worker(const ChainArgs &a, char *lds, TV *v, int64_
                     const StepRow row = *reinterpret_cast<const StepRow *>(cur + u * kGroupBytes + kWave * 16 + t * kShortScalars + 16);
                     const StepScalars<TV> sc = *reinterpret_cast<const StepScalars<TV> *>(cur + u * kGroupBytes + kWave * 16 + t * kShortScalars);
                     const int len = __builtin_amdgcn_readfirstlane(row.len);
+                    if (__builtin_amdgcn_ballot_w64(sc.cs != (TV)0) == 0) continue;      // behind the chain's end
                     if (len <= kShortLen) {
                         const uint32_t off = r == t ? rec[u][2] : 0xFFFFFFF0u;
                         TV now = *reinterpret_cast<const TV *>(lds + rec[u][1]);
