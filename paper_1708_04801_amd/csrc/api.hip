@@ -238,9 +238,9 @@ static int resolve_plan(const wpsgd_matrix *X, int k, wpsgd_loss loss, const wps
         // per 1024-thread workgroup, cut each chain into as many column slices as there are compute
         // units for (the widest workload: 8 slices of 8192 columns run 3 times as fast as one
         // workgroup of 1024; with fp64 state that row length has no one-workgroup shape at all).
-        // bf16 rows of 8193 to 16384 elements fit 256 threads, but with 64 elements each: six slices take 0.72 us per step
-        // instead of 1.48 (hinge) and 0.61 instead of 0.74 (logistic, which two slices would slow down to 0.77, and which has
-        // to earn back the start of the slices: 50 steps 47 us in one piece, 53 in six).
+        // bf16 rows of 8193 to 16384 elements fit 256 threads, but with 64 elements each: eight chains at d = 16384 take 0.58 us
+        // per step in slices instead of 1.73 (hinge) and 0.35 instead of 0.63 (logistic, which two slices would slow down, and
+        // which has to earn back the start of the slices: d = 8200, 50 steps 47 us in one piece, 53 in six).
         const bool crowded = have && found.threads == 256 && found.ept >= 64 && !(loss == WPSGD_LOGISTIC && max_steps > 0 && max_steps < 128);
         if (f.slices == 0 && !f.threads && !f.block_steps && !f.prefetch && !f.rows && (!have || found.threads == 1024 || crowded)) {
             for (int c = 8; c >= (crowded && loss == WPSGD_LOGISTIC ? 3 : 2); --c) {
