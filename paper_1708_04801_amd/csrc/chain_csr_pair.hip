@@ -1,5 +1,5 @@
 // Sparse-row (CSR) SGD chains, three wavefronts per chain.  (Matrices whose rows have at most 16 entries
-// run four steps at a time instead: chain_csr_short.h.)
+// and seldom share columns run four steps at a time instead: chain_csr_short.h.)
 //
 // A step of a sparse chain is a short dependent recursion (gather the model at the row's columns,
 // reduce, decide, scatter), and one wavefront issues one instruction at a time: with a single

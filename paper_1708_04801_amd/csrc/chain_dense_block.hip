@@ -24,8 +24,8 @@
 // are a chain of comparison, scalar test and selection each); with fp64 rows of more than 128 elements the matrix
 // products (a quarter of them, for timing only: 0.129 -> 0.103 us per step at d = 256; a fourth scout, which shares
 // wave 0's fp64 unit, gave nothing, nor did deciding two slopes at a time for both outcomes of the first).
-// us per step, eight chains, one step at a time -> blocks: hinge d = 64 0.112 -> 0.061, d = 128 0.135 -> 0.081, d = 256
-// 0.135 -> 0.132; logistic 0.092 -> 0.052, 0.107 -> 0.057, 0.107 -> 0.085; bf16 d = 256 0.165 -> 0.136 and 0.138 -> 0.091.
+// us per step, eight chains, one step at a time -> blocks: hinge d = 64 0.110 -> 0.062, d = 128 0.133 -> 0.079; logistic 0.090 ->
+// 0.050, d = 256 0.104 -> 0.090; bf16 d = 256 0.162 -> 0.110, logistic (64 chains) 0.132 -> 0.098.
 #include <type_traits>
 
 #include "device_utils.h"
@@ -184,8 +184,7 @@ __global__ __launch_bounds__(kBlockThreads) void chain_dense_block_kernel(ChainA
         // The block has a row that is not finite (or too large for fp32 products).  Two terms of an infinite product may
         // have different signs, and a step that is not taken still adds 0 times its row, so products must not be split
         // into v.x and Gram terms: from here on, on data no model is learnt from, one step is taken after the other.
-        // (The look-out for such rows, us per step at eight chains: hinge none to 2 %, logistic none up to d = 128 and 0.088 ->
-        // 0.094 at d = 256.)
+        // (The look-out for such rows, at eight chains: hinge d = 64 2 %, logistic d = 256 3 %, none elsewhere.)
         for (; b < nblk; ++b) {
             if ((b % kBlocksPerWindow) == 0 && b > 0) {
                 s_w *= rho64;
