@@ -20,12 +20,13 @@
 // rows one block (of its own) ahead and fills section (block mod 2) in its last block time, while wave 0 is
 // at the block before; wave 0 is S blocks behind the first scout.  All waves pass the same number of barriers.
 //
-// What bounds it: wave 0's dependent instructions (308 a block at d = 64, fp64, in some 2300 cycles; the sixteen slopes
-// are a chain of comparison, scalar test and selection each); with fp64 rows of more than 128 elements the matrix
-// products (a quarter of them, for timing only: 0.129 -> 0.103 us per step at d = 256; a fourth scout, which shares
-// wave 0's fp64 unit, gave nothing, nor did deciding two slopes at a time for both outcomes of the first).
-// us per step, eight chains, one step at a time -> blocks: hinge d = 64 0.110 -> 0.062, d = 128 0.133 -> 0.079; logistic 0.090 ->
-// 0.050, d = 256 0.104 -> 0.090; bf16 d = 256 0.162 -> 0.110, logistic (64 chains) 0.132 -> 0.098.
+// What bounds it: wave 0's dependent instructions (a step is its slope and one multiply-add that fetches the slope from its
+// lane, some 40 cycles; reading the slope into a scalar register, testing it there and selecting cost 50 to 60: us per step, eight
+// chains, hinge d = 64 0.062 -> 0.054, d = 128 0.078 -> 0.070, logistic d = 64 0.050 -> 0.0445); with fp64 rows of more than 128
+// elements the matrix products (a quarter of them, for timing only: 0.129 -> 0.103 at d = 256; a fourth scout, which shares
+// wave 0's vector unit, gave nothing: fp64 and fp32 matrix products keep it to themselves).
+// us per step, eight chains, one step at a time -> blocks: hinge d = 64 0.110 -> 0.054, d = 128 0.133 -> 0.070; logistic 0.090 ->
+// 0.0445, d = 256 0.104 -> 0.090; bf16 d = 256 0.162 -> 0.110, logistic (64 chains) 0.132 -> 0.098.
 #include <type_traits>
 
 #include "device_utils.h"
@@ -153,25 +154,9 @@ __global__ __launch_bounds__(kBlockThreads) void chain_dense_block_kernel(ChainA
             p = merge_values<false>(p, p);    // the four quarters of the columns: every lane ends with the whole sum
             p = merge_values<true>(p, p);
             TV q = zs * p, c[kBlock];
-            if constexpr (LOSS == kLossHinge) {
-                uint32_t fired = 0;
+            const TV mine = cs * take_block_steps<LOSS>(q, gram);
 #pragma unroll
-                for (int t = 0; t < kBlock; ++t) {
-                    const TV moved = q + gram[t];
-                    const bool fires = ((uint32_t)__builtin_amdgcn_ballot_w64(q < 1.0) >> t) & 1u;
-                    q = fires ? moved : q;
-                    fired |= fires ? (1u << t) : 0u;
-                }
-                const TV mine = ((fired >> j) & 1u) ? cs : 0.0;
-#pragma unroll
-                for (int t = 0; t < kBlock; ++t) c[t] = lane_read(mine, t);
-            } else {
-#pragma unroll
-                for (int t = 0; t < kBlock; ++t) {
-                    c[t] = lane_read(cs * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(q)), t);
-                    q += c[t] * gram[t];
-                }
-            }
+            for (int t = 0; t < kBlock; ++t) c[t] = lane_read(mine, t);
 #pragma unroll
             for (int t = 0; t < kBlock; ++t)
 #pragma unroll
@@ -357,9 +342,8 @@ __global__ __launch_bounds__(kBlockThreads) void chain_dense_block_kernel(ChainA
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int t = Gram<TV>::row(r, lane);
-            // (the hinge adds a step whole or not at all: its coefficient goes in here)
-            if constexpr (LOSS == kLossHinge) sec.gram[t][j] = zs * __shfl(cs, t) * gram.d[r];
-            else sec.gram[t][j] = zs * gram.d[r];
+            const TV unit = zs * __shfl(cs, t) * gram.d[r];        // (in every lane: a lane that stands aside has nothing to give)
+            sec.gram[t][j] = t < j ? unit : (TV)0;
         }
         section_barrier();
         if (++beat == beats) break;

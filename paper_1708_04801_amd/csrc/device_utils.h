@@ -359,6 +359,41 @@ __device__ inline double lane_read(double t, int j)
     return __longlong_as_double(lane_read_i64(__double_as_longlong(t), j));
 }
 
+// acc += (x of lane T of the row of sixteen lanes) * y, one instruction.  (A DPP operand written by the instruction before needs
+// two wait states; fp64 instructions know this DPP control only.)
+template <int T>
+__device__ inline void fma_from_lane(float &acc, float x, float y)
+{
+    asm volatile("s_nop 1\n\tv_fmac_f32_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(x), "v"(y), "n"(T));
+}
+template <int T>
+__device__ inline void fma_from_lane(double &acc, double x, double y)
+{
+    asm volatile("s_nop 1\n\tv_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(x), "v"(y), "n"(T));
+}
+
+// The dependent steps of a block of N <= 16 rows, in every row of sixteen lanes: lane j holds q = y_j yhat_j (times log2 e for the logistic
+// loss) without the block's own steps; own[a][j] is what step a adds to it per unit of slope (0 for a >= j, so that q stays once
+// step j is taken).  Per step: the slope in all lanes, of which lane a's is the right one, and a multiply-add that fetches it from there.
+// Returns the slopes, step j's in lane j.
+template <int LOSS, typename TV>
+__device__ inline TV unit_slope(TV q)
+{
+    if constexpr (LOSS == kLossHinge) return q < 1.0 ? 1.0 : 0.0;
+    else return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(q));
+}
+template <int LOSS, int N, int T = 0, typename TV>
+__device__ inline TV take_block_steps(TV &q, const TV (&own)[N])
+{
+    const TV u = unit_slope<LOSS>(q);
+    if constexpr (T + 1 < N) {
+        fma_from_lane<T>(q, u, own[T]);
+        return take_block_steps<LOSS, N, T + 1>(q, own);
+    } else {
+        return u;
+    }
+}
+
 // bfloat16 is the upper half of a binary32: widening is a shift.
 __device__ inline float bf16_lo(uint32_t packed) { return __uint_as_float(packed << 16); }
 __device__ inline float bf16_hi(uint32_t packed) { return __uint_as_float(packed & 0xFFFF0000u); }
