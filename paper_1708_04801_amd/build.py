@@ -35,6 +35,7 @@ UNITS = [
     ("objective", "objective.hip", []),
     ("chain_dense_mem", "chain_dense_mem.hip", []),
     ("chain_dense_block", "chain_dense_block.hip", []),
+    ("chain_dense_pipe", "chain_dense_pipe.hip", []),
     ("chain_delay", "chain_delay.hip", []),
     ("chain_csr", "chain_csr.hip", []),
     ("chain_csr_pair", "chain_csr_pair.hip", []),

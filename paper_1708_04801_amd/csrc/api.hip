@@ -281,6 +281,19 @@ static int resolve_plan(const wpsgd_matrix *X, int k, wpsgd_loss loss, const wps
             found.scouts = 3;
             found.state_bytes_per_elem = 0;
             have = true;
+            // With everything but the slopes off the dependent path a block takes half to two thirds of the time where a chain has a
+            // compute unit to itself, but twice the matrix products: fp64 ones (hinge) bind rows of more than 64 elements, and so does a
+            // second chain on the unit, which bf16 products and short fp32 rows leave room for.  Lines (us, blocks | pipelined, longest
+            // chain of so many steps): d = 64 hinge, one chain, 200 29.8 | 29.0, 1000 68.8 | 63.5, 512 chains of 1000 90 | 103; d = 128 hinge
+            // 85.6 | 86.0; logistic d = 64, 32 20.3 | 19.6, 1000 59.1 | 46.8, 512 chains of 200 42.4 | 40.4, of 32 32.0 | 35.0, 1024 chains of
+            // 1000 97 | 116; d = 128, 50 22.3 | 22.8, 300 34.6 | 32.4, 512 chains of 300 54.0 | 51.6; d = 256, 50 22.8 | 24.9, 300 48.0 | 41.5, 512 chains of
+            // 300 60.6 | 76.0; bf16 logistic d = 256, 50 24.7 | 23.0, 1000 103.5 | 62.4, 512 chains of 50 37.9 | 43.7, of 300 69.8 | 61.2.
+            const bool light = loss == WPSGD_LOGISTIC && X->dtype == WPSGD_BF16;
+            int64_t pipe_worth = 0;                      // steps of the longest chain from which it pays; 0: it does not
+            if (loss == WPSGD_HINGE) pipe_worth = X->d <= 64 && k <= compute_units() ? 200 : 0;
+            else if (k <= compute_units()) pipe_worth = light || X->d <= 64 ? 32 : X->d <= 128 ? 100 : 160;
+            else if (k <= 2 * compute_units()) pipe_worth = X->d <= 64 || (light && X->d <= 128) ? 200 : light || X->d <= 128 ? 300 : 0;
+            found.pipelined = pipe_worth > 0 && max_steps >= pipe_worth;
         }
         if (have) {
             *out = found;
@@ -467,14 +480,18 @@ int wpsgd_describe_plan(const wpsgd_matrix *X, int k, wpsgd_loss loss, const wps
     if (hp > 0) std::snprintf(helped, sizeof(helped), " helpers=%d", hp);
     if (p.family == Family::DenseReg && p.slices > 1) std::snprintf(helped, sizeof(helped), " slices=%d", p.slices);
     if (p.scouts > 0) std::snprintf(helped, sizeof(helped), " scouts=%d", p.scouts);
+    // (the steps of a call are not known here: what long chains run on instead)
+    char longer[32] = "";
+    Plan steady;
+    if (resolve_plan(X, k, loss, plan, &steady, 1.0, INT32_MAX) == WPSGD_OK && steady.pipelined) std::snprintf(longer, sizeof(longer), " long=pipelined");
     char load[16] = "";                  // rows of single elements that are fetched several at a time all the same
     if (p.vec > p.align && p.scouts == 0) std::snprintf(load, sizeof(load), " load=%d", p.vec);
-    std::snprintf(buf, buf_bytes, "%s %s %s nt=%d ept=%d vec=%d%s B=%d P=%d state=%s%s%s",
+    std::snprintf(buf, buf_bytes, "%s %s %s nt=%d ept=%d vec=%d%s B=%d P=%d state=%s%s%s%s",
                   family_name(p.family), p.dtype == WPSGD_BF16 ? "bf16" : "f32",
                   p.loss == WPSGD_HINGE ? "hinge" : "logistic", p.threads, p.ept, std::min(p.vec, p.align), load,
                   p.block_steps, p.prefetch,
                   p.state_bytes_per_elem == 0 ? "registers" : (p.state_bytes_per_elem == 8 ? "hbm-f64" : "hbm-f32"),
-                  p.family == Family::DenseReg ? kRows[p.rows] : "", helped);
+                  p.family == Family::DenseReg ? kRows[p.rows] : "", helped, longer);
     return WPSGD_OK;
 }
 
@@ -501,7 +518,9 @@ static SlicedLaunchOrder g_sliced;
 static hipError_t launch_whole(Plan p, const ChainArgs &a, hipStream_t s)
 {
     switch (p.family) {
-    case Family::DenseReg: return p.scouts > 0 ? launch_dense_block(p, a, s) : dense_reg_dispatch(p, &a, s);
+    case Family::DenseReg:
+        if (p.pipelined) return launch_dense_pipe(p, a, s);
+        return p.scouts > 0 ? launch_dense_block(p, a, s) : dense_reg_dispatch(p, &a, s);
     case Family::DenseMem: return launch_dense_mem(p, a, s);
     default: return launch_csr(p, a, s);
     }

@@ -93,7 +93,8 @@ __global__ __launch_bounds__(kBlockThreads) void chain_dense_block_kernel(ChainA
     __shared__ __attribute__((aligned(16))) TV model[C];
     // does block b (in word b mod 4) hold an element whose products with others may not be finite?
     __shared__ uint32_t excess[4];
-    constexpr float kProbe = LOSS == kLossHinge ? 0.0f : 0x1p70f;        // (fp64 products of fp32 numbers do not overflow; 256 fp32 squares of less than 2^58 do not)
+    // (fp64 products of fp32 numbers do not overflow; 256 fp32 squares of less than 2^32 do not, nor with the coefficients eta/s, s >= 2^-30, on them)
+    constexpr float kProbe = LOSS == kLossHinge ? 0.0f : 0x1p96f;
 
     const int lane = (int)(threadIdx.x & (kWave - 1));
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);

@@ -22,13 +22,13 @@ __host__ __device__ inline uint32_t mul_hi_u32(uint32_t a, uint32_t b)
     return (uint32_t)(((uint64_t)a * (uint64_t)b) >> 32);   // lowers to v_mul_hi_u32 on the GPU
 }
 
-__host__ __device__ inline uint32_t philox4x32_10_word0(uint32_t c0, uint32_t c1, uint32_t c2,
-                                                        uint32_t c3, uint32_t k0, uint32_t k1)
+__host__ __device__ inline void philox4x32_rounds(uint32_t &c0, uint32_t &c1, uint32_t &c2, uint32_t &c3, uint32_t &k0, uint32_t &k1,
+                                                  int rounds)
 {
     constexpr uint32_t M0 = 0xD2511F53u, M1 = 0xCD9E8D57u;
     constexpr uint32_t W0 = 0x9E3779B9u, W1 = 0xBB67AE85u;
 #pragma unroll
-    for (int r = 0; r < 10; ++r) {
+    for (int r = 0; r < rounds; ++r) {
         const uint32_t hi0 = mul_hi_u32(M0, c0), lo0 = M0 * c0;
         const uint32_t hi1 = mul_hi_u32(M1, c2), lo1 = M1 * c2;
         c0 = hi1 ^ c1 ^ k0;
@@ -38,6 +38,12 @@ __host__ __device__ inline uint32_t philox4x32_10_word0(uint32_t c0, uint32_t c1
         k0 += W0;
         k1 += W1;
     }
+}
+
+__host__ __device__ inline uint32_t philox4x32_10_word0(uint32_t c0, uint32_t c1, uint32_t c2,
+                                                        uint32_t c3, uint32_t k0, uint32_t k1)
+{
+    philox4x32_rounds(c0, c1, c2, c3, k0, k1, 10);
     return c0;
 }
 
@@ -372,6 +378,20 @@ __device__ inline void fma_from_lane(double &acc, double x, double y)
     asm volatile("s_nop 1\n\tv_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(x), "v"(y), "n"(T));
 }
 
+// both at once: one wait for x
+template <int T>
+__device__ inline void fma2_from_lane(float &a, float &b, float x, float ya, float yb)
+{
+    asm volatile("s_nop 1\n\tv_fmac_f32_dpp %0, %2, %3 row_newbcast:%5 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f32_dpp %1, %2, %4 row_newbcast:%5 row_mask:0xf bank_mask:0xf" : "+v"(a), "+v"(b) : "v"(x), "v"(ya), "v"(yb), "n"(T));
+}
+template <int T>
+__device__ inline void fma2_from_lane(double &a, double &b, double x, double ya, double yb)
+{
+    asm volatile("s_nop 1\n\tv_fmac_f64_dpp %0, %2, %3 row_newbcast:%5 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f64_dpp %1, %2, %4 row_newbcast:%5 row_mask:0xf bank_mask:0xf" : "+v"(a), "+v"(b) : "v"(x), "v"(ya), "v"(yb), "n"(T));
+}
+
 // The dependent steps of a block of N <= 16 rows, in every row of sixteen lanes: lane j holds q = y_j yhat_j (times log2 e for the logistic
 // loss) without the block's own steps; own[a][j] is what step a adds to it per unit of slope (0 for a >= j, so that q stays once
 // step j is taken).  Per step: the slope in all lanes, of which lane a's is the right one, and a multiply-add that fetches it from there.
@@ -390,6 +410,19 @@ __device__ inline TV take_block_steps(TV &q, const TV (&own)[N])
         fma_from_lane<T>(q, u, own[T]);
         return take_block_steps<LOSS, N, T + 1>(q, own);
     } else {
+        return u;
+    }
+}
+// the same, and next[j] += what the steps add to the q of the block behind this one
+template <int LOSS, int N, int T = 0, typename TV>
+__device__ inline TV take_block_steps(TV &q, const TV (&own)[N], TV &next, const TV (&cross)[N])
+{
+    const TV u = unit_slope<LOSS>(q);
+    if constexpr (T + 1 < N) {
+        fma2_from_lane<T>(q, next, u, own[T], cross[T]);
+        return take_block_steps<LOSS, N, T + 1>(q, own, next, cross);
+    } else {
+        fma_from_lane<T>(next, u, cross[T]);
         return u;
     }
 }

@@ -95,6 +95,7 @@ struct Plan {
     int rows;        // DenseReg: 1 rows wait in registers, 2 next row staged in LDS, 3 rows streamed twice
     int slices;      // DenseReg, rows = 1: workgroups (column slices) per chain
     int scouts;      // DenseReg: waves beside the chain's own that prepare blocks of 16 steps (chain_dense_block.hip); 0: none
+    bool pipelined;  // DenseReg with scouts: everything but the slopes off the dependent path (chain_dense_pipe.hip)
     size_t state_bytes_per_elem;   // 0 when the state lives in registers
 };
 
@@ -103,6 +104,7 @@ hipError_t launch_dense_reg(const Plan &p, const ChainArgs &a, hipStream_t s);
 // chains of short rows, sixteen steps per block (rows of at least four elements: the kernel reads four at a time)
 constexpr int kBlockMinColumns = 4, kBlockMaxColumns = 256;
 hipError_t launch_dense_block(const Plan &p, const ChainArgs &a, hipStream_t s);
+hipError_t launch_dense_pipe(const Plan &p, const ChainArgs &a, hipStream_t s);
 hipError_t launch_dense_mem(const Plan &p, const ChainArgs &a, hipStream_t s);
 hipError_t launch_csr(const Plan &p, const ChainArgs &a, hipStream_t s);
 hipError_t launch_csr_pair(const Plan &p, const ChainArgs &a, hipStream_t s);   // two waves per chain
