@@ -13,7 +13,7 @@
 #include <atomic>
 #include <type_traits>
 
-#include "device_utils.h"
+#include "dense_rows.h"
 #include "internal.h"
 
 namespace wpsgd {
@@ -227,7 +227,7 @@ __global__ __launch_bounds__(kObjThreads) void objective_short_rows_kernel(const
 // cycle, from LDS many.  HEAD > 0: the model's first HEAD columns are copied to LDS and only the others are gathered from
 // memory (lanes that need none ask for an offset past the end, which is no access), if at least a quarter of the sampled
 // entries, one per thread, lie there.  A million rows of 80 entries, 2^20 columns (Zipf): 0.41 -> 0.31 ms (2.1 TB/s), the
-// same without the copy 0.41; half a million rows of 40, logistic: 225 -> 70 us.
+// same without the copy 0.41, with four entries a load 0.27, of which the gathers from memory take 0.11: a line of L2 each; half a million rows of 40, logistic: 225 -> 70 us.
 // Long rows take the whole wave, since with 16 lanes a row keeps a quarter as much on its way: one by one inside a batch
 // (one row of 100000 entries among 200000 of 20: 1530 us with 16 lanes, 322 with 64), and one row per wave throughout where
 // the average row is long, where rows are so few that each may have a wave, or where no head is used (1000 rows of
@@ -331,24 +331,28 @@ void objective_csr_kernel(const int64_t *row_ptr, const int32_t *col_idx,
             if constexpr (AHEAD) ask_lane(row0 + nwaves * batch);
             double held = 0.0;
             if (entries > 0) {
+                // A lane takes four entries that follow each other with one load for the columns and one for the values, a quarter of
+                // the instructions of single entries (a million rows of 80, Zipf: 313 -> 272 us; of 110, 433 -> 369; of 8, 85 | 86).  The loads
+                // are checked against the arrays' end, dword by dword, and count from the batch's first entry; a batch too long
+                // for their 32-bit offsets goes row by row.
+                const int64_t base = lane_read_i64(lo, 0);
+                const bool near_rows = lane_read_i64(lo, kWave - 1) + __builtin_amdgcn_readlane(len, kWave - 1) - base < (1 << 28);
+                const uint32_t room = (uint32_t)min(first + entries - base, (int64_t)(1 << 29)) * 4u;
+                const __amdgpu_buffer_rsrc_t cres = make_rsrc(col_idx + base, room), vres = make_rsrc(vals + base, room);
+                const uint32_t mine = (uint32_t)(lo - base);
                 for (int it = 0; it < turns; ++it) {
                     const int from = it * ROWS + r;
-                    const int64_t p0 = (int64_t)(((uint64_t)(uint32_t)__shfl((int)(lo >> 32), from) << 32) | (uint32_t)__shfl((int)(uint32_t)lo, from));
-                    const int whole = __shfl(len, from), n = whole > kLongRow ? 0 : whole;
+                    const uint32_t p0 = (uint32_t)__shfl((int)mine, from);
+                    const int whole = __shfl(len, from), n = whole > kLongRow || !near_rows ? 0 : whole;
                     double acc = 0.0;
                     for (int e0 = 0; __any(e0 < n); e0 += kAtOnce * LPR) {
-                        uint32_t col[kAtOnce];
-                        float val[kAtOnce], wv[kAtOnce];
+                        const int e = e0 + kAtOnce * c;
+                        const uint32_t off = e < n ? (p0 + (uint32_t)e) * 4u : 0xFFFFFFF0u;
+                        const u32x4 col = __builtin_amdgcn_raw_buffer_load_b128(cres, off, 0, 0), val = __builtin_amdgcn_raw_buffer_load_b128(vres, off, 0, 0);
+                        float wv[kAtOnce];
 #pragma unroll
                         for (int i = 0; i < kAtOnce; ++i) {
-                            const int e = e0 + i * LPR + c;
-                            const int64_t p = e < n ? p0 + e : first;          // (that entry exists)
-                            col[i] = (uint32_t)col_idx[p];
-                            val[i] = vals[p];
-                        }
-#pragma unroll
-                        for (int i = 0; i < kAtOnce; ++i) {
-                            const bool in = e0 + i * LPR + c < n;
+                            const bool in = e + i < n;
                             if constexpr (COPIED) {
                                 const bool near = col[i] < (uint32_t)HEAD;
                                 const float far = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(wres, in && !near ? col[i] * 4u : 0xFFFFFFF0u, 0, 0));
@@ -358,18 +362,18 @@ void objective_csr_kernel(const int64_t *row_ptr, const int32_t *col_idx,
                             }
                         }
 #pragma unroll
-                        for (int i = 0; i < kAtOnce; ++i) acc += e0 + i * LPR + c < n ? (double)wv[i] * (double)val[i] : 0.0;
+                        for (int i = 0; i < kAtOnce; ++i) acc += e + i < n ? (double)wv[i] * (double)__uint_as_float(val[i]) : 0.0;
                     }
                     acc += dpp_move<0xB1, 0xF>(acc);
                     acc += dpp_move<0x4E, 0xF>(acc);
                     acc += dpp_move<0x141, 0xF>(acc);
                     acc += dpp_move<0x140, 0xF>(acc);
                     held = c == it ? acc : held;
-                    uint64_t longer = __builtin_amdgcn_ballot_w64(whole > kLongRow && c == 0);
+                    uint64_t longer = __builtin_amdgcn_ballot_w64((whole > kLongRow || (!near_rows && whole > 0)) && c == 0);
                     while (__builtin_expect(longer != 0, 0)) {                // (one bit per such row, at its first lane)
                         const int at = __builtin_ctzll(longer);
                         longer &= longer - 1;
-                        const double yhat = whole_row(lane_read_i64(p0, at), __builtin_amdgcn_readlane(whole, at));
+                        const double yhat = whole_row(lane_read_i64(lo, it * ROWS + at / LPR), __builtin_amdgcn_readlane(whole, at));
                         held = c == it && r == at / LPR ? yhat : held;
                     }
                 }

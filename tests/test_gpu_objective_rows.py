@@ -126,3 +126,30 @@ def test_long_sparse_rows_keep_a_wave_busy():
     lens = np.full(200000, 20)
     lens[100000] = 100000
     assert _best_us(*_sparse(lens, d)[:3])[0] <= 650.0
+
+
+@pytest.mark.parametrize("m,mean", [(37, 5), (5000, 3), (401000, 9), (401000, 70), (1000, 200)])
+def test_sparse_rows_four_entries_a_lane(m, mean):
+    """Rows of 0 to 3 * mean entries from any entry of the arrays on, the last one at the arrays' end; the first row_ptr is not zero."""
+    d, rng = 5000, np.random.default_rng(m + mean)
+    lens = np.minimum(rng.integers(0, 3 * mean, m), rng.integers(0, 3 * mean, m))
+    lens[-1] = mean
+    skip = 3
+    row_ptr = np.zeros(m + 1, dtype=np.int64)
+    np.cumsum(lens, out=row_ptr[1:])
+    nnz = int(row_ptr[-1])
+    gap = rng.integers(1, d // (3 * mean), nnz).astype(np.int64)
+    total = np.concatenate([[0], np.cumsum(gap)])
+    col = (total[1:] - np.repeat(total[row_ptr[:-1]], lens) - 1).astype(np.int32)
+    val = rng.standard_normal(nnz).astype(np.float32)
+    w = rng.standard_normal(d).astype(np.float32)
+    y = np.where(rng.random(m) < 0.5, 1.0, -1.0).astype(np.float32)
+    cg = torch.from_numpy(np.concatenate([np.full(skip, d - 1, np.int32), col])).cuda()
+    vg = torch.from_numpy(np.concatenate([np.full(skip, np.nan, np.float32), val])).cuda()
+    X = api.Matrix(m, d, row_ptr=torch.from_numpy(row_ptr + skip).cuda(), col_idx=cg, vals=vg)
+    got = api.wpsgd_objective(X, torch.from_numpy(y).cuda(), torch.from_numpy(w).cuda(), 0.1, wl.HINGE).cpu().numpy()
+    prod = np.concatenate([[0.0], np.cumsum(w[col].astype(np.float64) * val.astype(np.float64))])
+    yhat = prod[row_ptr[1:]] - prod[row_ptr[:-1]]
+    ref = 0.05 * float(w.astype(np.float64) @ w) + np.maximum(0.0, 1.0 - y * yhat).mean()
+    # running sums of nnz terms of size 1: nnz^1.5 * 1e-16 at most, over the mean of m losses of size 1 and more
+    assert abs(got[0] - ref) <= 1e-9 * ref
