@@ -36,6 +36,7 @@ UNITS = [
     ("chain_dense_mem", "chain_dense_mem.hip", []),
     ("chain_dense_block", "chain_dense_block.hip", []),
     ("chain_dense_pipe", "chain_dense_pipe.hip", []),
+    ("chain_dense_octet", "chain_dense_octet.hip", []),
     ("chain_delay", "chain_delay.hip", []),
     ("chain_csr", "chain_csr.hip", []),
     ("chain_csr_pair", "chain_csr_pair.hip", []),

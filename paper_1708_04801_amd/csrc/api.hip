@@ -103,6 +103,11 @@ static int compute_units()
     return cus;
 }
 
+// Helper workgroups per chain of blocks of eight steps: a multiple of eight behind the chains, on compute units of the chain's XCD that no chain
+// occupies (one that has to wait for a compute unit is worse than none: d = 767, 84 chains, two helpers each: 33 workgroups for the 32 units of an XCD,
+// 0.147 us per step, as without).
+static int octet_helpers(int k) { return std::min(compute_units() / ((k + 7) / 8 * 8) - 1, 3); }
+
 static int resolve_plan(const wpsgd_matrix *X, int k, wpsgd_loss loss, const wpsgd_plan *force, Plan *out,
                         double rho = 1.0, int64_t max_steps = 0)
 {
@@ -296,6 +301,16 @@ static int resolve_plan(const wpsgd_matrix *X, int k, wpsgd_loss loss, const wps
             found.pipelined = pipe_worth > 0 && max_steps >= pipe_worth;
         }
         if (have) {
+            // Longer rows, fewer chains: blocks of eight steps whose products between rows two or three helper workgroups per chain form (chain_dense_octet.hip).
+            // One helper is too slow (us per step, rounds of two steps | blocks of eight, 128 chains: d = 1024 0.150 | 0.139, bf16 d = 2048 0.176 |
+            // 0.168, d = 512 0.120 | 0.132; 64 chains: 0.148 | 0.115, bf16 d = 2048 0.174 | 0.131).  Up to 512 columns the register kernel has one or two waves
+            // and there is little to gain (0.121 | 0.107, bf16 64 chains 0.129 | 0.129).  The start costs some 3 us more (us per call: d = 1024, 16 chains of
+            // 64 steps 27.3 | 28.2, of 150 38.8 | 37.3, 64 chains of 200 44.5 | 45.1; bf16 d = 2048, 64 chains of 200 52.6 | 50.6).
+            // (found above holds what runs where the workspace has no room for records)
+            found.octets = found.family == Family::DenseReg && found.scouts == 0 && found.slices == 1 && loss == WPSGD_LOGISTIC &&
+                           X->d >= kOctetMinColumns && X->d <= octet_max_columns((int)X->dtype) && wide == (X->dtype == WPSGD_BF16 ? 8 : 4) &&
+                           octet_helpers(k) >= 2 && max_steps >= (k <= 32 ? 192 : 256) &&
+                           !f.threads && !f.block_steps && !f.prefetch && !f.rows && !f.slices && !f.helpers;
             *out = found;
             return WPSGD_OK;
         }
@@ -356,6 +371,7 @@ static size_t slice_table_words(int k) { return (size_t)k * (8 * 2 * 32 + 8); }
 // them, and only on compute units no chain occupies (at most 128 chains).
 static int helpers_per_chain(const Plan &p, const wpsgd_matrix *X, int k, const wpsgd_plan *force)
 {
+    if (p.octets) return octet_helpers(k);
     if (p.family != Family::DenseReg || p.threads != 256 || p.rows != 1 || k > 128 || p.slices > 1) return 0;
     const int asked = force ? force->helpers : 0;
     if (asked < 0) return 0;
@@ -483,7 +499,8 @@ int wpsgd_describe_plan(const wpsgd_matrix *X, int k, wpsgd_loss loss, const wps
     // (the steps of a call are not known here: what long chains run on instead)
     char longer[32] = "";
     Plan steady;
-    if (resolve_plan(X, k, loss, plan, &steady, 1.0, INT32_MAX) == WPSGD_OK && steady.pipelined) std::snprintf(longer, sizeof(longer), " long=pipelined");
+    if (resolve_plan(X, k, loss, plan, &steady, 1.0, INT32_MAX) == WPSGD_OK && (steady.pipelined || steady.octets))
+        std::snprintf(longer, sizeof(longer), steady.pipelined ? " long=pipelined" : " long=octets");
     char load[16] = "";                  // rows of single elements that are fetched several at a time all the same
     if (p.vec > p.align && p.scouts == 0) std::snprintf(load, sizeof(load), " load=%d", p.vec);
     std::snprintf(buf, buf_bytes, "%s %s %s nt=%d ept=%d vec=%d%s B=%d P=%d state=%s%s%s%s",
@@ -519,6 +536,7 @@ static hipError_t launch_whole(Plan p, const ChainArgs &a, hipStream_t s)
 {
     switch (p.family) {
     case Family::DenseReg:
+        if (p.octets) return launch_dense_octet(p, a, s);
         if (p.pipelined) return launch_dense_pipe(p, a, s);
         return p.scouts > 0 ? launch_dense_block(p, a, s) : dense_reg_dispatch(p, &a, s);
     case Family::DenseMem: return launch_dense_mem(p, a, s);
@@ -590,6 +608,9 @@ static int run_chains_from(const wpsgd_matrix *X, const float *y, int k, const i
     const size_t need = h.total + perm_bytes(X->m) + align256(behind);
     if (!workspace || ((uintptr_t)workspace % 256) != 0) return WPSGD_INVALID_ARG;
     if (workspace_bytes < need) return WPSGD_WORKSPACE_TOO_SMALL;
+    // (a caller that brings less than the query asks for, which the register kernels do not need, gets those)
+    const size_t ring = (size_t)k * kOctetRingRecords * 256;
+    if (p.octets && workspace_bytes < h.total + perm_bytes(X->m) + ring) p.octets = false;
     hipStream_t s = static_cast<hipStream_t>(stream);
 
     // longest chain first (stable, so equal lengths keep their order); order and step counts
@@ -677,12 +698,16 @@ static int run_chains_from(const wpsgd_matrix *X, const float *y, int k, const i
     a.state = state_dev;
 
     hipError_t e = hipSuccess;
+    if (p.octets) {
+        e = launch_zero_words(static_cast<uint32_t *>(state_dev), ring / sizeof(uint32_t), s);
+        if (e != hipSuccess) return hip_fail(e);
+    }
     for (int64_t span = 0; span < (spans ? spans->count : 1); ++span) {
         a.span = span;
         if (span > 0) {
             a.w_start = spans->average;
-            // the helpers' counters start at zero (the first time they come zeroed with the header)
-            if (a.helpers > 0) e = launch_zero_words(a.progress, (size_t)k * 2 + 16, s);
+            // the helpers' counters start at zero (the first time they come zeroed with the header; blocks of eight steps count on)
+            if (a.helpers > 0 && !p.octets) e = launch_zero_words(a.progress, (size_t)k * 2 + 16, s);
             if (e != hipSuccess) return hip_fail(e);
         }
         e = a.slices > 1 ? launch_sliced(p, a, s) : launch_whole(p, a, s);

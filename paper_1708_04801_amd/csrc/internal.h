@@ -96,6 +96,7 @@ struct Plan {
     int slices;      // DenseReg, rows = 1: workgroups (column slices) per chain
     int scouts;      // DenseReg: waves beside the chain's own that prepare blocks of 16 steps (chain_dense_block.hip); 0: none
     bool pipelined;  // DenseReg with scouts: everything but the slopes off the dependent path (chain_dense_pipe.hip)
+    bool octets;     // DenseReg: blocks of eight steps whose products between rows other workgroups form (chain_dense_octet.hip)
     size_t state_bytes_per_elem;   // 0 when the state lives in registers
 };
 
@@ -105,6 +106,12 @@ hipError_t launch_dense_reg(const Plan &p, const ChainArgs &a, hipStream_t s);
 constexpr int kBlockMinColumns = 4, kBlockMaxColumns = 256;
 hipError_t launch_dense_block(const Plan &p, const ChainArgs &a, hipStream_t s);
 hipError_t launch_dense_pipe(const Plan &p, const ChainArgs &a, hipStream_t s);
+// chains of longer rows, eight steps per block; per chain a ring of records of 256 bytes in xchg (zero at the call's start), which together
+// take no more than a model vector does
+constexpr int kOctetMinColumns = 513;
+constexpr int octet_max_columns(int dtype) { return dtype == WPSGD_BF16 ? 2048 : 1024; }
+constexpr int kOctetRingRecords = 8;
+hipError_t launch_dense_octet(const Plan &p, const ChainArgs &a, hipStream_t s);
 hipError_t launch_dense_mem(const Plan &p, const ChainArgs &a, hipStream_t s);
 hipError_t launch_csr(const Plan &p, const ChainArgs &a, hipStream_t s);
 hipError_t launch_csr_pair(const Plan &p, const ChainArgs &a, hipStream_t s);   // two waves per chain

@@ -1,0 +1,144 @@
+"""Logistic chains of longer rows, eight steps per block, whose products between rows other workgroups form: every way a row, a block, a
+window or a chain can end, against the oracle.  (The longest chain of a call decides whether this kernel runs: see the planner.)"""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import oracle as orc
+from paper_1708_04801_amd import api
+from paper_1708_04801_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+STEPS = np.array([0, 1, 7, 8, 9, 31, 32, 33, 63, 64, 65, 72, 128, 333], dtype=np.int64)
+TOL = 2e-5                         # fp32 state: some 300 roundings of 6e-8 an element
+SHAPES = [(False, d) for d in (513, 514, 515, 767, 1001, 1022, 1023, 1024)] + \
+         [(True, d) for d in (520, 1016, 1024, 2040, 2048)]
+
+
+def _data(m, d, bf16, seed):
+    rng = np.random.default_rng(seed)
+    X = (rng.standard_normal((m, d)) / math.sqrt(d)).astype(np.float32)
+    y = np.where(rng.random(m) < 0.5, 1.0, -1.0).astype(np.float32)
+    if bf16:
+        bits = wl.f32_to_bf16_bits(X)
+        return bits, torch.from_numpy(bits.view(np.int16)).cuda().view(torch.bfloat16), y
+    return X, torch.from_numpy(X).cuda(), y
+
+
+def _compare(W, ref, tol):
+    for i in range(len(ref)):
+        assert np.linalg.norm(W[i] - ref[i]) <= tol * max(np.linalg.norm(ref[i]), 1e-30), i
+
+
+@pytest.mark.parametrize("bf16,d", SHAPES)
+def test_every_row_end_and_chain_end(bf16, d):
+    host, dev, y = _data(200, d, bf16, d)
+    X, yg = api.Matrix(200, d, dense=dev), torch.from_numpy(y).cuda()
+    assert "long=octets" in api.wpsgd_describe_plan(X, len(STEPS), wl.LOGISTIC)
+    W = api.wpsgd_run_chains(X, yg, STEPS, 0.5, 1e-3, wl.LOGISTIC, 9)
+    _compare(W.cpu().numpy(), orc.run_chains(orc.Dense(host), y, STEPS, 0.5, 1e-3, wl.LOGISTIC, 9)[0], TOL)
+
+
+@pytest.mark.parametrize("d", [513, 700, 1024])
+def test_results_do_not_depend_on_the_helpers(d):
+    """Three helpers a chain and two: a chain of the same number takes the same steps and has the same bits, whichever
+    products were there in time."""
+    _, dev, y = _data(500, d, False, d)
+    X, yg = api.Matrix(500, d, dense=dev), torch.from_numpy(y).cuda()
+    runs = []
+    for k in (6, 6, 60, 80):
+        n = np.full(k, 700, dtype=np.int64)
+        runs.append(api.wpsgd_run_chains(X, yg, n, 0.5, 1e-3, wl.LOGISTIC, 9)[:6])
+    for W in runs[1:]:
+        assert torch.equal(W, runs[0])
+
+
+@pytest.mark.parametrize("sampling", [api.SAMPLE_STREAM, api.SAMPLE_SHARDS])
+def test_start_vector_offsets_shards_and_row_stride(sampling):
+    d, m = 601, 61                                # shares of four or five rows: a block runs round them
+    host, _, y = _data(m, d, False, 5)
+    padded = torch.zeros((m, d + 6), device="cuda")
+    padded[:, :d] = torch.from_numpy(host).cuda()
+    X, yg = api.Matrix(m, d, dense=padded[:, :d]), torch.from_numpy(y).cuda()
+    w0 = torch.linspace(-1.0, 1.0, d, device="cuda")
+    off = np.arange(len(STEPS), dtype=np.int64) * 37
+    args = (X, yg, STEPS, 0.3, 1e-2, wl.LOGISTIC, 3)
+    W = api.wpsgd_run_chains_from(*args, w_start=w0, step_offsets=off, sampling=sampling)
+    other = api.wpsgd_run_chains_from(*args, w_start=w0, step_offsets=off, sampling=sampling,
+                                      plan={"threads": 256, "block_steps": 1})
+    _compare(W.cpu().numpy(), other.cpu().numpy().astype(np.float64), TOL)
+    assert torch.equal(W[0], w0)
+
+
+def test_spans_are_runs_one_after_the_other():
+    d, m, k = 520, 300, 10
+    _, dev, y = _data(m, d, False, 6)
+    X, yg = api.Matrix(m, d, dense=dev), torch.from_numpy(y).cuda()
+    n = np.arange(k, dtype=np.int64) * 9 + 120
+    w = None
+    for s in range(4):
+        W = api.wpsgd_run_chains_from(X, yg, n, 0.4, 1e-3, wl.LOGISTIC, 3, w_start=w, step_offsets=n * s)
+        w = api.wpsgd_combine(W, api.wpsgd_weights(n, 0.4, 1e-3))
+    assert torch.equal(api.wpsgd_run_spans(X, yg, n, 4, 0.4, 1e-3, wl.LOGISTIC, 3), w)
+
+
+@pytest.mark.parametrize("d", [600, 1001])
+def test_scale_is_folded_at_every_window(d):
+    """eta*lambda = 0.4: the scale falls below 2^-30 within a window."""
+    host, dev, y = _data(64, d, False, 8)
+    X, yg = api.Matrix(64, d, dense=dev), torch.from_numpy(y).cuda()
+    W = api.wpsgd_run_chains(X, yg, STEPS, 0.8, 0.5, wl.LOGISTIC, 4).cpu().numpy()
+    _compare(W, orc.run_chains(orc.Dense(host), y, STEPS, 0.8, 0.5, wl.LOGISTIC, 4)[0], TOL)
+
+
+@pytest.mark.parametrize("d", [513, 1024])
+def test_rows_that_are_not_finite(d):
+    """From the step that meets an infinity on, the model holds infinities or NaN; which ones, and where the rest of it
+    stands still, is as with one step at a time."""
+    m, k = 300, 40
+    rng = np.random.default_rng(d)
+    host = (rng.standard_normal((m, d)) / math.sqrt(d)).astype(np.float32)
+    bad = rng.choice(m, 12, replace=False)
+    host[bad, rng.integers(0, d, 12)] = np.resize(np.array([math.inf, -math.inf, math.nan], dtype=np.float32), 12)
+    y = np.where(rng.random(m) < 0.5, 1.0, -1.0).astype(np.float32)
+    w0 = rng.standard_normal(d).astype(np.float32)
+    n = np.full(k, 45, dtype=np.int64)
+    n[-1] = 200
+    W = api.wpsgd_run_chains_from(api.Matrix(m, d, dense=torch.from_numpy(host).cuda()), torch.from_numpy(y).cuda(), n, 0.5, 1e-3, wl.LOGISTIC, 9,
+                                  w_start=torch.from_numpy(w0).cuda()).cpu().numpy()
+    spoiled = 0
+    with np.errstate(invalid="ignore"):
+        for i in range(k):
+            ref, _ = orc.sgd(orc.Dense(host), y, orc.sample_indices(9, i, 0, int(n[i]), m), 0.5, 1e-3, wl.LOGISTIC, w0=w0.astype(np.float64))
+            spoiled += not np.isfinite(ref).all()
+            # elementwise: a few dozen fp32 roundings of the model's entries, whose size is 1
+            np.testing.assert_allclose(W[i], ref, rtol=1e-5, atol=1e-5, equal_nan=True)
+    assert 10 <= spoiled <= k
+
+
+def test_rows_too_large_for_products():
+    """Rows of 1e17 an element: their fp32 products are finite or not, with their coefficients they are not."""
+    m, k, d = 100, 9, 520
+    host, _, y = _data(m, d, False, d)
+    host[::7] *= np.float32(1e18)
+    n = np.full(k, 200, dtype=np.int64)
+    args = (api.Matrix(m, d, dense=torch.from_numpy(host).cuda()), torch.from_numpy(y).cuda(), n, 0.5, 1e-3, wl.LOGISTIC, 9)
+    W = api.wpsgd_run_chains(*args).cpu().numpy()
+    other = api.wpsgd_run_chains(*args, plan={"threads": 256, "block_steps": 1}).cpu().numpy()
+    assert np.isfinite(other).all() and np.abs(other).max() > 1e15
+    for i in range(k):            # after a step of 1e17 an element nothing else is left of the model: a few roundings of the largest
+        assert np.abs(W[i] - other[i]).max() <= 1e-4 * np.abs(other[i]).max(), i
+
+
+def test_workspace_without_room_for_records():
+    """The register kernels need no room behind the header and the shuffled order: a call that brings only that is still served."""
+    d, m = 1024, 100
+    host, dev, y = _data(m, d, False, 2)
+    X, yg = api.Matrix(m, d, dense=dev), torch.from_numpy(y).cuda()
+    whole = api.wpsgd_run_chains_workspace(X, len(STEPS), wl.LOGISTIC)
+    ws = torch.empty(whole - len(STEPS) * d * 4, dtype=torch.uint8, device="cuda")
+    W = api.wpsgd_run_chains(X, yg, STEPS, 0.5, 1e-3, wl.LOGISTIC, 9, workspace=ws)
+    _compare(W.cpu().numpy(), orc.run_chains(orc.Dense(host), y, STEPS, 0.5, 1e-3, wl.LOGISTIC, 9)[0], TOL)
