@@ -98,7 +98,7 @@ def test_scale_is_folded_at_every_window(d):
 def test_rows_that_are_not_finite(d):
     """From the step that meets an infinity on, the model holds infinities or NaN; which ones, and where the rest of it
     stands still, is as with one step at a time."""
-    m, k = 300, 40
+    m, k = 300, 30                                # (up to 32 chains, blocks of eight from 192 steps on)
     rng = np.random.default_rng(d)
     host = (rng.standard_normal((m, d)) / math.sqrt(d)).astype(np.float32)
     bad = rng.choice(m, 12, replace=False)
