@@ -74,9 +74,14 @@ typedef struct wpsgd_matrix {
  * Used by the tests and the tuner to reach every kernel variant at any size.      */
 typedef struct wpsgd_plan {
     int threads;         /* workgroup size of a chain: 64, 128, 256, 512 or 1024 (dense); 64 or 192 (CSR)    */
-    int block_steps;     /* dense: SGD steps folded into one reduction round: 1, 2 or 4; 16: blocks of
+    int block_steps;     /* dense: SGD steps folded into one reduction round: 1, 2 or 4; 8 (alone or with
+                            `helpers`): blocks of eight steps whose products between rows helper workgroups
+                            form, or the chain itself where there are none (logistic; fp32 rows of 513 to
+                            1024 elements, 16-byte aligned bf16 rows of 513 to 2048); 16: blocks of
                             sixteen steps prepared by three more waves (rows of 4 to 256 elements)    */
-    int prefetch;        /* dense: rounds of sample rows kept in flight ahead of the one being consumed.
+    int prefetch;        /* dense: rounds of sample rows kept in flight ahead of the one being consumed;
+                            7 with block_steps = 16: those blocks in a pipeline that leaves a chain's slopes
+                            alone on its dependent path (hinge: rows of at most 64 elements).
                             CSR: selects the kernel - 1 plain gather/scatter; 4 one wave per chain, hot
                             columns in LDS, cold model values fetched 4 steps ahead; 8 the same with two
                             more waves per chain that prepare the rows (the default)                  */
@@ -85,10 +90,12 @@ typedef struct wpsgd_plan {
                             1 registers, requested `prefetch` rounds ahead; 2 registers, with the next
                             row landing in LDS meanwhile (rows up to 128 KiB); 3 nowhere: the row is
                             streamed twice (rows too long for 1 and 2)                                 */
-    int helpers;         /* dense, 256 threads, k a multiple of 8: workgroups per chain that run ahead of
+    int helpers;         /* dense, 256 threads: workgroups per chain that run ahead of
                             it on otherwise idle compute units and pull its rows into the L2 cache the
                             chain's compute unit shares.  0: choose (2 when compute units are to spare
-                            and rows are 8 KiB or longer); -1: none; 1..3: that many, room permitting  */
+                            and rows are 8 KiB or longer); -1: none; 1..3: that many, room permitting.
+                            Blocks of eight steps have helpers of their own; left to choose, a call has them
+                            only with `helpers` 0, and -1 gives the rounds of two steps instead        */
     int slices;          /* dense, 256 or 512 threads, rows in registers: compute units per chain.  Each takes a
                             slice of threads x (elements per thread) columns of the model vector and of every
                             row; the slices add their partial sums through global memory once per round

@@ -272,15 +272,18 @@ static int resolve_plan(const wpsgd_matrix *X, int k, wpsgd_loss loss, const wps
                                     : X->d <= 128 ? (k <= compute_units() ? 100 : k <= 2 * compute_units() ? 256 : 768)
                                     : 512;
         const bool block_shape = X->d >= kBlockMinColumns && X->d <= kBlockMaxColumns && (uintptr_t)X->dense % (X->dtype == WPSGD_BF16 ? 2 : 4) == 0;
-        const bool asked_block = f.block_steps == 16 && (!f.threads || f.threads == kWave) && !f.prefetch && !f.rows && f.slices <= 1;
-        if (block_shape && (asked_block || (have && !f.threads && !f.block_steps && !f.prefetch && !f.rows && f.slices <= 1 && k <= block_chains &&
+        // A forced plan names one kernel, whatever the chains' lengths: the blocks, or with the pipeline's lead the pipeline.
+        const bool asked = f.block_steps == 16 && (!f.threads || f.threads == kWave) && !f.rows && f.slices <= 1;
+        const bool asked_block = asked && !f.prefetch;
+        const bool asked_pipe = asked && f.prefetch == kPipeAhead && (loss == WPSGD_LOGISTIC || X->d <= kPipeHingeMaxColumns);
+        if (block_shape && (asked_block || asked_pipe || (have && !f.threads && !f.block_steps && !f.prefetch && !f.rows && f.slices <= 1 && k <= block_chains &&
                                             (max_steps == 0 || max_steps >= block_worth)))) {
             if (!have) found = p;
             found.family = Family::DenseReg;
             found.threads = kWave;
             found.ept = X->d <= 64 ? 1 : (X->d <= 128 ? 2 : 4);
             found.block_steps = 16;
-            found.prefetch = 2;
+            found.prefetch = asked_pipe ? kPipeAhead : 2;
             found.rows = 1;
             found.slices = 1;
             found.scouts = 3;
@@ -292,13 +295,28 @@ static int resolve_plan(const wpsgd_matrix *X, int k, wpsgd_loss loss, const wps
             // chain of so many steps): d = 64 hinge, one chain, 200 29.8 | 29.0, 1000 68.8 | 63.5, 512 chains of 1000 90 | 103; d = 128 hinge
             // 85.6 | 86.0; logistic d = 64, 32 20.3 | 19.6, 1000 59.1 | 46.8, 512 chains of 200 42.4 | 40.4, of 32 32.0 | 35.0, 1024 chains of
             // 1000 97 | 116; d = 128, 50 22.3 | 22.8, 300 34.6 | 32.4, 512 chains of 300 54.0 | 51.6; d = 256, 50 22.8 | 24.9, 300 48.0 | 41.5, 512 chains of
-            // 300 60.6 | 76.0; bf16 logistic d = 256, 50 24.7 | 23.0, 1000 103.5 | 62.4, 512 chains of 50 37.9 | 43.7, of 300 69.8 | 61.2.
+            // 300 60.6 | 76.0; bf16 logistic d = 256, 50 24.7 | 23.0, 1000 103.5 | 62.4.  (Where block_worth is
+            // the later line, that one counts; more than 128 columns come here with a compute unit per chain only.)
             const bool light = loss == WPSGD_LOGISTIC && X->dtype == WPSGD_BF16;
             int64_t pipe_worth = 0;                      // steps of the longest chain from which it pays; 0: it does not
-            if (loss == WPSGD_HINGE) pipe_worth = X->d <= 64 && k <= compute_units() ? 200 : 0;
+            if (loss == WPSGD_HINGE) pipe_worth = X->d <= kPipeHingeMaxColumns && k <= compute_units() ? 200 : 0;
             else if (k <= compute_units()) pipe_worth = light || X->d <= 64 ? 32 : X->d <= 128 ? 100 : 160;
-            else if (k <= 2 * compute_units()) pipe_worth = X->d <= 64 || (light && X->d <= 128) ? 200 : light || X->d <= 128 ? 300 : 0;
-            found.pipelined = pipe_worth > 0 && max_steps >= pipe_worth;
+            else if (k <= 2 * compute_units()) pipe_worth = X->d <= 64 || light ? 200 : 300;
+            found.pipelined = asked_pipe || (!asked_block && pipe_worth > 0 && max_steps >= pipe_worth);
+        }
+        const bool octet_shape = loss == WPSGD_LOGISTIC && X->d >= kOctetMinColumns && X->d <= octet_max_columns((int)X->dtype) &&
+                                 wide == (X->dtype == WPSGD_BF16 ? 8 : 4);
+        if (octet_shape && f.block_steps == 8 && (!f.threads || f.threads == 256) && !f.prefetch && !f.rows && f.slices <= 1) {
+            p.family = Family::DenseReg;                 // asked for: with as many helpers as there is room for, or as the plan says
+            p.threads = 256;
+            p.ept = X->dtype == WPSGD_BF16 ? 8 : 4;
+            p.vec = wide;
+            p.block_steps = 8;
+            p.prefetch = 2;
+            p.rows = p.slices = 1;
+            p.octets = true;
+            *out = p;
+            return WPSGD_OK;
         }
         if (have) {
             // Longer rows, fewer chains: blocks of eight steps whose products between rows two or three helper workgroups per chain form (chain_dense_octet.hip).
@@ -307,9 +325,7 @@ static int resolve_plan(const wpsgd_matrix *X, int k, wpsgd_loss loss, const wps
             // and there is little to gain (0.121 | 0.107, bf16 64 chains 0.129 | 0.129).  The start costs some 3 us more (us per call: d = 1024, 16 chains of
             // 64 steps 27.3 | 28.2, of 150 38.8 | 37.3, 64 chains of 200 44.5 | 45.1; bf16 d = 2048, 64 chains of 200 52.6 | 50.6).
             // (found above holds what runs where the workspace has no room for records)
-            found.octets = found.family == Family::DenseReg && found.scouts == 0 && found.slices == 1 && loss == WPSGD_LOGISTIC &&
-                           X->d >= kOctetMinColumns && X->d <= octet_max_columns((int)X->dtype) && wide == (X->dtype == WPSGD_BF16 ? 8 : 4) &&
-                           octet_helpers(k) >= 2 && max_steps >= (k <= 32 ? 192 : 256) &&
+            found.octets = octet_shape && found.family == Family::DenseReg && found.scouts == 0 && found.slices == 1 && octet_helpers(k) >= 2 && max_steps >= (k <= 32 ? 192 : 256) &&
                            !f.threads && !f.block_steps && !f.prefetch && !f.rows && !f.slices && !f.helpers;
             *out = found;
             return WPSGD_OK;
@@ -371,7 +387,10 @@ static size_t slice_table_words(int k) { return (size_t)k * (8 * 2 * 32 + 8); }
 // them, and only on compute units no chain occupies (at most 128 chains).
 static int helpers_per_chain(const Plan &p, const wpsgd_matrix *X, int k, const wpsgd_plan *force)
 {
-    if (p.octets) return octet_helpers(k);
+    if (p.octets) {
+        const int asked = force ? force->helpers : 0, room = compute_units() / ((k + 7) / 8 * 8) - 1;
+        return asked < 0 ? 0 : std::max(0, std::min(asked > 0 ? asked : octet_helpers(k), room));
+    }
     if (p.family != Family::DenseReg || p.threads != 256 || p.rows != 1 || k > 128 || p.slices > 1) return 0;
     const int asked = force ? force->helpers : 0;
     if (asked < 0) return 0;
@@ -496,10 +515,12 @@ int wpsgd_describe_plan(const wpsgd_matrix *X, int k, wpsgd_loss loss, const wps
     if (hp > 0) std::snprintf(helped, sizeof(helped), " helpers=%d", hp);
     if (p.family == Family::DenseReg && p.slices > 1) std::snprintf(helped, sizeof(helped), " slices=%d", p.slices);
     if (p.scouts > 0) std::snprintf(helped, sizeof(helped), " scouts=%d", p.scouts);
-    // (the steps of a call are not known here: what long chains run on instead)
+    // (the steps of a call are not known here: what long chains run on instead, unless the plan names the kernel)
     char longer[32] = "";
     Plan steady;
-    if (resolve_plan(X, k, loss, plan, &steady, 1.0, INT32_MAX) == WPSGD_OK && (steady.pipelined || steady.octets))
+    if (p.pipelined) std::snprintf(longer, sizeof(longer), " pipelined");
+    else if (p.octets) std::snprintf(longer, sizeof(longer), " octets");
+    else if (resolve_plan(X, k, loss, plan, &steady, 1.0, INT32_MAX) == WPSGD_OK && (steady.pipelined || steady.octets))
         std::snprintf(longer, sizeof(longer), steady.pipelined ? " long=pipelined" : " long=octets");
     char load[16] = "";                  // rows of single elements that are fetched several at a time all the same
     if (p.vec > p.align && p.scouts == 0) std::snprintf(load, sizeof(load), " load=%d", p.vec);
@@ -610,7 +631,10 @@ static int run_chains_from(const wpsgd_matrix *X, const float *y, int k, const i
     if (workspace_bytes < need) return WPSGD_WORKSPACE_TOO_SMALL;
     // (a caller that brings less than the query asks for, which the register kernels do not need, gets those)
     const size_t ring = (size_t)k * kOctetRingRecords * 256;
-    if (p.octets && workspace_bytes < h.total + perm_bytes(X->m) + ring) p.octets = false;
+    if (p.octets && workspace_bytes < h.total + perm_bytes(X->m) + ring) {
+        if (p.block_steps == 8) return WPSGD_WORKSPACE_TOO_SMALL;         // (asked for)
+        p.octets = false;
+    }
     hipStream_t s = static_cast<hipStream_t>(stream);
 
     // longest chain first (stable, so equal lengths keep their order); order and step counts

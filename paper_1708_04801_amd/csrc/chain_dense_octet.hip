@@ -464,7 +464,7 @@ hipError_t launch(const ChainArgs &a, hipStream_t s)
 
 hipError_t launch_dense_octet(const Plan &p, const ChainArgs &a, hipStream_t s)
 {
-    if (p.loss != WPSGD_LOGISTIC || a.helpers < a.k || a.d < kOctetMinColumns || a.d > octet_max_columns(p.dtype)) return hipErrorInvalidValue;
+    if (p.loss != WPSGD_LOGISTIC || a.d < kOctetMinColumns || a.d > octet_max_columns(p.dtype)) return hipErrorInvalidValue;
     if (p.dtype == WPSGD_BF16) return launch<uint16_t, 256, 8>(a, s);
     return launch<float, 256, 4>(a, s);
 }

@@ -35,6 +35,7 @@ constexpr int kBlock = 16;                    // steps per block
 constexpr int kLead = 4;                      // beats between a block's rows reaching LDS and its slopes
 constexpr int kTiles = kLead + 1;             // blocks whose rows are in LDS: from kLead beats before the slopes to the slopes' own
 constexpr int kBlocksPerWindow = kWave / kBlock;
+static_assert(kPipeAhead == kLead + 3, "rows are requested three beats before they reach LDS");
 static_assert(kBlocksPerWindow == kWindowParts && kWindowParts == 4, "the scouts' requests run three blocks ahead of their rows, in one window of 64 steps or the next");
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -528,7 +529,8 @@ template <typename TX, int LOSS>
 hipError_t launch_width(const ChainArgs &a, hipStream_t s)
 {
     if (a.d <= 64) return launch<TX, LOSS, 64>(a, s);
-    if constexpr (LOSS == kLossLogistic) {    // (longer hinge rows are bound by fp64 matrix products)
+    static_assert(kPipeHingeMaxColumns == 64, "what is built for the hinge");
+    if constexpr (LOSS == kLossLogistic) {
         if (a.d <= 128) return launch<TX, LOSS, 128>(a, s);
         return launch<TX, LOSS, 256>(a, s);
     }

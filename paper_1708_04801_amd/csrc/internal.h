@@ -105,6 +105,8 @@ hipError_t launch_dense_reg(const Plan &p, const ChainArgs &a, hipStream_t s);
 // chains of short rows, sixteen steps per block (rows of at least four elements: the kernel reads four at a time)
 constexpr int kBlockMinColumns = 4, kBlockMaxColumns = 256;
 hipError_t launch_dense_block(const Plan &p, const ChainArgs &a, hipStream_t s);
+constexpr int kPipeAhead = 7;                 // blocks from the request of a block's rows to its slopes: the plan's prefetch that names the pipeline
+constexpr int kPipeHingeMaxColumns = 64;      // (longer hinge rows are bound by fp64 matrix products)
 hipError_t launch_dense_pipe(const Plan &p, const ChainArgs &a, hipStream_t s);
 // chains of longer rows, eight steps per block; per chain a ring of records of 256 bytes in xchg (zero at the call's start), which together
 // take no more than a model vector does

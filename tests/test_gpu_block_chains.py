@@ -42,6 +42,8 @@ def test_every_row_end_and_chain_end(d, bf16, loss):
     X = api.Matrix(200, d, dense=dev)
     yg = torch.from_numpy(y).cuda()
     assert ("scouts=3" in api.wpsgd_describe_plan(X, len(STEPS), loss)) == (d <= 128 or bf16 or loss == wl.LOGISTIC)
+    forced = api.wpsgd_describe_plan(X, len(STEPS), loss, BLOCK)
+    assert "B=16 P=2" in forced and "pipelined" not in forced                   # (the pipeline has tests of its own)
     W = api.wpsgd_run_chains(X, yg, STEPS, 0.5, 1e-3, loss, 9, plan=BLOCK)
     ref = orc.run_chains(orc.Dense(host), y, STEPS, 0.5, 1e-3, loss, 9)[0]
     _compare(W.cpu().numpy(), ref, TOL[loss])

@@ -44,14 +44,14 @@ def test_every_row_end_and_chain_end(bf16, d):
 
 @pytest.mark.parametrize("d", [513, 700, 1024])
 def test_results_do_not_depend_on_the_helpers(d):
-    """Three helpers a chain and two: a chain of the same number takes the same steps and has the same bits, whichever
+    """Three helpers a chain, two, one and none: a chain of the same number takes the same steps and has the same bits, whichever
     products were there in time."""
     _, dev, y = _data(500, d, False, d)
     X, yg = api.Matrix(500, d, dense=dev), torch.from_numpy(y).cuda()
     runs = []
-    for k in (6, 6, 60, 80):
+    for k, plan in ((6, None), (6, None), (60, None), (80, None), (6, {"block_steps": 8, "helpers": 1}), (6, {"block_steps": 8, "helpers": -1})):
         n = np.full(k, 700, dtype=np.int64)
-        runs.append(api.wpsgd_run_chains(X, yg, n, 0.5, 1e-3, wl.LOGISTIC, 9)[:6])
+        runs.append(api.wpsgd_run_chains(X, yg, n, 0.5, 1e-3, wl.LOGISTIC, 9, plan=plan)[:6])
     for W in runs[1:]:
         assert torch.equal(W, runs[0])
 

@@ -1,5 +1,5 @@
 """Chains of short rows with everything but the slopes off the dependent path: every way a row, a block, a window or a
-chain can end, against the oracle.  (The longest chain of a call decides whether this kernel runs: see the planner.)"""
+chain can end, against the oracle.  (The plan names the kernel: left to choose, calls of few steps run others.)"""
 import math
 
 import numpy as np
@@ -15,6 +15,7 @@ pytestmark = pytest.mark.gpu
 STEPS = np.array([0, 1, 15, 16, 17, 47, 48, 63, 64, 65, 128, 333], dtype=np.int64)
 # fp64 state leaves the rounding of the result to fp32 (6e-8 an element); fp32 state some 300 roundings of it
 TOL = {wl.HINGE: 2e-7, wl.LOGISTIC: 2e-5}
+PIPE = {"block_steps": 16, "prefetch": 7}
 SHAPES = [(wl.HINGE, b, d) for b in (False, True) for d in (4, 5, 16, 31, 63, 64)] + \
          [(wl.LOGISTIC, b, d) for b in (False, True) for d in (4, 7, 17, 64, 65, 98, 128, 129, 191, 255, 256)]
 
@@ -39,9 +40,9 @@ def test_every_row_end_and_chain_end(loss, bf16, d):
     host, dev, y = _data(200, d, bf16, d + 7 * loss)
     X, yg = api.Matrix(200, d, dense=dev), torch.from_numpy(y).cuda()
     assert "long=pipelined" in api.wpsgd_describe_plan(X, len(STEPS), loss)
-    W = api.wpsgd_run_chains(X, yg, STEPS, 0.5, 1e-3, loss, 9)
+    W = api.wpsgd_run_chains(X, yg, STEPS, 0.5, 1e-3, loss, 9, plan=PIPE)
     _compare(W.cpu().numpy(), orc.run_chains(orc.Dense(host), y, STEPS, 0.5, 1e-3, loss, 9)[0], TOL[loss])
-    assert torch.equal(W, api.wpsgd_run_chains(X, yg, STEPS, 0.5, 1e-3, loss, 9))
+    assert torch.equal(W, api.wpsgd_run_chains(X, yg, STEPS, 0.5, 1e-3, loss, 9, plan=PIPE))
 
 
 @pytest.mark.parametrize("loss", [wl.HINGE, wl.LOGISTIC])
@@ -53,7 +54,7 @@ def test_start_vector_offsets_and_shards(loss, sampling):
     w0 = torch.linspace(-1.0, 1.0, d, device="cuda")
     off = np.arange(len(STEPS), dtype=np.int64) * 37
     args = (X, yg, STEPS, 0.3, 1e-2, loss, 3)
-    W = api.wpsgd_run_chains_from(*args, w_start=w0, step_offsets=off, sampling=sampling)
+    W = api.wpsgd_run_chains_from(*args, w_start=w0, step_offsets=off, sampling=sampling, plan=PIPE)
     other = api.wpsgd_run_chains_from(*args, w_start=w0, step_offsets=off, sampling=sampling,
                                       plan={"threads": 64, "block_steps": 1, "prefetch": 8})
     _compare(W.cpu().numpy(), other.cpu().numpy().astype(np.float64), TOL[loss])
@@ -69,7 +70,7 @@ def test_scale_is_folded_at_every_window(d, loss):
     host, dev, y = _data(64, d, False, 8)
     n = np.resize(STEPS, k)
     X, yg = api.Matrix(64, d, dense=dev), torch.from_numpy(y).cuda()
-    W = api.wpsgd_run_chains(X, yg, n, 0.8, 0.5, loss, 4).cpu().numpy()
+    W = api.wpsgd_run_chains(X, yg, n, 0.8, 0.5, loss, 4, plan=PIPE if loss == wl.LOGISTIC or d <= 64 else None).cpu().numpy()
     _compare(W[:24], orc.run_chains(orc.Dense(host), y, n, 0.8, 0.5, loss, 4, chain_ids=np.arange(24))[0], TOL[loss])
     _compare(W[-12:], orc.run_chains(orc.Dense(host), y, n, 0.8, 0.5, loss, 4, chain_ids=np.arange(k - 12, k))[0], TOL[loss])
 
@@ -88,7 +89,7 @@ def test_rows_that_are_not_finite(d, loss):
     n = np.full(k, 45, dtype=np.int64)
     n[-1] = 200
     W = api.wpsgd_run_chains_from(api.Matrix(m, d, dense=torch.from_numpy(host).cuda()), torch.from_numpy(y).cuda(), n, 0.5, 1e-3, loss, 9,
-                                  w_start=torch.from_numpy(w0).cuda()).cpu().numpy()
+                                  w_start=torch.from_numpy(w0).cuda(), plan=PIPE).cpu().numpy()
     spoiled = 0
     with np.errstate(invalid="ignore"):
         for i in range(k):

@@ -13,6 +13,8 @@ pytestmark = pytest.mark.gpu
 
 ONE_WAVE = {"threads": 64, "block_steps": 1, "prefetch": 8}
 BLOCK = {"block_steps": 16}
+PIPE = {"block_steps": 16, "prefetch": 7}
+OCTET = {"block_steps": 8}
 
 
 def _run(d, k, n, plan, bf16=False):
@@ -29,10 +31,29 @@ def _run(d, k, n, plan, bf16=False):
     (128, 4, 99, 100), (100, 300, 255, 256), (128, 900, 767, 768),
     (200, 4, 511, 512), (256, 250, 511, 512)])
 def test_blocks_of_sixteen_steps(d, k, few, enough):
-    assert torch.equal(_run(d, k, enough, None), _run(d, k, enough, BLOCK))
+    blocks = PIPE if enough >= 100 and k <= 256 else BLOCK               # (long enough for the pipeline at once)
+    assert torch.equal(_run(d, k, enough, None), _run(d, k, enough, blocks))
     if few:
         assert torch.equal(_run(d, k, few, None), _run(d, k, few, ONE_WAVE))
-        assert not torch.equal(_run(d, k, few, BLOCK), _run(d, k, few, ONE_WAVE))
+        assert not torch.equal(_run(d, k, few, blocks), _run(d, k, few, ONE_WAVE))
+
+
+@pytest.mark.parametrize("d,k,few,bf16", [
+    (64, 4, 31, False), (50, 256, 31, False), (64, 300, 199, False),     # at most a chain per compute unit; two
+    (128, 300, 299, False), (128, 300, 255, True)])
+def test_blocks_of_sixteen_steps_in_a_pipeline(d, k, few, bf16):
+    assert torch.equal(_run(d, k, few + 1, None, bf16), _run(d, k, few + 1, PIPE, bf16))
+    other = ONE_WAVE if bf16 else BLOCK
+    assert torch.equal(_run(d, k, few, None, bf16), _run(d, k, few, other, bf16))
+    assert not torch.equal(_run(d, k, few, PIPE, bf16), _run(d, k, few, other, bf16))
+
+
+@pytest.mark.parametrize("d,k,few,bf16", [(1024, 4, 191, False), (513, 32, 191, False), (700, 33, 255, False), (2048, 64, 255, True)])
+def test_blocks_of_eight_steps(d, k, few, bf16):
+    rounds = {"helpers": -1}
+    assert torch.equal(_run(d, k, few + 1, None, bf16), _run(d, k, few + 1, OCTET, bf16))
+    assert torch.equal(_run(d, k, few, None, bf16), _run(d, k, few, rounds, bf16))
+    assert not torch.equal(_run(d, k, few, OCTET, bf16), _run(d, k, few, rounds, bf16))
 
 
 @pytest.mark.parametrize("d,slices", [(40000, 5), (16384 * 3, 6)])

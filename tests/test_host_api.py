@@ -164,6 +164,31 @@ def test_planner_picks_registers_when_the_vector_fits_and_hbm_otherwise():
         assert err.value.status == api.INVALID_ARG
 
 
+def test_a_forced_plan_names_one_kernel():
+    d = api.wpsgd_describe_plan
+    for loss in (api.HINGE, api.LOGISTIC):
+        for cols in (4, 64, 65, 256):
+            text = d(_FakeMatrix(4096, cols), 12, loss, plan={"block_steps": 16})
+            assert "B=16 P=2" in text and "pipelined" not in text
+            if loss == api.LOGISTIC or cols <= 64:
+                text = d(_FakeMatrix(4096, cols), 12, loss, plan={"block_steps": 16, "prefetch": 7})
+                assert "B=16 P=7" in text and text.endswith(" pipelined")
+    text = d(_FakeMatrix(4096, 1024), 12, api.LOGISTIC, plan={"block_steps": 8})
+    assert "B=8" in text and "helpers=3" in text and text.endswith(" octets")
+    assert "helpers" not in d(_FakeMatrix(4096, 1024), 12, api.LOGISTIC, plan={"block_steps": 8, "helpers": -1})
+    assert "helpers" not in d(_FakeMatrix(4096, 1024), 300, api.LOGISTIC, plan={"block_steps": 8})
+    refused = [(1024, api.F32, api.HINGE, {"block_steps": 8}), (512, api.F32, api.LOGISTIC, {"block_steps": 8}),
+               (1025, api.F32, api.LOGISTIC, {"block_steps": 8}), (2049, api.BF16, api.LOGISTIC, {"block_steps": 8}),
+               (1001, api.BF16, api.LOGISTIC, {"block_steps": 8}), (1024, api.F32, api.LOGISTIC, {"block_steps": 8, "threads": 64}),
+               (1024, api.F32, api.LOGISTIC, {"block_steps": 8, "prefetch": 2}), (65, api.F32, api.HINGE, {"block_steps": 16, "prefetch": 7}),
+               (64, api.F32, api.HINGE, {"block_steps": 16, "prefetch": 2}), (257, api.F32, api.LOGISTIC, {"block_steps": 16, "prefetch": 7}),
+               (3, api.F32, api.LOGISTIC, {"block_steps": 16, "prefetch": 7})]
+    for cols, dtype, loss, plan in refused:
+        with pytest.raises(api.WpsgdError) as err:
+            d(_FakeMatrix(4096, cols, dtype), 12, loss, plan=plan)
+        assert err.value.status == api.UNSUPPORTED, (cols, plan)
+
+
 def test_planner_shapes_cover_the_row_for_any_size():
     """Whatever d, k, storage and loss: a register plan's lanes cover every column, a sliced plan
     leaves no slice empty and never asks for more workgroups than the device has compute units,
