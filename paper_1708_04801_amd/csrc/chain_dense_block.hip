@@ -93,8 +93,8 @@ __global__ __launch_bounds__(kBlockThreads) void chain_dense_block_kernel(ChainA
     __shared__ __attribute__((aligned(16))) TV model[C];
     // does block b (in word b mod 4) hold an element whose products with others may not be finite?
     __shared__ uint32_t excess[4];
-    // (fp64 products of fp32 numbers do not overflow; 256 fp32 squares of less than 2^32 do not, nor with the coefficients eta/s, s >= 2^-30, on them)
-    constexpr float kProbe = LOSS == kLossHinge ? 0.0f : 0x1p96f;
+    // (fp64 products of fp32 numbers do not overflow; 256 fp32 squares of less than 2^58 do not)
+    constexpr float kProbe = LOSS == kLossHinge ? 0.0f : 0x1p70f;
 
     const int lane = (int)(threadIdx.x & (kWave - 1));
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
@@ -343,7 +343,11 @@ __global__ __launch_bounds__(kBlockThreads) void chain_dense_block_kernel(ChainA
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int t = Gram<TV>::row(r, lane);
-            const TV unit = zs * __shfl(cs, t) * gram.d[r];        // (in every lane: a lane that stands aside has nothing to give)
+            // zs and cs first: for t < j they are eta log2 e s_j/s_{t+1} at most eta log2 e, whatever the scale has shrunk to; cs alone may be
+            // eta 2^85 (a window may start at 2^-30 and end at 2^-85).  (In every lane: a lane that stands aside has nothing to give.)
+            TV unit = (zs * __shfl(cs, t)) * gram.d[r];
+            // A large eta may take a product of 2^124 past the largest number; a slope of 0 times an infinity would be a NaN where nothing is added.
+            if constexpr (LOSS == kLossLogistic) unit = __builtin_amdgcn_fmed3f(unit, -0x1.fffffep127f, 0x1.fffffep127f);
             sec.gram[t][j] = t < j ? unit : (TV)0;
         }
         section_barrier();

@@ -65,6 +65,35 @@ def test_start_vector_offsets_and_shards(loss, sampling):
     assert torch.equal(W[0], w0)
 
 
+@pytest.mark.parametrize("d", [33, 128, 200])
+@pytest.mark.parametrize("shift", [20, 40, 54])
+def test_large_rows_stay_in_blocks(d, shift):
+    """Rows 2^s times as large, eta 2^-2s and lambda 2^2s times: the models are 2^-s times as large, bit for bit, unless the blocks
+    give up on rows that large and take one step after the other, whose sums have another order."""
+    _, dev, y = _data(200, d, False, d)
+    yg, s = torch.from_numpy(y).cuda(), 2.0 ** shift
+    W = api.wpsgd_run_chains(api.Matrix(200, d, dense=dev), yg, STEPS, 0.5, 1e-3, wl.LOGISTIC, 9, plan=BLOCK)
+    scaled = api.wpsgd_run_chains(api.Matrix(200, d, dense=dev * s), yg, STEPS, 0.5 / (s * s), 1e-3 * (s * s), wl.LOGISTIC, 9, plan=BLOCK)
+    assert torch.equal(scaled * s, W)
+
+
+@pytest.mark.parametrize("d,e", [(33, 54), (200, 52)])
+def test_large_rows_and_a_large_eta(d, e):
+    """Products between rows that are finite and, with a step's coefficient, are not: the first step moves the model by half of eta, to
+    where no later one moves it, and a slope of 0 times such a product must stay 0."""
+    rng = np.random.default_rng(d)
+    y = np.where(rng.random(100) < 0.5, 1.0, -1.0).astype(np.float32)
+    host = np.repeat(y[:, None] * np.float32(2.0 ** e), d, axis=1)
+    product = np.float32(d * 4.0 ** e)
+    eta = 2.0 ** 127.57 / float(product)
+    with np.errstate(over="ignore"):
+        assert np.isfinite(product * np.float32(0.5 * eta / math.log(2))) and np.isinf(product * np.float32(eta / math.log(2)))
+    n = np.full(9, 48, dtype=np.int64)
+    args = (api.Matrix(100, d, dense=torch.from_numpy(host).cuda()), torch.from_numpy(y).cuda(), n, eta, 0.0, wl.LOGISTIC, 9)
+    W = api.wpsgd_run_chains(*args, plan=BLOCK).cpu().numpy()
+    np.testing.assert_allclose(W, np.full((9, d), 0.5 * eta * 2.0 ** e), rtol=1e-6)            # (a handful of fp32 roundings)
+
+
 @pytest.mark.parametrize("loss", [wl.HINGE, wl.LOGISTIC])
 def test_scale_is_folded_and_many_chains_run(loss):
     """eta*lambda = 0.4: the scale falls below 2^-30 within a window.  900 chains: several to a compute unit."""
