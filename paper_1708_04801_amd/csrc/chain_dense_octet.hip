@@ -29,6 +29,7 @@ namespace {
 constexpr int kOctet = 8;                             // steps per block
 constexpr int kPairs = kOctet * (kOctet - 1) / 2;     // products between its rows: of rows j > t at j(j-1)/2 + t
 constexpr int kOctetsPerWindow = kWave / kOctet;
+constexpr int kHelperLooks = 1 << 15;                 // (0.4 us each: a sleep of 256 cycles, a load from memory and a barrier)
 constexpr uint32_t kLdsClaim = 84 * 1024;             // more than half a compute unit's: helpers stay off the chains' compute units
 
 template <typename TX, int NT, int EPT>
@@ -112,8 +113,8 @@ __device__ inline void beat_barrier()         // everything this wave wrote to L
 }
 
 // Helper q of a chain's Q forms the products of blocks q+1, q+1+Q, ...; it leaves out those the chain is about to form itself, stays
-// `lead` blocks ahead at most (so that the rows are still cached when the chain asks for them), and ends when the chain has ended or does not
-// move.  Its last wave watches the chain, adds up the others' shares and writes the records.
+// `lead` blocks ahead at most (so that the rows are still cached when the chain asks for them), and ends when the chain has ended, or has
+// not moved for kHelperLooks looks (13 ms; a block takes the chain a microsecond).  Its last wave watches the chain, adds up the others' shares and writes the records.
 template <typename TX, int NT, int EPT>
 __device__ inline void help(const ChainArgs &a, OctetLds<NT / kWave> &lds, int cb, int q, int Q)
 {
@@ -125,13 +126,15 @@ __device__ inline void help(const ChainArgs &a, OctetLds<NT / kWave> &lds, int c
     const int lead = min(Q + 4, kOctetRingRecords - 1);
     int64_t cur = 1 + q;
     if (cur >= nblk) return;
-    int64_t polls = nblk + (1 << 15);         // every wait draws on this
+    int polls = kHelperLooks;                 // every look while too far ahead draws on this, until the chain moves
     int64_t seen = 0, nxt = cur + Q;
     int parity = 0;
     // All waves of the workgroup take the same decisions from what the last wave has seen.
     auto look = [&]() {
         beat_barrier();
-        seen = max((int)((uint32_t)__builtin_amdgcn_readfirstlane((int)lds.seen[parity]) - base), 0);
+        const int64_t now = max((int)((uint32_t)__builtin_amdgcn_readfirstlane((int)lds.seen[parity]) - base), 0);
+        if (now > seen) polls = kHelperLooks;
+        seen = now;
         parity ^= 1;
     };
     auto far_ahead = [&]() { return nxt < nblk && nxt > seen + lead; };
