@@ -105,8 +105,10 @@ static int compute_units()
 
 // Helper workgroups per chain of blocks of eight steps: a multiple of eight behind the chains, on compute units of the chain's XCD that no chain
 // occupies (one that has to wait for a compute unit is worse than none: d = 767, 84 chains, two helpers each: 33 workgroups for the 32 units of an XCD,
-// 0.147 us per step, as without).
-static int octet_helpers(int k) { return std::min(compute_units() / ((k + 7) / 8 * 8) - 1, 3); }
+// 0.147 us per step, as without).  A workgroup has its compute unit to itself, so helpers leave as many units as the chains take for a call on another
+// stream: its chains start at once, without helpers until the first call's have ended (us, one call of 4000 steps | two on two streams, 64 chains: d = 1024
+// three helpers each 456 | 885, two 464 | 685, rounds of two steps 582 | 775; bf16 d = 2048 524 | 1022, 528 | 790, 712 | 1000).
+static int octet_helpers(int k) { return std::min(compute_units() / ((k + 7) / 8 * 8) - 2, 3); }
 
 static int resolve_plan(const wpsgd_matrix *X, int k, wpsgd_loss loss, const wpsgd_plan *force, Plan *out,
                         double rho = 1.0, int64_t max_steps = 0)
@@ -321,7 +323,8 @@ static int resolve_plan(const wpsgd_matrix *X, int k, wpsgd_loss loss, const wps
         if (have) {
             // Longer rows, fewer chains: blocks of eight steps whose products between rows two or three helper workgroups per chain form (chain_dense_octet.hip).
             // One helper is too slow (us per step, rounds of two steps | blocks of eight, 128 chains: d = 1024 0.150 | 0.139, bf16 d = 2048 0.176 |
-            // 0.168, d = 512 0.120 | 0.132; 64 chains: 0.148 | 0.115, bf16 d = 2048 0.174 | 0.131).  Up to 512 columns the register kernel has one or two waves
+            // 0.168, d = 512 0.120 | 0.132; 64 chains: 0.148 | 0.115, bf16 d = 2048 0.174 | 0.131; us per call of 80 chains of 300 steps, alone | two on two
+            // streams: d = 1024 68 | 96, 69 | 102, bf16 77 | 112, 79 | 116).  Up to 512 columns the register kernel has one or two waves
             // and there is little to gain (0.121 | 0.107, bf16 64 chains 0.129 | 0.129).  The start costs some 3 us more (us per call: d = 1024, 16 chains of
             // 64 steps 27.3 | 28.2, of 150 38.8 | 37.3, 64 chains of 200 44.5 | 45.1; bf16 d = 2048, 64 chains of 200 52.6 | 50.6).
             // (found above holds what runs where the workspace has no room for records)

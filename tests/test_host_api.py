@@ -176,6 +176,11 @@ def test_a_forced_plan_names_one_kernel():
     text = d(_FakeMatrix(4096, 1024), 12, api.LOGISTIC, plan={"block_steps": 8})
     assert "B=8" in text and "helpers=3" in text and text.endswith(" octets")
     assert "helpers" not in d(_FakeMatrix(4096, 1024), 12, api.LOGISTIC, plan={"block_steps": 8, "helpers": -1})
+    # left to choose, helpers leave as many compute units as the chains take to a call on another stream, or there are none
+    for k, helpers in ((48, "helpers=3"), (49, "helpers=2"), (64, "helpers=2"), (65, "helpers=1"), (80, "helpers=1")):
+        assert helpers in d(_FakeMatrix(4096, 1024), k, api.LOGISTIC, plan={"block_steps": 8})
+        assert ("long=octets" in d(_FakeMatrix(4096, 1024), k, api.LOGISTIC)) == (helpers != "helpers=1")
+    assert "helpers=2" in d(_FakeMatrix(4096, 1024), 80, api.LOGISTIC, plan={"block_steps": 8, "helpers": 3})
     assert "helpers" not in d(_FakeMatrix(4096, 1024), 300, api.LOGISTIC, plan={"block_steps": 8})
     refused = [(1024, api.F32, api.HINGE, {"block_steps": 8}), (512, api.F32, api.LOGISTIC, {"block_steps": 8}),
                (1025, api.F32, api.LOGISTIC, {"block_steps": 8}), (2049, api.BF16, api.LOGISTIC, {"block_steps": 8}),
