@@ -128,12 +128,18 @@ def test_long_sparse_rows_keep_a_wave_busy():
     assert _best_us(*_sparse(lens, d)[:3])[0] <= 650.0
 
 
-@pytest.mark.parametrize("m,mean", [(37, 5), (5000, 3), (401000, 9), (401000, 70), (1000, 200)])
-def test_sparse_rows_four_entries_a_lane(m, mean):
+@pytest.mark.parametrize("m,mean,d", [
+    (37, 5, 5000), (5000, 3, 5000), (401000, 9, 5000), (401000, 70, 5000),
+    (1000, 200, 5000),                            # (a wave to a row)
+    (20000, 110, 30000), (401000, 70, 30000),     # columns in the copied head and behind it; rows of 256 entries and of more among them
+    (401000, 9, 200000)])                         # columns mostly behind the head
+def test_sparse_rows_four_entries_a_lane(m, mean, d):
     """Rows of 0 to 3 * mean entries from any entry of the arrays on, the last one at the arrays' end; the first row_ptr is not zero."""
-    d, rng = 5000, np.random.default_rng(m + mean)
+    rng = np.random.default_rng(m + mean)
     lens = np.minimum(rng.integers(0, 3 * mean, m), rng.integers(0, 3 * mean, m))
     lens[-1] = mean
+    if mean == 110:
+        lens[5:3000:7] = 256 + np.arange(428) % 3 - 1      # (up to 256 entries 16 lanes, from 257 on the whole wave)
     skip = 3
     row_ptr = np.zeros(m + 1, dtype=np.int64)
     np.cumsum(lens, out=row_ptr[1:])
@@ -141,6 +147,7 @@ def test_sparse_rows_four_entries_a_lane(m, mean):
     gap = rng.integers(1, d // (3 * mean), nnz).astype(np.int64)
     total = np.concatenate([[0], np.cumsum(gap)])
     col = (total[1:] - np.repeat(total[row_ptr[:-1]], lens) - 1).astype(np.int32)
+    col = np.where(np.repeat(np.arange(m) % 2, lens), d - 1 - col, col).astype(np.int32)      # every other row from the last column down
     val = rng.standard_normal(nnz).astype(np.float32)
     w = rng.standard_normal(d).astype(np.float32)
     y = np.where(rng.random(m) < 0.5, 1.0, -1.0).astype(np.float32)
@@ -153,3 +160,28 @@ def test_sparse_rows_four_entries_a_lane(m, mean):
     ref = 0.05 * float(w.astype(np.float64) @ w) + np.maximum(0.0, 1.0 - y * yhat).mean()
     # running sums of nnz terms of size 1: nnz^1.5 * 1e-16 at most, over the mean of m losses of size 1 and more
     assert abs(got[0] - ref) <= 1e-9 * ref
+
+
+def test_a_sparse_batch_of_more_than_32_bit_offsets():
+    """A row of 2^28 entries: the rows that share its batch go one by one."""
+    m, d, n = 4500000, 1000, 1 << 28
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1)
+    lens = torch.randint(0, 4, (m,), generator=g, device="cuda", dtype=torch.int64)
+    lens[m // 2] = n
+    ptr = torch.zeros(m + 1, dtype=torch.int64, device="cuda")
+    torch.cumsum(lens, 0, out=ptr[1:])
+    nnz = int(ptr[-1])
+    cols = torch.arange(nnz, dtype=torch.int64, device="cuda").remainder_(d).to(torch.int32)
+    w = torch.randn(d, generator=g, device="cuda") / 8
+    vals = torch.ones(nnz, device="cuda")
+    y = torch.where(torch.rand(m, generator=g, device="cuda") < 0.5, 1.0, -1.0)
+    out = api.wpsgd_objective(api.Matrix(m, d, row_ptr=ptr, col_idx=cols, vals=vals), y, w, 0.01, wl.HINGE).cpu().numpy()
+    w64, p = w.double().cpu().numpy(), ptr.cpu().numpy()
+    sums = np.concatenate([[0.0], np.cumsum(w64)])         # w.x of a row: its columns follow each other, round and round
+    z = y.double().cpu().numpy() * ((p[1:] // d - p[:-1] // d) * sums[-1] + sums[p[1:] % d] - sums[p[:-1] % d])
+    z[p[1:] == p[:-1]] = 0.0
+    want = 0.005 * (w64 @ w64) + np.maximum(0.0, 1.0 - z).mean()
+    # a lane adds up to 2^22 terms of the long row in fp64, 2^22 * 2^-53 of a sum of 1e6 at most, and the row is one of m
+    assert abs(out[0] - want) <= 1e-9 * want
+    assert abs(out[1] - (z <= 0).mean()) * m <= 1.0

@@ -120,8 +120,8 @@ def test_rows_that_are_not_finite(d):
     assert 10 <= spoiled <= k
 
 
-def test_rows_too_large_for_products():
-    """Rows of 1e17 an element: their fp32 products are finite or not, with their coefficients they are not."""
+def test_rows_of_very_different_size():
+    """Rows of 1e17 an element among rows of 0.1: products of 1e36, 1e18 and 1 in one block."""
     m, k, d = 100, 9, 520
     host, _, y = _data(m, d, False, d)
     host[::7] *= np.float32(1e18)
@@ -184,6 +184,30 @@ def test_helpers_stay_with_a_long_chain(bf16, d):
     X, yg = api.Matrix(2000, d, dense=dev), torch.from_numpy(y).cuda()
     usual, long = _us_per_step(X, yg, 8, 200000), _us_per_step(X, yg, 8, 1500000)
     assert long <= 1.07 * usual, (long, usual)
+
+
+@pytest.mark.parametrize("size,eta", [(1e20, 0.5), (1e19, 8.0)])
+def test_rows_too_large_for_products(size, eta):
+    """Finite rows whose fp32 products overflow (1e20), or whose products do with a step's coefficient on them (1e19).  Large rows share a
+    direction and have no element below zero, so that v.x may be infinite but is never a NaN one step at a time."""
+    m, k, d = 100, 9, 520
+    rng = np.random.default_rng(d)
+    host, _, y = _data(m, d, False, d)
+    u = np.abs(rng.standard_normal(d))
+    host[::4] = (size * u / np.linalg.norm(u)).astype(np.float32)
+    n = np.full(k, 200, dtype=np.int64)
+    pairs = 0                     # of large rows in a block
+    for i in range(k):
+        blocks = (orc.sample_indices(9, i, 0, 200, m) % 4 == 0)[:200 // 8 * 8].reshape(-1, 8).sum(axis=1)
+        pairs += int((blocks * (blocks - 1) // 2).sum())
+    product, most = float(host[0].astype(np.float64) @ host[0]), float(np.finfo(np.float32).max)
+    assert pairs >= 100 and (product > 2 * most if size == 1e20 else 0.25 * most < product < 0.5 * most and eta * product / math.log(2) > 2 * most)
+    args = (api.Matrix(m, d, dense=torch.from_numpy(host).cuda()), torch.from_numpy(y).cuda(), n, eta, 1e-3, wl.LOGISTIC, 9)
+    W = api.wpsgd_run_chains(*args, plan={"block_steps": 8}).cpu().numpy()
+    other = api.wpsgd_run_chains(*args, plan={"threads": 256, "block_steps": 1}).cpu().numpy()
+    assert np.isfinite(other).all() and np.abs(other).max() > 1e17
+    for i in range(k):            # after a step of that size nothing else is left of the model: a few roundings of the largest
+        assert np.abs(W[i] - other[i]).max() <= 1e-4 * np.abs(other[i]).max(), i
 
 
 def test_workspace_without_room_for_records():

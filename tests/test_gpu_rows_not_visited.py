@@ -14,6 +14,7 @@ pytestmark = pytest.mark.gpu
 
 # fp64 state leaves the rounding of the result to fp32 (6e-8 an element); fp32 state a few dozen roundings of it
 TOL = {wl.HINGE: 2e-7, wl.LOGISTIC: 5e-6}
+PIPE, OCTET = {"block_steps": 16, "prefetch": 7}, {"block_steps": 8}
 M, SEED, ETA, LAM = 4000, 9, 0.5, 1e-3
 
 
@@ -50,6 +51,15 @@ def test_dense_chains(d, bf16, plan, loss, sampling):
         X = dev.float().cpu().numpy()
     W = api.wpsgd_run_chains_from(api.Matrix(M, d, dense=dev), torch.from_numpy(y).cuda(), n, ETA, LAM, loss, SEED, sampling=sampling, plan=plan)
     _check(W.cpu().numpy(), orc.Dense(X), y, visits, loss)
+
+
+@pytest.mark.parametrize("d,bf16,loss,plan", [
+    (50, False, wl.HINGE, PIPE), (64, True, wl.HINGE, PIPE), (50, False, wl.LOGISTIC, PIPE), (128, True, wl.LOGISTIC, PIPE),
+    (200, False, wl.LOGISTIC, PIPE), (700, False, wl.LOGISTIC, OCTET), (1024, False, wl.LOGISTIC, OCTET), (2040, True, wl.LOGISTIC, OCTET)])
+@pytest.mark.parametrize("sampling", [api.SAMPLE_STREAM, api.SAMPLE_SHARDS])
+def test_blocks_that_run_ahead(d, bf16, loss, plan, sampling):
+    """Waves and workgroups that prepare blocks reach furthest behind a chain's end."""
+    test_dense_chains(d, bf16, plan, loss, sampling)
 
 
 @pytest.mark.parametrize("per", [7, 40])                       # four steps at a time; one at a time
