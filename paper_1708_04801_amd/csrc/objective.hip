@@ -233,6 +233,19 @@ __global__ __launch_bounds__(kObjThreads) void objective_short_rows_kernel(const
 // the average row is long, where rows are so few that each may have a wave, or where no head is used (1000 rows of
 // 3000: 63 -> 29 us; 1000000 rows of 80 uniform columns: 632 -> 605).
 constexpr int kLongRow = 256;                 // entries
+constexpr int kBriefRow = 32;                 // entries of the average row
+// E dwords that follow each other, each zero from the resource's end on
+template <int E> struct EntryLoad {
+    typedef uint32_t words __attribute__((ext_vector_type(E)));
+    words q;
+    __device__ EntryLoad(__amdgpu_buffer_rsrc_t from, uint32_t off)
+    {
+        if constexpr (E == 4) q = __builtin_bit_cast(words, __builtin_amdgcn_raw_buffer_load_b128(from, off, 0, 0));
+        else if constexpr (E == 2) q = __builtin_bit_cast(words, __builtin_amdgcn_raw_buffer_load_b64(from, off, 0, 0));
+        else q[0] = __builtin_amdgcn_raw_buffer_load_b32(from, off, 0, 0);
+    }
+    __device__ uint32_t at(int i) const { return q[i]; }
+};
 template <int THREADS, int HEAD>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(HEAD > 0 ? THREADS / 128 : 1)))
 void objective_csr_kernel(const int64_t *row_ptr, const int32_t *col_idx,
@@ -322,8 +335,10 @@ void objective_csr_kernel(const int64_t *row_ptr, const int32_t *col_idx,
         return;
     }
 
+    const bool brief = entries <= m * kBriefRow || !copied;
     auto rows_in_batches = [&](auto copied_tag) {
         constexpr bool COPIED = decltype(copied_tag)::value;
+        auto near = [](uint32_t col) { return COPIED && col < (uint32_t)HEAD; };
         for (int64_t row0 = wave_id * batch; row0 < m; row0 += nwaves * batch) {
             if constexpr (!AHEAD) ask_lane(row0);
             const int64_t lo = lo_lane;
@@ -332,7 +347,10 @@ void objective_csr_kernel(const int64_t *row_ptr, const int32_t *col_idx,
             double held = 0.0;
             if (entries > 0) {
                 // A lane takes four entries that follow each other with one load for the columns and one for the values, a quarter of
-                // the instructions of single entries (a million rows of 80, Zipf: 313 -> 272 us; of 110, 433 -> 369; of 8, 85 | 86).  The loads
+                // the instructions of single entries (a million rows of 80, Zipf: 313 -> 272 us; of 110, 433 -> 369).  A lane's entries wait for each other's
+                // loads of the model, so the last 16 or 32 of brief rows go one or two to a lane (us, a million rows, half of the columns behind the head,
+                // single entries | four to a lane | this: mean 2 69 | 73 | 49, 10 72 | 80 | 59, 16 75 | 82 | 63, 40 190 | 172 | 170; all columns in it, mean 10
+                // 77 | 76 | 55).  Not where longer rows meet a copied head: 260 us for the rows of 80 with every rest to a lane's four, 267 this way.  The loads
                 // are checked against the arrays' end, dword by dword, and count from the batch's first entry; a batch too long
                 // for their 32-bit offsets goes row by row.
                 const int64_t base = lane_read_i64(lo, 0);
@@ -345,24 +363,27 @@ void objective_csr_kernel(const int64_t *row_ptr, const int32_t *col_idx,
                     const uint32_t p0 = (uint32_t)__shfl((int)mine, from);
                     const int whole = __shfl(len, from), n = whole > kLongRow || !near_rows ? 0 : whole;
                     double acc = 0.0;
-                    for (int e0 = 0; __any(e0 < n); e0 += kAtOnce * LPR) {
-                        const int e = e0 + kAtOnce * c;
+                    auto take = [&](auto entries_tag, int e0) {
+                        constexpr int E = decltype(entries_tag)::value;      // a lane's entries from e0 on
+                        const int e = e0 + E * c;
                         const uint32_t off = e < n ? (p0 + (uint32_t)e) * 4u : 0xFFFFFFF0u;
-                        const u32x4 col = __builtin_amdgcn_raw_buffer_load_b128(cres, off, 0, 0), val = __builtin_amdgcn_raw_buffer_load_b128(vres, off, 0, 0);
-                        float wv[kAtOnce];
+                        const EntryLoad<E> col(cres, off), val(vres, off);
+                        float wv[E];
 #pragma unroll
-                        for (int i = 0; i < kAtOnce; ++i) {
-                            const bool in = e + i < n;
-                            if constexpr (COPIED) {
-                                const bool near = col[i] < (uint32_t)HEAD;
-                                const float far = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(wres, in && !near ? col[i] * 4u : 0xFFFFFFF0u, 0, 0));
-                                wv[i] = near ? head[near ? col[i] : 0u] : far;
-                            } else {
-                                wv[i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(wres, in ? col[i] * 4u : 0xFFFFFFF0u, 0, 0));
-                            }
+                        for (int i = 0; i < E; ++i) {
+                            const float far = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(wres, e + i < n && !near(col.at(i)) ? col.at(i) * 4u : 0xFFFFFFF0u, 0, 0));
+                            wv[i] = near(col.at(i)) ? head[near(col.at(i)) ? col.at(i) : 0u] : far;
                         }
 #pragma unroll
-                        for (int i = 0; i < kAtOnce; ++i) acc += e + i < n ? (double)wv[i] * (double)__uint_as_float(val[i]) : 0.0;
+                        for (int i = 0; i < E; ++i) acc += e + i < n ? (double)wv[i] * (double)__uint_as_float(val.at(i)) : 0.0;
+                    };
+                    for (int e0 = 0; __any(e0 < n); e0 += kAtOnce * LPR) {
+                        if (brief && !__any(e0 + 2 * LPR < n)) {       // the rest of the four rows
+                            if (__any(e0 + LPR < n)) take(std::integral_constant<int, 2>{}, e0);
+                            else take(std::integral_constant<int, 1>{}, e0);
+                            break;
+                        }
+                        take(std::integral_constant<int, kAtOnce>{}, e0);
                     }
                     acc += dpp_move<0xB1, 0xF>(acc);
                     acc += dpp_move<0x4E, 0xF>(acc);

@@ -116,6 +116,12 @@ def test_sparse_rows_longer_than_a_batch_takes(m, kind):
     _check(out, z, w.cpu().numpy().astype(np.float64), 0.01, wl.HINGE)
 
 
+def test_short_sparse_rows_with_columns_on_both_sides_of_the_head():
+    """Times, with a margin of a sixth: four entries to a lane whatever the row's length, each waiting for the one before, took 80 us instead of 59."""
+    lens = np.random.default_rng(1).integers(0, 21, 1000000)
+    assert _best_us(*_sparse(lens, 30000)[:3])[0] <= 69.0
+
+
 def test_long_sparse_rows_keep_a_wave_busy():
     """Times, with a margin of a third and of two: 16 lanes to such rows took 71 us instead of 37 (30 for short rows), and
     1530 instead of 322."""
@@ -132,7 +138,8 @@ def test_long_sparse_rows_keep_a_wave_busy():
     (37, 5, 5000), (5000, 3, 5000), (401000, 9, 5000), (401000, 70, 5000),
     (1000, 200, 5000),                            # (a wave to a row)
     (20000, 110, 30000), (401000, 70, 30000),     # columns in the copied head and behind it; rows of 256 entries and of more among them
-    (401000, 9, 200000)])                         # columns mostly behind the head
+    (401000, 9, 200000),                          # columns mostly behind the head
+    (401000, 29, 5000), (401000, 29, 30000), (401000, 29, 200000)])      # 64 entries and the rest of a row, two to a lane and one
 def test_sparse_rows_four_entries_a_lane(m, mean, d):
     """Rows of 0 to 3 * mean entries from any entry of the arrays on, the last one at the arrays' end; the first row_ptr is not zero."""
     rng = np.random.default_rng(m + mean)
