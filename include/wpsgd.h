@@ -300,8 +300,10 @@ int wpsgd_stream_rows(const wpsgd_matrix *X, int groups, int64_t rows_per_group,
 
 const char *wpsgd_strerror(int status);
 int wpsgd_last_hip_error(void);           /* hipError_t of the last failed HIP call on this thread */
-/* Writes a short description of the kernel the given problem would run with chains of a thousand steps
- * or more (for logs and the tuner), e.g. "dense_reg f32 logistic nt=256 ept=16 vec=4 B=4 P=2".  HOST.
+/* Writes a short description of the kernel the given problem would run (for logs and the tuner), e.g.
+ * "dense_reg f32 logistic nt=256 ept=16 vec=4 B=4 P=2".  HOST.  It does not see the chains' lengths: a kernel
+ * that only chains of some hundred steps and more go to stands at the end, long=pipelined (block_steps 16,
+ * prefetch 7) or long=octets (block_steps 8).
  * nt: threads that own columns of the model; scouts=S: S waves beside them that prepare blocks of steps.
  * vec: elements per load of rows that are whole 16-byte pieces, else 1; load=L: rows that are not are
  * fetched L elements at a time all the same.                                                          */

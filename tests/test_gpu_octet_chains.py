@@ -217,5 +217,8 @@ def test_workspace_without_room_for_records():
     X, yg = api.Matrix(m, d, dense=dev), torch.from_numpy(y).cuda()
     whole = api.wpsgd_run_chains_workspace(X, len(STEPS), wl.LOGISTIC)
     ws = torch.empty(whole - len(STEPS) * d * 4, dtype=torch.uint8, device="cuda")
+    with pytest.raises(api.WpsgdError) as err:             # (but a plan that names the kernel is not given another)
+        api.wpsgd_run_chains(X, yg, STEPS, 0.5, 1e-3, wl.LOGISTIC, 9, workspace=ws, plan={"block_steps": 8})
+    assert err.value.status == api.WORKSPACE_TOO_SMALL
     W = api.wpsgd_run_chains(X, yg, STEPS, 0.5, 1e-3, wl.LOGISTIC, 9, workspace=ws)
     _compare(W.cpu().numpy(), orc.run_chains(orc.Dense(host), y, STEPS, 0.5, 1e-3, wl.LOGISTIC, 9)[0], TOL)
