@@ -765,6 +765,33 @@ static size_t delay_ring_bytes(const wpsgd_matrix *X, int k, int tau)
 // a table of 32 bytes per row: what the Check function needs of a row and not of the model
 static size_t delay_table_bytes(const wpsgd_matrix *X) { return align256((size_t)X->m * 32); }
 
+// Teams of workgroups for the servers of a call under the Check function: the smallest number of samples per member at which all members
+// find a compute unit.  What a team costs are some ten exchanges of 8 us, one per acceptance, mostly at the start, so short servers
+// stay alone (fp32, d = 1024, m = 4000, 16 servers of 200 samples: 114 us alone, 146 in teams; 4 of up to 600: 247 and 113), and so does
+// every server where the longest would gain little.
+constexpr int64_t kDelayTeamShare = 32, kDelayTeamWorth = 384, kDelayVisitsWorth = 96;
+static int64_t delay_team_share(int k, const int64_t *n_samples, int *helpers)
+{
+    *helpers = 0;
+    int64_t most = 0;
+    for (int i = 0; i < k; ++i) most = std::max(most, n_samples[i]);
+    const int units = compute_units();
+    if (k >= units || most < kDelayTeamWorth || most > ((int64_t)1 << 30)) return 0;
+    auto members = [&](int64_t share) {
+        int64_t sum = 0;
+        for (int i = 0; i < k; ++i) sum += delay_team_size(n_samples[i], share);
+        return sum;
+    };
+    int64_t lo = kDelayTeamShare, hi = most;       // hi: one workgroup per server
+    while (lo < hi) {
+        const int64_t mid = lo + (hi - lo) / 2;
+        if (members(mid) <= units) hi = mid;
+        else lo = mid + 1;
+    }
+    *helpers = (int)(members(lo) - k);
+    return *helpers > 0 && lo <= most - most / 8 ? lo : 0;
+}
+
 size_t wpsgd_run_delay_chains_workspace(const wpsgd_matrix *X, int k, int tau)
 {
     if (check_matrix(X) != WPSGD_OK || !X->dense || k < 1 || tau < 0 || tau > kDelayMaxTau) return 0;
@@ -809,13 +836,23 @@ int wpsgd_run_delay_chains(const wpsgd_matrix *X, const float *y, int k, const i
     a.ring = reinterpret_cast<double *>(base + align256((size_t)k * sizeof(int64_t)));
     a.W = W;
     a.accepted = accepted;
-    // The row table costs a pass over the whole data set: it pays when the servers together visit a
-    // good part of the rows (the kernel that uses it is only chosen under the Check function).
-    int64_t visits = 0;
-    for (int i = 0; i < k; ++i) visits += std::min<int64_t>(n_samples[i], INT64_MAX / 2 / k);
-    a.row_table = (check != 0 && visits >= X->m / 4)
+    // The table of what the Check function needs of a row costs a pass over the data set: one entry per row where the servers
+    // together visit a good part of the rows, else one per visit.  Servers of a few dozen samples do without (fp32, d = 4096,
+    // m = 65536: 200 servers of 50 samples 98 us without, 112 with; one of 200 samples 242 and 125).
+    int64_t visits = 0, most = 0;
+    for (int i = 0; i < k; ++i) {
+        visits += std::min<int64_t>(n_samples[i], INT64_MAX / 2 / k);
+        most = std::max(most, n_samples[i]);
+    }
+    const bool per_visit = visits < X->m / 4;
+    a.row_table = check != 0 && (!per_visit || most >= kDelayVisitsWorth)
                       ? base + align256((size_t)k * sizeof(int64_t)) + align256(delay_ring_bytes(X, k, tau))
                       : nullptr;
+    a.visits = per_visit ? visits : 0;
+    if (a.row_table && (size_t)k * kDelayTeamWords * sizeof(uint64_t) <= delay_ring_bytes(X, k, tau)) {
+        a.team_share = delay_team_share(k, n_samples, &a.helpers);
+        a.team = a.team_share ? reinterpret_cast<uint64_t *>(a.ring) : nullptr;      // (no kernel that has teams keeps its iterates there)
+    }
     const bool start_ok = !w_start || (uintptr_t)w_start % 4 == 0;
     if (!start_ok) return WPSGD_INVALID_ARG;
     hipError_t e = launch_delay_servers(a, (int)X->dtype, dense_vec(X), buffer_vec(X), s);

@@ -73,11 +73,24 @@ struct DelayArgs {
     int loss, tau, check;
     uint32_t seed_lo, seed_hi;
     double *ring;             // DEVICE, k x (max(tau,1)+2) x d: the iterates each server keeps
-    void *row_table;          // DEVICE, m x 32 bytes: room for what the Check function needs of each row, or
-                              // NULL when the servers visit too few rows for such a table to pay
+    void *row_table;          // DEVICE, m x 32 bytes: room for what the Check function needs of each row, or of each visit
+    int64_t visits;           // samples of all servers together where they are so few that the table has an entry per visit
+                              // (the servers' samples one server after the other), 0: an entry per row
     float *W;                 // k x d out
     int64_t *accepted;        // k out: updates each server has made
+    uint64_t *team;           // DEVICE, k x kDelayTeamWords: tables of the servers' teams (cleared by the launch), or NULL: no teams
+    int64_t team_share;       // samples per member that the teams are sized for
+    int helpers;              // members beyond the first, all servers together
 };
+
+// Several workgroups per server under the Check function (chain_delay.hip): how many, and the words of a team's table.
+constexpr int kDelayTeamMax = 64;
+constexpr int kDelayTeamWords = 176;
+__host__ __device__ inline int delay_team_size(int64_t n, int64_t share)
+{
+    const int64_t members = (n + share - 1) / share;
+    return members < 1 ? 1 : members > kDelayTeamMax ? kDelayTeamMax : (int)members;
+}
 
 enum class Family { DenseReg, DenseMem, Csr };
 
