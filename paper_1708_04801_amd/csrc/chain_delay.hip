@@ -334,32 +334,36 @@ __global__ __launch_bounds__(kDelayThreads) void delay_server_reg_kernel(DelayAr
         for (int i = 0; i < R1; ++i) n2[i] = v[0];
     }
 
+    // Rows and labels of the next PF samples are on their way at any time; beyond the end the last sample's again, so that no request
+    // sits under a branch, where each would be waited for on the spot, and labels travel with the rows (a scalar load would be
+    // drained by the exchange of sums).  128 servers of up to 2000 samples, fp32, d = 4096, tau = 0, without Check: 2.29 -> 1.97 ms,
+    // without the squared lengths that only Check wants 1.61.
     RowWindow win;
     win.init(a.seed_lo, a.seed_hi, (uint32_t)chain, (uint32_t)a.m);
     Frag x[PF];
     float ys[PF];
     auto request = [&](int u, int64_t s) {
-        const uint32_t row = win.get(s);
+        const uint32_t row = win.get(s < n ? s : n - 1);
+        uint32_t lane_row;
+        asm volatile("v_mov_b32 %0, %1" : "=v"(lane_row) : "s"(row));
+        ys[u] = a.y[lane_row];
         const __amdgpu_buffer_rsrc_t rx = make_rsrc(X + (int64_t)row * row_stride, row_bytes);
 #pragma unroll
         for (int c = 0; c < Frag::kChunks; ++c) x[u].load_chunk(c, rx, off[c]);
-        ys[u] = a.y[row];
     };
+    if (n > 0) {
 #pragma unroll
-    for (int u = 0; u < PF; ++u)
-        if (u < n) request(u, u);
+        for (int u = 0; u < PF; ++u) request(u, u);
+    }
 
     int64_t J = 0;
-    for (int64_t s0 = 0; s0 < n; s0 += PF) {
-#pragma unroll
-        for (int u = 0; u < PF; ++u) {
-            const int64_t s = s0 + u;
-            if (s >= n) break;
+    auto sample = [&](int u, int64_t s, auto more_tag) {
+        {
             double xe[EPT];
 #pragma unroll
             for (int e = 0; e < EPT; ++e) xe[e] = (double)x[u].at(e);
             const double y = (double)ys[u];
-            if (s + PF < n) request(u, s + PF);
+            if constexpr (decltype(more_tag)::value) request(u, s + PF);
 
             double v[R1 + 1];                        // v[i] = w_{J-i}.x, v[R1] = x.x
 #pragma unroll
@@ -424,14 +428,24 @@ __global__ __launch_bounds__(kDelayThreads) void delay_server_reg_kernel(DelayAr
                     r[0][e] = w;
                     u2[0] += w * w;
                 }
-                block_sums(u2, std::integral_constant<int, 1>{});
+                if (a.check) {                       // (the squared lengths are the tests' business)
+                    block_sums(u2, std::integral_constant<int, 1>{});
 #pragma unroll
-                for (int i = R1 - 1; i >= 1; --i) n2[i] = n2[i - 1];
-                n2[0] = u2[0];
+                    for (int i = R1 - 1; i >= 1; --i) n2[i] = n2[i - 1];
+                    n2[0] = u2[0];
+                }
                 ++J;
             }
         }
+    };
+    int64_t s0 = 0;
+    for (; s0 + PF <= n; s0 += PF) {
+#pragma unroll
+        for (int u = 0; u < PF; ++u) sample(u, s0 + u, std::true_type{});
     }
+#pragma unroll
+    for (int u = 0; u < PF; ++u)
+        if (s0 + u < n) sample(u, s0 + u, std::false_type{});
 
     float *out = a.W + (int64_t)chain * a.d;
 #pragma unroll
@@ -1327,6 +1341,25 @@ hipError_t launch_reg(const DelayArgs &a, bool staged, hipStream_t s, bool *done
     return hipSuccess;
 }
 
+// bfloat16 rows that are no whole 16-byte pieces: the per-sample kernel with a load per element (81 servers of 400 samples, d = 301,
+// tau = 0, without Check: 216 us, 1024 with the ring in memory; 30 of up to 1000, d = 4001, tau = 4, under it: 1.62 ms, 15.2).
+hipError_t launch_reg_elements(const DelayArgs &a, hipStream_t s, bool *done)
+{
+    const int r1 = (a.tau > 1 ? a.tau : 1) + 1;
+    *done = true;
+#define WPSGD_DELAY_REG(EPT, R1)                                                                                 \
+    if (a.d <= (int64_t)kDelayThreads * EPT && r1 == R1) {                                                       \
+        hipLaunchKernelGGL((delay_server_reg_kernel<uint16_t, EPT, 1, R1, kDelayAhead>), dim3(a.k), dim3(kDelayThreads), 0, s, a); \
+        return hipGetLastError();                                                                                \
+    }
+    WPSGD_DELAY_REG(2, 2) WPSGD_DELAY_REG(2, 3) WPSGD_DELAY_REG(2, 4) WPSGD_DELAY_REG(2, 5)
+    WPSGD_DELAY_REG(8, 2) WPSGD_DELAY_REG(8, 3) WPSGD_DELAY_REG(8, 4) WPSGD_DELAY_REG(8, 5)
+    WPSGD_DELAY_REG(16, 2) WPSGD_DELAY_REG(16, 3) WPSGD_DELAY_REG(16, 4) WPSGD_DELAY_REG(16, 5)
+#undef WPSGD_DELAY_REG
+    *done = false;
+    return hipSuccess;
+}
+
 template <typename TX, int VEC>
 hipError_t launch_reach(const DelayArgs &a, hipStream_t s)
 {
@@ -1347,9 +1380,10 @@ hipError_t launch_reach(const DelayArgs &a, hipStream_t s)
 
 hipError_t launch_delay_servers(const DelayArgs &a, int dtype, int vec, int buffer_vec, hipStream_t s)
 {
-    if (buffer_vec > 1 && a.tau <= kDelayRegMaxTau && a.d * (dtype == WPSGD_BF16 ? 2 : 4) < (int64_t)1 << 31) {
+    if (a.tau <= kDelayRegMaxTau && (buffer_vec > 1 || dtype == WPSGD_BF16) && a.d * (dtype == WPSGD_BF16 ? 2 : 4) < (int64_t)1 << 31) {
         bool done = false;
-        const hipError_t e = dtype == WPSGD_BF16 ? launch_reg<uint16_t, 8>(a, vec > 1, s, &done)
+        const hipError_t e = buffer_vec == 1 ? launch_reg_elements(a, s, &done)
+                             : dtype == WPSGD_BF16 ? launch_reg<uint16_t, 8>(a, vec > 1, s, &done)
                                                  : launch_reg<float, 4>(a, vec > 1, s, &done);
         if (done) return e;
     }
