@@ -595,6 +595,7 @@ static hipError_t launch_sliced(Plan p, const ChainArgs &a, hipStream_t s)
 // Periodic averaging: after each of `count` spans the models are averaged into `average`, from which the next span
 // starts.  Everything the spans share - header, shuffled order, weights - is prepared once per call, so that a span
 // is its launches and nothing else (25 spans of 200 steps, 16 chains, d = 1024: 1.03 ms with a header copied per span, 0.92 without).
+constexpr int kStartModelsMost = 63;       // chains whose models each chain averages for itself
 struct Spans {
     int64_t count;
     const double *weights;         // HOST, k entries
@@ -729,9 +730,26 @@ static int run_chains_from(const wpsgd_matrix *X, const float *y, int k, const i
         e = launch_zero_words(static_cast<uint32_t *>(state_dev), ring / sizeof(uint32_t), s);
         if (e != hipSuccess) return hip_fail(e);
     }
+    // Between two spans the chains of short rows form the average themselves (start_values), one launch instead of two: the models then
+    // lie in two places in turn, W and a part of the workspace that the plan leaves idle (the vectors of the HBM-state kernels, else
+    // the shuffled order).  Every chain reads all models, 16 rows at once, in the order in which combine_kernel adds fewer than
+    // 64.  us a span, two launches -> one, spans of 40 to 200 steps: d = 64 hinge, 16 chains 18.9 -> 15.3, 63 chains 27.3 -> 17.7;
+    // d = 128 logistic, 32 chains 21.3 -> 17.4; d = 64 logistic, 32 chains of 5 to 20 steps 11.7 -> 6.7.  Longer rows gain nothing
+    // or lose (blocks of eight steps: d = 1024, 16 chains 29.4 -> 30.2, bf16 d = 2048 34.8 -> 45.8: a workgroup alone draws k rows more
+    // slowly than the average's own launch does).
+    float *other = nullptr;
+    if (spans && spans->count > 1 && p.family == Family::DenseReg && p.scouts > 0 && !p.octets && k <= kStartModelsMost) {
+        const size_t models = (size_t)k * (size_t)X->d * sizeof(float), used = h.total + perm_bytes(X->m);
+        if (workspace_bytes >= used + models) other = reinterpret_cast<float *>(ws + used);
+        else if (!a.perm && models <= perm_bytes(X->m)) other = reinterpret_cast<float *>(perm_dev);
+    }
     for (int64_t span = 0; span < (spans ? spans->count : 1); ++span) {
         a.span = span;
-        if (span > 0) {
+        if (span > 0 && other) {
+            a.models = a.W;
+            a.model_weights = spans->weights_dev;
+            a.W = a.W == W ? other : W;
+        } else if (span > 0) {
             a.w_start = spans->average;
             // the helpers' counters start at zero (the first time they come zeroed with the header; blocks of eight steps count on)
             if (a.helpers > 0 && !p.octets) e = launch_zero_words(a.progress, (size_t)k * 2 + 16, s);
@@ -740,8 +758,8 @@ static int run_chains_from(const wpsgd_matrix *X, const float *y, int k, const i
         e = a.slices > 1 ? launch_sliced(p, a, s) : launch_whole(p, a, s);
         if (e == hipErrorInvalidValue) return WPSGD_UNSUPPORTED;
         if (e != hipSuccess) return hip_fail(e);
-        if (spans) {
-            e = launch_combine(W, spans->weights_dev, k, X->d, spans->average, s);
+        if (spans && (!other || span + 1 == spans->count)) {
+            e = launch_combine(a.W, spans->weights_dev, k, X->d, spans->average, s);
             if (e != hipSuccess) return hip_fail(e);
         }
     }

@@ -31,6 +31,7 @@
 
 #include "device_utils.h"
 #include "internal.h"
+#include "step_rows.h"
 
 namespace wpsgd {
 namespace {
@@ -104,7 +105,7 @@ __global__ __launch_bounds__(kBlockThreads) void chain_dense_block_kernel(ChainA
     const int d = (int)a.d;
     float *out = a.W + (int64_t)chain * a.d;
     if (n == 0) {
-        for (int c = (int)threadIdx.x; c < d; c += kBlockThreads) out[c] = a.w_start ? a.w_start[c] : 0.0f;
+        for (int c = (int)threadIdx.x; c < d; c += kBlockThreads) out[c] = start_value(a, c);
         return;
     }
     const int64_t nblk = (n + kBlock - 1) / kBlock, beats = nblk + kScouts;
@@ -114,12 +115,9 @@ __global__ __launch_bounds__(kBlockThreads) void chain_dense_block_kernel(ChainA
         // ------------------------------------------------------------------------- the chain
         __builtin_amdgcn_s_setprio(2);
         TV v[CE];
+        start_values(a, v, [&](int e) { return lane * CE + e; });
 #pragma unroll
-        for (int e = 0; e < CE; ++e) {
-            const int col = lane * CE + e;
-            v[e] = (a.w_start && col < d) ? (TV)a.w_start[col] : (TV)0;
-            model[col] = v[e];
-        }
+        for (int e = 0; e < CE; ++e) model[lane * CE + e] = v[e];
         double s_w = 1.0;
 #pragma unroll 1
         for (int q = 0; q < kScouts; ++q) section_barrier();

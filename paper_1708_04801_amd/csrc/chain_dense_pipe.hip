@@ -161,7 +161,7 @@ __global__ __launch_bounds__((Team<TX, LOSS, C>::kWaves) * kWave) void chain_den
     const int d = (int)a.d;
     float *out = a.W + (int64_t)a.order[cb] * a.d;
     if (n == 0) {
-        for (int c = (int)threadIdx.x; c < d; c += Us::kWaves * kWave) out[c] = a.w_start ? a.w_start[c] : 0.0f;
+        for (int c = (int)threadIdx.x; c < d; c += Us::kWaves * kWave) out[c] = start_value(a, c);
         return;
     }
     const int64_t nblk = (n + kBlock - 1) / kBlock;
@@ -209,8 +209,7 @@ __global__ __launch_bounds__((Team<TX, LOSS, C>::kWaves) * kWave) void chain_den
         __builtin_amdgcn_s_setprio(2);
         const int w0 = role - Us::kModel, first = w0 * CE * kWave, col = first + lane * CE;      // (of the wave, of the lane)
         TV v[CE];
-#pragma unroll
-        for (int e = 0; e < CE; ++e) v[e] = (a.w_start && col + e < d) ? (TV)a.w_start[col + e] : (TV)0;
+        start_values(a, v, [&](int e) { return col + e; });
         double s_w = 1.0, eos_w = a.eta;
         TV xu[CE][kBlock];                    // rows of the block to update with: this lane's columns
         f32x4 xd[4 * CE];                     // rows of the block to multiply with: row j, columns 16*i + 4*g ..

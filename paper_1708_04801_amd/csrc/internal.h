@@ -54,6 +54,10 @@ struct ChainArgs {
     // outputs / scratch
     float *W;                 // k x d
     void *state;              // k x d model vectors in HBM (state_in_hbm plans), else unused
+    // Periodic averaging: the chains start from sum_i model_weights[i] * models[i] (k x d, DEVICE) instead of w_start, when models is
+    // set (kernels that call start_values only)
+    const float *models;
+    const double *model_weights;
 };
 
 // position in the sample stream of workgroup b's first step of this launch

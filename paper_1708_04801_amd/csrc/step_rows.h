@@ -1,4 +1,4 @@
-// Which rows a chain's steps visit.
+// Which rows a chain's steps visit, and where a chain starts.
 #pragma once
 #include "device_utils.h"
 #include "internal.h"
@@ -76,5 +76,61 @@ struct StepRows {
         return sample_row(seed_lo, seed_hi, chain, (uint64_t)(step0 + t), m);
     }
 };
+
+// Where a chain starts: from a vector, from zero, or from the weighted sum of the models of the span before (periodic averaging),
+// which every chain forms for itself, in the order and precision of combine_kernel: the same bits, without its launch between two
+// spans.  What it costs is a trip to memory per kStartModels rows, whose loads are all on their way at once: none is conditional
+// (with eight rows and a branch per row 16 chains, d = 64, hinge took 17.9 us a span, so 15.1).  The rule is in api.hip.
+constexpr int kStartModels = 16;
+template <typename TV, int N, typename F>
+__device__ inline void start_values(const ChainArgs &a, TV (&v)[N], F &&column)
+{
+    if (!a.models) {
+#pragma unroll
+        for (int e = 0; e < N; ++e) v[e] = (a.w_start && column(e) < a.d) ? (TV)a.w_start[column(e)] : (TV)0;
+        return;
+    }
+    double acc[N];
+    int64_t at[N];
+#pragma unroll
+    for (int e = 0; e < N; ++e) {
+        acc[e] = 0.0;
+        at[e] = column(e) < a.d ? column(e) : 0;
+    }
+    // (quadruples of columns are consecutive: every caller's columns are)
+    const bool quads = N % 4 == 0 && a.d % 4 == 0;
+    for (int i = 0; i < a.k; i += kStartModels) {
+        float x[kStartModels][N];
+        double w[kStartModels];
+#pragma unroll
+        for (int u = 0; u < kStartModels; ++u) {
+            const int r = i + u < a.k ? i + u : a.k - 1;
+            w[u] = a.model_weights[r];
+            const float *row = a.models + (int64_t)r * a.d;
+            if (quads) {
+#pragma unroll
+                for (int e = 0; e + 3 < N; e += 4) {
+                    const float4 q = *reinterpret_cast<const float4 *>(row + at[e]);
+                    x[u][e] = q.x; x[u][e + 1] = q.y; x[u][e + 2] = q.z; x[u][e + 3] = q.w;
+                }
+            } else {
+#pragma unroll
+                for (int e = 0; e < N; ++e) x[u][e] = row[at[e]];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kStartModels; ++u)
+#pragma unroll
+            for (int e = 0; e < N; ++e) acc[e] += i + u < a.k ? w[u] * (double)x[u][e] : 0.0;
+    }
+#pragma unroll
+    for (int e = 0; e < N; ++e) v[e] = column(e) < a.d ? (TV)(float)acc[e] : (TV)0;
+}
+__device__ inline float start_value(const ChainArgs &a, int column)
+{
+    float v[1];
+    start_values(a, v, [&](int) { return column; });
+    return v[0];
+}
 
 }  // namespace wpsgd

@@ -1,0 +1,31 @@
+"""Periodic averaging of short rows: the chains of a span form the average of the span before by themselves.  Compared, bit for bit,
+with one call per span and the averaging entry point between them."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1708_04801_amd import api
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("k", [1, 2, 15, 16, 17, 32, 33, 63, 64])
+@pytest.mark.parametrize("d", [4, 5, 63, 64, 66, 128, 252, 256])
+@pytest.mark.parametrize("loss,bf16,sampling", [(api.HINGE, False, api.SAMPLE_STREAM), (api.LOGISTIC, False, api.SAMPLE_SHARDS),
+                                                (api.LOGISTIC, True, api.SAMPLE_STREAM), (api.HINGE, True, api.SAMPLE_SHARDS)])
+def test_spans_of_short_rows_equal_one_call_per_span(k, d, loss, bf16, sampling):
+    rng = np.random.default_rng(1000 * k + d)
+    m = 70
+    X = torch.from_numpy((rng.standard_normal((m, d)) / np.sqrt(d)).astype(np.float32)).cuda()
+    X = api.Matrix(m, d, dense=X.to(torch.bfloat16) if bf16 else X)
+    y = torch.from_numpy(np.where(rng.random(m) < 0.5, 1.0, -1.0).astype(np.float32)).cuda()
+    steps = rng.integers(0, 40, k).astype(np.int64)         # idle chains among them
+    steps[0] = 40
+    eta, lam, spans = 0.3, 1e-3, 4
+    w = torch.full((d,), 0.01, device="cuda")
+    got = api.wpsgd_run_spans(X, y, steps, spans, eta, lam, loss, 11, w_start=w, sampling=sampling)
+    a = api.wpsgd_weights(steps, eta, lam)
+    for s in range(spans):
+        W = api.wpsgd_run_chains_from(X, y, steps, eta, lam, loss, 11, w_start=w, step_offsets=s * steps, sampling=sampling)
+        w = api.wpsgd_combine(W, a)
+    assert torch.equal(got, w)
