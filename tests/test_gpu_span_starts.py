@@ -29,3 +29,16 @@ def test_spans_of_short_rows_equal_one_call_per_span(k, d, loss, bf16, sampling)
         W = api.wpsgd_run_chains_from(X, y, steps, eta, lam, loss, 11, w_start=w, step_offsets=s * steps, sampling=sampling)
         w = api.wpsgd_combine(W, a)
     assert torch.equal(got, w)
+
+
+@pytest.mark.parametrize("k", [1, 15, 16, 17, 63, 64])
+@pytest.mark.parametrize("d", [1, 63, 64, 65, 16383, 16384, 16385])
+def test_average_of_few_models(k, d):
+    """One rounding of an fp64 sum: half a unit in the last place of fp32, and as much again of fp64 per addition."""
+    rng = np.random.default_rng(k + d)
+    W = rng.standard_normal((k, d)).astype(np.float32)
+    a = rng.random(k)
+    got = api.wpsgd_combine(torch.from_numpy(W).cuda(), a).cpu().numpy().astype(np.float64)
+    want = (a[:, None] * W.astype(np.float64)).sum(axis=0)
+    bound = np.abs(want) * 2.0**-24 + (np.abs(a[:, None] * W).sum(axis=0) * k) * 2.0**-52 + 2.0**-149
+    assert (np.abs(got - want) <= bound).all()
