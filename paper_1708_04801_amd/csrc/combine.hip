@@ -3,7 +3,7 @@
 //
 // The average is a pure stream over the k x d matrix W: every column is owned by one thread
 // (four adjacent columns when alignment allows), rows are walked in ascending order with
-// several loads in flight, and the sum is kept in fp64 and rounded once.  When there are too
+// several loads in flight, and the sum is kept in fp64 by fused multiply-adds and rounded once.  When there are too
 // few columns to fill the chip, the rows are split over RS slices of a workgroup whose partial
 // sums are added in slice order through LDS, so the result does not depend on timing.
 #include "device_utils.h"
@@ -58,7 +58,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(6))) vo
             for (int u = 0; u < UNROLL; ++u) {
                 const double w = a[i + u];
 #pragma unroll
-                for (int j = 0; j < VEC; ++j) acc[j] += w * (double)x[u][j];
+                for (int j = 0; j < VEC; ++j) acc[j] = fma(w, (double)x[u][j], acc[j]);
             }
         }
         for (; i < i1; i += TAIL) {
@@ -77,7 +77,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(6))) vo
                 if (u < left) {
                     const double w = a[i + u];
 #pragma unroll
-                    for (int j = 0; j < VEC; ++j) acc[j] += w * (double)x[u][j];
+                    for (int j = 0; j < VEC; ++j) acc[j] = fma(w, (double)x[u][j], acc[j]);
                 }
             }
         }
@@ -129,7 +129,10 @@ __global__ __launch_bounds__(kWave) void combine_small_kernel(const float *__res
             w[u] = a[r];
         }
 #pragma unroll
-        for (int u = 0; u < AHEAD; ++u) acc += i + u < k ? w[u] * (double)x[u] : 0.0;
+        for (int u = 0; u < AHEAD; ++u) {
+            const double t = fma(w[u], (double)x[u], acc);
+            acc = i + u < k ? t : acc;
+        }
     }
     if (col < d) out[col] = (float)acc;
 }

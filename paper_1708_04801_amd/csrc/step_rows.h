@@ -121,7 +121,10 @@ __device__ inline void start_values(const ChainArgs &a, TV (&v)[N], F &&column)
 #pragma unroll
         for (int u = 0; u < kStartModels; ++u)
 #pragma unroll
-            for (int e = 0; e < N; ++e) acc[e] += i + u < a.k ? w[u] * (double)x[u][e] : 0.0;
+            for (int e = 0; e < N; ++e) {
+                const double t = fma(w[u], (double)x[u][e], acc[e]);
+                acc[e] = i + u < a.k ? t : acc[e];
+            }
     }
 #pragma unroll
     for (int e = 0; e < N; ++e) v[e] = column(e) < a.d ? (TV)(float)acc[e] : (TV)0;
