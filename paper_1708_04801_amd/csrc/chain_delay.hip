@@ -277,8 +277,8 @@ __global__ __launch_bounds__(kDelayThreads) void delay_server_kernel(DelayArgs a
 }
 
 // The ring in registers.  R1 = max(tau, 1) + 1 iterates are kept: r[i] is w_{J-i}; before J reaches i
-// the slot holds w_0, which is what an index below zero means.  n2[i] is |w_{J-i}|^2.
-template <typename TX, int EPT, int VEC, int R1, int PF>
+// the slot holds w_0, which is what an index below zero means.  n2[i] is |w_{J-i}|^2 (CHECK only).
+template <typename TX, int EPT, int VEC, int R1, int PF, bool CHECK>
 __global__ __launch_bounds__(kDelayThreads) void delay_server_reg_kernel(DelayArgs a)
 {
     constexpr int NT = kDelayThreads, NW = kDelayWaves;
@@ -318,7 +318,7 @@ __global__ __launch_bounds__(kDelayThreads) void delay_server_reg_kernel(DelayAr
         parity ^= 1;
     };
 
-    double r[R1][EPT], n2[R1];
+    double r[R1][EPT], n2[CHECK ? R1 : 1];
     {
         double v[1] = {0.0};
 #pragma unroll
@@ -329,24 +329,24 @@ __global__ __launch_bounds__(kDelayThreads) void delay_server_reg_kernel(DelayAr
             for (int i = 0; i < R1; ++i) r[i][e] = w;
             v[0] += w * w;
         }
-        block_sums(v, std::integral_constant<int, 1>{});
+        if constexpr (CHECK) {                       // (the squared lengths are the tests' business)
+            block_sums(v, std::integral_constant<int, 1>{});
 #pragma unroll
-        for (int i = 0; i < R1; ++i) n2[i] = v[0];
+            for (int i = 0; i < R1; ++i) n2[i] = v[0];
+        }
     }
 
     // Rows and labels of the next PF samples are on their way at any time; beyond the end the last sample's again, so that no request
     // sits under a branch, where each would be waited for on the spot, and labels travel with the rows (a scalar load would be
-    // drained by the exchange of sums).  128 servers of up to 2000 samples, fp32, d = 4096, tau = 0, without Check: 2.29 -> 1.97 ms,
-    // without the squared lengths that only Check wants 1.61.
+    // drained by the exchange of sums, its address takes no registers).  128 servers of up to 400 samples, fp32, d = 4096, tau = 0,
+    // without Check: 470 -> 301 us.
     RowWindow win;
     win.init(a.seed_lo, a.seed_hi, (uint32_t)chain, (uint32_t)a.m);
     Frag x[PF];
     float ys[PF];
     auto request = [&](int u, int64_t s) {
         const uint32_t row = win.get(s < n ? s : n - 1);
-        uint32_t lane_row;
-        asm volatile("v_mov_b32 %0, %1" : "=v"(lane_row) : "s"(row));
-        ys[u] = a.y[lane_row];
+        ys[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(make_rsrc(a.y + row, 4u), 0, 0, 0));
         const __amdgpu_buffer_rsrc_t rx = make_rsrc(X + (int64_t)row * row_stride, row_bytes);
 #pragma unroll
         for (int c = 0; c < Frag::kChunks; ++c) x[u].load_chunk(c, rx, off[c]);
@@ -356,19 +356,26 @@ __global__ __launch_bounds__(kDelayThreads) void delay_server_reg_kernel(DelayAr
         for (int u = 0; u < PF; ++u) request(u, u);
     }
 
+    // What a sample costs here is issue and the exchange, so more servers than compute units want two or three workgroups on each.  The
+    // sample's code therefore stands once per place in a round, and calls under Check have a kernel of their own: with the last round
+    // written out a second time, and one kernel for both, it took up to 115 registers more and half the waves per SIMD (us, 600
+    // servers of up to 400 samples, fp32: d = 2047, tau = 4, under Check 1141 -> 726; d = 4096, tau = 0, without it 780 -> 540).
     int64_t J = 0;
-    auto sample = [&](int u, int64_t s, auto more_tag) {
-        {
+    for (int64_t s0 = 0; s0 < n; s0 += PF) {
+#pragma unroll
+        for (int u = 0; u < PF; ++u) {
+            const int64_t s = s0 + u;
+            if (s >= n) break;
             double xe[EPT];
 #pragma unroll
             for (int e = 0; e < EPT; ++e) xe[e] = (double)x[u].at(e);
             const double y = (double)ys[u];
-            if constexpr (decltype(more_tag)::value) request(u, s + PF);
+            request(u, s + PF);
 
             double v[R1 + 1];                        // v[i] = w_{J-i}.x, v[R1] = x.x
 #pragma unroll
             for (int i = 0; i <= R1; ++i) v[i] = 0.0;
-            if (a.check) {
+            if constexpr (CHECK) {
 #pragma unroll
                 for (int e = 0; e < EPT; ++e) {
                     v[R1] += xe[e] * xe[e];
@@ -389,7 +396,7 @@ __global__ __launch_bounds__(kDelayThreads) void delay_server_reg_kernel(DelayAr
             // no slope), then the intervals of the first call (the root), then the candidate's (the slope).
             bool keep = true;
             double g = 0.0;
-            if (a.check) {
+            if constexpr (CHECK) {
                 if (beta2 > 0.0) {
 #pragma unroll
                     for (int i = 0; i + 1 < R1; ++i)      // pairs (w_{J-i-1}, w_{J-i}) that some triple holds
@@ -428,7 +435,7 @@ __global__ __launch_bounds__(kDelayThreads) void delay_server_reg_kernel(DelayAr
                     r[0][e] = w;
                     u2[0] += w * w;
                 }
-                if (a.check) {                       // (the squared lengths are the tests' business)
+                if constexpr (CHECK) {
                     block_sums(u2, std::integral_constant<int, 1>{});
 #pragma unroll
                     for (int i = R1 - 1; i >= 1; --i) n2[i] = n2[i - 1];
@@ -437,15 +444,7 @@ __global__ __launch_bounds__(kDelayThreads) void delay_server_reg_kernel(DelayAr
                 ++J;
             }
         }
-    };
-    int64_t s0 = 0;
-    for (; s0 + PF <= n; s0 += PF) {
-#pragma unroll
-        for (int u = 0; u < PF; ++u) sample(u, s0 + u, std::true_type{});
     }
-#pragma unroll
-    for (int u = 0; u < PF; ++u)
-        if (s0 + u < n) sample(u, s0 + u, std::false_type{});
 
     float *out = a.W + (int64_t)chain * a.d;
 #pragma unroll
@@ -1274,6 +1273,15 @@ constexpr int kDelayAhead = 4;          // samples whose rows are in flight
 constexpr int kDelayBatch = 4;          // samples looked at side by side under Check
 constexpr int kDelaySlots = 8;          // rows in LDS or on their way there
 
+template <typename TX, int EPT, int VEC, int R1>
+void launch_sample(const DelayArgs &a, hipStream_t s)
+{
+    if (a.check)
+        hipLaunchKernelGGL((delay_server_reg_kernel<TX, EPT, VEC, R1, kDelayAhead, true>), dim3(a.k), dim3(kDelayThreads), 0, s, a);
+    else
+        hipLaunchKernelGGL((delay_server_reg_kernel<TX, EPT, VEC, R1, kDelayAhead, false>), dim3(a.k), dim3(kDelayThreads), 0, s, a);
+}
+
 // The batch kernel claims S row slots of LDS, which is more than a kernel may have without asking.
 template <typename TX, int EPT, int VEC, int R1, bool TEAM>
 bool launch_batch(const DelayArgs &a, hipStream_t s)
@@ -1331,7 +1339,7 @@ hipError_t launch_reg(const DelayArgs &a, bool staged, hipStream_t s, bool *done
         else if (!a.check && staged && a.tau >= 1 && a.m < (1 << 30) && launch_plain<TX, EPT, VEC, R1>(a, s))    \
             return hipGetLastError();                                                                            \
         else                                                                                                     \
-            hipLaunchKernelGGL((delay_server_reg_kernel<TX, EPT, VEC, R1, kDelayAhead>), dim3(a.k), dim3(kDelayThreads), 0, s, a); \
+            launch_sample<TX, EPT, VEC, R1>(a, s);                                                               \
         return hipGetLastError();                                                                                \
     }
     WPSGD_DELAY_REG(8, 2) WPSGD_DELAY_REG(8, 3) WPSGD_DELAY_REG(8, 4) WPSGD_DELAY_REG(8, 5)
@@ -1349,7 +1357,7 @@ hipError_t launch_reg_elements(const DelayArgs &a, hipStream_t s, bool *done)
     *done = true;
 #define WPSGD_DELAY_REG(EPT, R1)                                                                                 \
     if (a.d <= (int64_t)kDelayThreads * EPT && r1 == R1) {                                                       \
-        hipLaunchKernelGGL((delay_server_reg_kernel<uint16_t, EPT, 1, R1, kDelayAhead>), dim3(a.k), dim3(kDelayThreads), 0, s, a); \
+        launch_sample<uint16_t, EPT, 1, R1>(a, s);                                                               \
         return hipGetLastError();                                                                                \
     }
     WPSGD_DELAY_REG(2, 2) WPSGD_DELAY_REG(2, 3) WPSGD_DELAY_REG(2, 4) WPSGD_DELAY_REG(2, 5)
