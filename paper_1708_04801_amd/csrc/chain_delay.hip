@@ -982,9 +982,11 @@ __global__ __launch_bounds__(kDelayThreads) void delay_server_batch_kernel(Delay
                 for (int i = 0; i < R1; ++i) red[parity][mine * R1 + i][wave] = L[i];
             }
             if constexpr (TEAM) {
+                // (Records are those that the batch before asked for: an epoch's first batch has none.  What LDS still holds may be 256
+                // epochs old and carry this one's stamp.)
                 if (W > 1 && wave == 0) {
                     int whose;
-                    const uint32_t first = team_first_found(*(volatile uint32_t *)&others[lane], members >> lane & 1, epoch, whose);
+                    const uint32_t first = pos == 0 ? kTeamNone : team_first_found(*(volatile uint32_t *)&others[lane], members >> lane & 1, epoch, whose);
                     if (lane == 0) known[parity] = first;
                 }
             }
