@@ -701,7 +701,7 @@ __device__ inline bool window_passes(const double *L, const double (&n2)[R1], do
 //  * A member learns of the others' acceptances from their records, one load per batch that lands in LDS behind the rows
 //    (an ordinary load would wait for them).
 //  * Nobody waits for a workgroup that is not running: a team is made of those that have reported within some 0.1 ms of the
-//    owner's start (owners are launched first), the others leave.  All waits are bounded: an owner whose members do not
+//    owner's start (owners are launched first), the others leave when they see that an order has been given without them.  All waits are bounded: an owner whose members do not
 //    answer goes on alone from the base of the epoch, members without orders leave.
 // fp32, d = 4096, m = 65536, tau = 2, up to 8000 samples a server, ms per call: 128 servers 4.20 -> 2.37 (half of it HBM: 10.8 GB of
 // rows), 64: 4.13 -> 1.36, 8: 4.10 -> 0.55.
@@ -730,14 +730,15 @@ __device__ inline void team_order(uint64_t *team, uint32_t epoch, uint32_t pos, 
     team_store(team + kTeamOrder + 1, epoch, (uint32_t)(payload >> 32));
     team_store(team + kTeamOrder + 2, epoch, (uint32_t)payload);
 }
-// the order that begins `epoch` (or ends the team), for one whole wave; kTeamOver if none comes
+// the order that begins `epoch` (or ends the team), for one whole wave; kTeamOver if none comes.  An order of a later epoch is for
+// those who were there in time: the owner gives none before a member has answered the one before.
 __device__ inline uint32_t team_await_order(const uint64_t *team, uint32_t epoch, uint32_t &pos, uint64_t &payload)
 {
     const int lane = (int)(threadIdx.x & (kWave - 1));
     for (int tries = 0; tries < kTeamPolls; ++tries) {
         const uint64_t w = team_load(team + kTeamOrder + (lane < 2 ? lane : 2));
         const uint32_t stamp = (uint32_t)(w >> 32);
-        if (__builtin_amdgcn_ballot_w64(stamp == kTeamOver)) return kTeamOver;
+        if (__builtin_amdgcn_ballot_w64(stamp > epoch)) return kTeamOver;       // (kTeamOver itself among them)
         if (__builtin_amdgcn_ballot_w64(stamp == epoch) == ~0ull) {
             pos = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)w, 0);
             payload = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)w, 1) << 32) |
