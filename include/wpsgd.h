@@ -186,6 +186,9 @@ int wpsgd_chains_status(const void *workspace, void *stream);
  *   workspace    DEVICE scratch of at least wpsgd_run_delay_chains_workspace(X, k, tau) bytes (0 is
  *                returned for arguments the call would refuse), 256-byte aligned: the sample counts, room
  *                for the servers' iterates, and 32 bytes per row of X for what the test needs of a row
+ * Under the Check function idle compute units share the longer servers' samples.  Calls that do so and together
+ * want more units than the device has run one after the other within one process, whatever streams
+ * they are queued on; results depend neither on that nor on which units are free.
  * Errors: INVALID_ARG, UNSUPPORTED, WORKSPACE_TOO_SMALL, HIP_ERROR.                              */
 size_t wpsgd_run_delay_chains_workspace(const wpsgd_matrix *X, int k, int tau);
 int wpsgd_run_delay_chains(const wpsgd_matrix *X, const float *y, int k, const int64_t *n_samples,

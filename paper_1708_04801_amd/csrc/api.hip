@@ -788,6 +788,12 @@ static size_t delay_table_bytes(const wpsgd_matrix *X) { return align256((size_t
 // stay alone (fp32, d = 1024, m = 4000, 16 servers of 200 samples: 114 us alone, 146 in teams; 4 of up to 600: 247 and 113), and so does
 // every server where the longest would gain little.
 constexpr int64_t kDelayTeamShare = 32, kDelayTeamWorth = 384, kDelayVisitsWorth = 96;
+// Launches with teams run in turn (chain_delay.hip) where their members look at this many samples each and teams gain a third and
+// more.  The event behind a launch costs 3 us (8 servers of up to 3000 samples, d = 1024: 59 | 62), and a launch as short as that is over before
+// an owner gives up waiting for members (two calls of them on two streams 109 us as they come, 122 in turn).  Where teams
+// gain less, calls side by side are the better for sharing units (200 servers of up to 4000, d = 256, four calls on each of two streams: 6986 us without
+// teams, 7977 as they come, 9289 in turn; one call 1458 | 1190).
+constexpr int64_t kDelayTurnShare = 128;
 static int64_t delay_team_share(int k, const int64_t *n_samples, int *helpers)
 {
     *helpers = 0;
@@ -869,6 +875,8 @@ int wpsgd_run_delay_chains(const wpsgd_matrix *X, const float *y, int k, const i
     a.visits = per_visit ? visits : 0;
     if (a.row_table && (size_t)k * kDelayTeamWords * sizeof(uint64_t) <= delay_ring_bytes(X, k, tau)) {
         a.team_share = delay_team_share(k, n_samples, &a.helpers);
+        a.units = compute_units();
+        a.in_turn = a.team_share >= kDelayTurnShare && 3 * a.team_share <= 2 * most;
         a.team = a.team_share ? reinterpret_cast<uint64_t *>(a.ring) : nullptr;      // (no kernel that has teams keeps its iterates there)
     }
     const bool start_ok = !w_start || (uintptr_t)w_start % 4 == 0;

@@ -23,6 +23,7 @@
 // per exchange without it, where the delay makes their gradients independent; both stage rows in LDS.
 // delay_server_kernel keeps the ring in the workspace and covers everything else.
 #include <atomic>
+#include <mutex>
 
 #include "dense_rows.h"
 #include "device_utils.h"
@@ -1285,9 +1286,71 @@ void launch_sample(const DelayArgs &a, hipStream_t s)
         hipLaunchKernelGGL((delay_server_reg_kernel<TX, EPT, VEC, R1, kDelayAhead, false>), dim3(a.k), dim3(kDelayThreads), 0, s, a);
 }
 
+// A call with teams wants its members seated together: an owner whose members start late goes on alone.  So launches with teams
+// that do not fit on the device side by side run in turn, on whatever streams this process queues them: what went before is waited
+// for, from the newest launch that leaves no room on.  (us, two calls on two streams, fp32, up to 8000 samples a server: without teams | with
+// teams, as they come | in turn: d = 4096, 128 servers 4587 | 6013 | 4374, 64 servers 4302 | 5184 | 2100; d = 1024, up to 4000, 128 servers 1939 | 1968 |
+// 1371.  One call: 4162 | 2207 | 2160, 4098 | 1073 | 1060, 1480 | 708 | 700.)  The rule for which launches it is worth stands with the teams' sizes.
+// An order for the sake of time only: where an event fails, and under stream capture, launches go without.
+struct TeamLaunches {
+    static constexpr int kMaxDevices = 64, kKept = 8;
+    struct Launch {
+        hipEvent_t done;
+        hipStream_t stream;
+        int workgroups;                             // 0: none
+    };
+    std::mutex lock;
+    Launch kept[kMaxDevices][kKept] = {};           // the latest launches, the next one goes to kept[next]
+    int next[kMaxDevices] = {};
+};
+TeamLaunches g_team_launches;
+
+template <typename F>
+hipError_t launch_in_turn(const DelayArgs &a, hipStream_t s, F &&launch)
+{
+    int dev = 0;
+    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+    if (!a.in_turn) {
+        launch();
+        return hipGetLastError();
+    }
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= TeamLaunches::kMaxDevices ||
+        hipStreamIsCapturing(s, &capturing) != hipSuccess || capturing != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();
+        launch();
+        return hipGetLastError();
+    }
+    using Turns = TeamLaunches;
+    std::lock_guard<std::mutex> guard(g_team_launches.lock);
+    Turns::Launch(&kept)[Turns::kKept] = g_team_launches.kept[dev];
+    int &next = g_team_launches.next[dev];
+    bool ok = true;
+    int beside = a.k + a.helpers;                   // workgroups that may run at once
+    for (int i = 1; i <= Turns::kKept; ++i) {       // newest first; the oldest makes room for this one
+        Turns::Launch &l = kept[(next + Turns::kKept - i) % Turns::kKept];
+        if (l.workgroups == 0 || l.stream == s) continue;
+        beside += l.workgroups;
+        if (beside > a.units || i == Turns::kKept) ok = ok && hipStreamWaitEvent(s, l.done, 0) == hipSuccess;
+    }
+    if (!ok) (void)hipGetLastError();
+    launch();
+    const hipError_t launched = hipGetLastError();
+    Turns::Launch &mine = kept[next];
+    mine.workgroups = 0;
+    if (!mine.done) ok = ok && hipEventCreateWithFlags(&mine.done, hipEventDisableTiming | hipEventDisableSystemFence) == hipSuccess;
+    if (ok && hipEventRecord(mine.done, s) == hipSuccess) {
+        mine.stream = s;
+        mine.workgroups = a.k + a.helpers;
+        next = (next + 1) % Turns::kKept;
+    } else {
+        (void)hipGetLastError();
+    }
+    return launched;
+}
+
 // The batch kernel claims S row slots of LDS, which is more than a kernel may have without asking.
 template <typename TX, int EPT, int VEC, int R1, bool TEAM>
-bool launch_batch(const DelayArgs &a, hipStream_t s)
+bool launch_batch(const DelayArgs &a, hipStream_t s, hipError_t *launched)
 {
     auto kernel = delay_server_batch_kernel<TX, EPT, VEC, R1, kDelayBatch, kDelaySlots, TEAM>;
     // (members of teams get a compute unit each: more than half of its LDS)
@@ -1305,7 +1368,14 @@ bool launch_batch(const DelayArgs &a, hipStream_t s)
     const int64_t entries = a.visits ? a.visits : a.m;
     hipLaunchKernelGGL((delay_row_table_kernel<TX, VEC>), dim3((unsigned)((entries + kDelayWaves - 1) / kDelayWaves)), dim3(kDelayThreads),
                        0, s, a, static_cast<DelayRowEntry *>(a.row_table), R1 - 1);
-    hipLaunchKernelGGL(kernel, dim3(a.k + (TEAM ? a.helpers : 0)), dim3(kDelayThreads), bytes, s, a);
+    *launched = hipGetLastError();
+    if (*launched != hipSuccess) return true;
+    if constexpr (TEAM) {
+        *launched = launch_in_turn(a, s, [&]() { hipLaunchKernelGGL(kernel, dim3(a.k + a.helpers), dim3(kDelayThreads), bytes, s, a); });
+    } else {
+        hipLaunchKernelGGL(kernel, dim3(a.k), dim3(kDelayThreads), bytes, s, a);
+        *launched = hipGetLastError();
+    }
     return true;
 }
 
@@ -1332,13 +1402,14 @@ bool launch_plain(const DelayArgs &a, hipStream_t s)
 template <typename TX, int VEC>
 hipError_t launch_reg(const DelayArgs &a, bool staged, hipStream_t s, bool *done)
 {
+    hipError_t e = hipSuccess;
     const int r1 = (a.tau > 1 ? a.tau : 1) + 1;
     *done = true;
 #define WPSGD_DELAY_REG(EPT, R1)                                                                                 \
     if (a.d <= (int64_t)kDelayThreads * EPT && r1 == R1) {                                                       \
         if (a.check && staged && a.row_table && a.m < (1 << 27) &&                                               \
-            (a.team ? launch_batch<TX, EPT, VEC, R1, true>(a, s) : launch_batch<TX, EPT, VEC, R1, false>(a, s))) \
-            return hipGetLastError();                                                                            \
+            (a.team ? launch_batch<TX, EPT, VEC, R1, true>(a, s, &e) : launch_batch<TX, EPT, VEC, R1, false>(a, s, &e))) \
+            return e;                                                                                            \
         else if (!a.check && staged && a.tau >= 1 && a.m < (1 << 30) && launch_plain<TX, EPT, VEC, R1>(a, s))    \
             return hipGetLastError();                                                                            \
         else                                                                                                     \

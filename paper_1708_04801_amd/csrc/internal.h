@@ -85,6 +85,7 @@ struct DelayArgs {
     uint64_t *team;           // DEVICE, k x kDelayTeamWords: tables of the servers' teams (cleared by the launch), or NULL: no teams
     int64_t team_share;       // samples per member that the teams are sized for
     int helpers;              // members beyond the first, all servers together
+    int units, in_turn;       // compute units of the device; whether launches that want more together run one after the other
 };
 
 // Several workgroups per server under the Check function (chain_delay.hip): how many, and the words of a team's table.
