@@ -436,7 +436,9 @@ struct StagingRing {
 };
 static thread_local StagingRing g_staging;
 
-static int upload(void *dst, const void *src, size_t bytes, hipStream_t s)
+// fill(host) writes the bytes into the staging buffer
+template <typename F>
+static int upload_filled(void *dst, size_t bytes, hipStream_t s, F &&fill)
 {
     StagingSlot &st = g_staging.slot[g_staging.next];
     g_staging.next = (g_staging.next + 1) % kStagingSlots;
@@ -459,13 +461,18 @@ static int upload(void *dst, const void *src, size_t bytes, hipStream_t s)
         e = hipEventCreateWithFlags(&st.last_copy, hipEventDisableTiming);
         if (e != hipSuccess) return hip_fail(e);
     }
-    std::memcpy(st.host, src, bytes);
+    fill(st.host);
     e = hipMemcpyAsync(dst, st.host, bytes, hipMemcpyHostToDevice, s);
     if (e != hipSuccess) return hip_fail(e);
     e = hipEventRecord(st.last_copy, s);
     if (e != hipSuccess) return hip_fail(e);
     st.pending = true;
     return WPSGD_OK;
+}
+
+static int upload(void *dst, const void *src, size_t bytes, hipStream_t s)
+{
+    return upload_filled(dst, bytes, s, [&](void *host) { std::memcpy(host, src, bytes); });
 }
 
 static int check_steps(int k, const int64_t *n_steps)
@@ -839,7 +846,32 @@ int wpsgd_run_delay_chains(const wpsgd_matrix *X, const float *y, int k, const i
     if (workspace_bytes < wpsgd_run_delay_chains_workspace(X, k, tau)) return WPSGD_WORKSPACE_TOO_SMALL;
     hipStream_t s = static_cast<hipStream_t>(stream);
     char *base = static_cast<char *>(workspace);
-    rc = upload(base, n_samples, (size_t)k * sizeof(int64_t), s);
+    const size_t head = align256((size_t)k * sizeof(int64_t)), ring = align256(delay_ring_bytes(X, k, tau));
+    // The table of what the Check function needs of a row costs a pass over the data set: one entry per row where the servers
+    // together visit a good part of the rows, else one per visit.  Servers of a few dozen samples do without (fp32, d = 4096,
+    // m = 65536: 200 servers of 50 samples 98 us without, 112 with; one of 200 samples 242 and 125).
+    int64_t visits = 0, most = 0;
+    for (int i = 0; i < k; ++i) {
+        visits += std::min<int64_t>(n_samples[i], INT64_MAX / 2 / k);
+        most = std::max(most, n_samples[i]);
+    }
+    const bool per_visit = visits < X->m / 4, table = check != 0 && (!per_visit || most >= kDelayVisitsWorth);
+    // With an entry per visit go the servers' first entries, where the ring begins (no kernel that has a table keeps its iterates there).
+    size_t used = 0;
+    if (table && per_visit) {
+        rc = upload_filled(base, head + (size_t)k * sizeof(int64_t), s, [&](void *host) {
+            int64_t *counts = static_cast<int64_t *>(host), *first = counts + head / sizeof(int64_t);
+            int64_t before = 0;
+            for (int i = 0; i < k; ++i) {
+                counts[i] = n_samples[i];
+                first[i] = before;
+                before += n_samples[i];
+            }
+        });
+        used = head;
+    } else {
+        rc = upload(base, n_samples, (size_t)k * sizeof(int64_t), s);
+    }
     if (rc != WPSGD_OK) return rc;
     DelayArgs a{};
     a.dense = X->dense;
@@ -857,27 +889,17 @@ int wpsgd_run_delay_chains(const wpsgd_matrix *X, const float *y, int k, const i
     a.check = check != 0;
     a.seed_lo = (uint32_t)seed;
     a.seed_hi = (uint32_t)(seed >> 32);
-    a.ring = reinterpret_cast<double *>(base + align256((size_t)k * sizeof(int64_t)));
+    a.ring = reinterpret_cast<double *>(base + head);
     a.W = W;
     a.accepted = accepted;
-    // The table of what the Check function needs of a row costs a pass over the data set: one entry per row where the servers
-    // together visit a good part of the rows, else one per visit.  Servers of a few dozen samples do without (fp32, d = 4096,
-    // m = 65536: 200 servers of 50 samples 98 us without, 112 with; one of 200 samples 242 and 125).
-    int64_t visits = 0, most = 0;
-    for (int i = 0; i < k; ++i) {
-        visits += std::min<int64_t>(n_samples[i], INT64_MAX / 2 / k);
-        most = std::max(most, n_samples[i]);
-    }
-    const bool per_visit = visits < X->m / 4;
-    a.row_table = check != 0 && (!per_visit || most >= kDelayVisitsWorth)
-                      ? base + align256((size_t)k * sizeof(int64_t)) + align256(delay_ring_bytes(X, k, tau))
-                      : nullptr;
-    a.visits = per_visit ? visits : 0;
-    if (a.row_table && (size_t)k * kDelayTeamWords * sizeof(uint64_t) <= delay_ring_bytes(X, k, tau)) {
+    a.row_table = table ? base + head + ring : nullptr;
+    a.visits = used ? visits : 0;
+    a.visits_before = used ? reinterpret_cast<const int64_t *>(base + head) : nullptr;
+    if (a.row_table && used + (size_t)k * kDelayTeamWords * sizeof(uint64_t) <= ring) {
         a.team_share = delay_team_share(k, n_samples, &a.helpers);
         a.units = compute_units();
         a.in_turn = a.team_share >= kDelayTurnShare && 3 * a.team_share <= 2 * most;
-        a.team = a.team_share ? reinterpret_cast<uint64_t *>(a.ring) : nullptr;      // (no kernel that has teams keeps its iterates there)
+        a.team = a.team_share ? reinterpret_cast<uint64_t *>(base + head + used) : nullptr;
     }
     const bool start_ok = !w_start || (uintptr_t)w_start % 4 == 0;
     if (!start_ok) return WPSGD_INVALID_ARG;

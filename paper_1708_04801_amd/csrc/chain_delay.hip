@@ -616,6 +616,23 @@ __device__ inline int server_of_item(int k, int at, int &before, F &&count)
     return -1;
 }
 
+// The same from the sums themselves, which begin with 0 and do not fall (`at` is below the sum of all counts): every round
+// leaves a 64th of the servers.  (us a call, d = 64, 20000 servers of up to 100 samples: 14476 with the counts
+// added up for every visit, 1938 now, 1998 with the per-sample kernel and no table; 4000 servers 893, 396, 467.)
+__device__ inline int server_of_visit(int k, int64_t at, const int64_t *before)
+{
+    const int lane = (int)(threadIdx.x & (kWave - 1));
+    int first = 0;
+    for (int left = k; left > 1;) {
+        const int step = (left + kWave - 1) / kWave;
+        const bool reached = lane * step < left && before[first + lane * step] <= at;
+        const int whole = __builtin_popcountll(__builtin_amdgcn_ballot_w64(reached)) - 1;
+        first += whole * step;
+        left = left - whole * step < step ? left - whole * step : step;
+    }
+    return first;
+}
+
 template <typename TX, int VEC>
 __global__ __launch_bounds__(kDelayThreads) void delay_row_table_kernel(DelayArgs a, DelayRowEntry *table, int reach)
 {
@@ -627,10 +644,9 @@ __global__ __launch_bounds__(kDelayThreads) void delay_row_table_kernel(DelayArg
             a.team[i] = 0;
     int64_t row = entry;
     if (a.visits) {
-        int first;
-        const int server = server_of_item(a.k, (int)entry, first, [&](int i) { return (int)a.n_samples[i]; });
-        if (server < 0) return;
-        row = sample_row(a.seed_lo, a.seed_hi, (uint32_t)server, (uint64_t)(entry - first), (uint32_t)a.m);
+        if (entry >= a.visits) return;
+        const int server = server_of_visit(a.k, entry, a.visits_before);
+        row = sample_row(a.seed_lo, a.seed_hi, (uint32_t)server, (uint64_t)(entry - a.visits_before[server]), (uint32_t)a.m);
     }
     if (row >= a.m) return;
     const TX *xr = static_cast<const TX *>(a.dense) + row * a.ld;
@@ -897,13 +913,7 @@ __global__ __launch_bounds__(kDelayThreads) void delay_server_batch_kernel(Delay
     using Index = std::conditional_t<TEAM, int32_t, int64_t>;
     const Index end = (Index)n;
     uint32_t first_visit = 0;                       // this server's first entry in a table of visits
-    if (a.visits) {
-        int64_t before = 0;
-        for (int c = 0; c < chain; c += kWave) before += c + lane < chain ? a.n_samples[c + lane] : 0;
-        int sum = (int)before;
-        for (int o = 1; o < kWave; o <<= 1) sum += __shfl_xor(sum, o);
-        first_visit = (uint32_t)__builtin_amdgcn_readfirstlane(sum);
-    }
+    if (a.visits) first_visit = (uint32_t)a.visits_before[chain];
     Index base = 0, limit = end, window = -1;
     uint32_t window_rows = 0;
     auto sample_of = [&](Index l) {
