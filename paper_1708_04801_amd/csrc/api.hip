@@ -796,7 +796,7 @@ static size_t delay_table_bytes(const wpsgd_matrix *X) { return align256((size_t
 // every server where the longest would gain little.
 constexpr int64_t kDelayTeamShare = 32, kDelayTeamWorth = 384, kDelayVisitsWorth = 96;
 // Launches with teams run in turn (chain_delay.hip) where their members look at this many samples each and teams gain a third and
-// more.  The event behind a launch costs 3 us (8 servers of up to 3000 samples, d = 1024: 59 | 62), and a launch as short as that is over before
+// more.  The event costs a call 1.5 to 2 us (29 servers of up to 2300 samples, bf16, d = 1912: 116 | 117), and a launch as short as that is over before
 // an owner gives up waiting for members (two calls of them on two streams 109 us as they come, 122 in turn).  Where teams
 // gain less, calls side by side are the better for sharing units (200 servers of up to 4000, d = 256, four calls on each of two streams: 6986 us without
 // teams, 7977 as they come, 9289 in turn; one call 1458 | 1190).

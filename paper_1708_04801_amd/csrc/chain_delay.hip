@@ -22,6 +22,8 @@
 // function, where nearly every sample is thrown away, with several workgroups per server while compute units are idle, and delay_server_plain_kernel takes tau + 1 samples
 // per exchange without it, where the delay makes their gradients independent; both stage rows in LDS.
 // delay_server_kernel keeps the ring in the workspace and covers everything else.
+#include <hip/hip_ext.h>
+
 #include <atomic>
 #include <mutex>
 
@@ -1321,13 +1323,13 @@ hipError_t launch_in_turn(const DelayArgs &a, hipStream_t s, F &&launch)
     int dev = 0;
     hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
     if (!a.in_turn) {
-        launch();
+        launch(nullptr);
         return hipGetLastError();
     }
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= TeamLaunches::kMaxDevices ||
         hipStreamIsCapturing(s, &capturing) != hipSuccess || capturing != hipStreamCaptureStatusNone) {
         (void)hipGetLastError();
-        launch();
+        launch(nullptr);
         return hipGetLastError();
     }
     using Turns = TeamLaunches;
@@ -1342,18 +1344,16 @@ hipError_t launch_in_turn(const DelayArgs &a, hipStream_t s, F &&launch)
         beside += l.workgroups;
         if (beside > a.units || i == Turns::kKept) ok = ok && hipStreamWaitEvent(s, l.done, 0) == hipSuccess;
     }
-    if (!ok) (void)hipGetLastError();
-    launch();
-    const hipError_t launched = hipGetLastError();
     Turns::Launch &mine = kept[next];
     mine.workgroups = 0;
     if (!mine.done) ok = ok && hipEventCreateWithFlags(&mine.done, hipEventDisableTiming | hipEventDisableSystemFence) == hipSuccess;
-    if (ok && hipEventRecord(mine.done, s) == hipSuccess) {
+    if (!ok) (void)hipGetLastError();
+    launch(ok ? mine.done : nullptr);               // (an event of the kernel's own: recorded behind it, it cost a call 1.5 us more)
+    const hipError_t launched = hipGetLastError();
+    if (ok && launched == hipSuccess) {
         mine.stream = s;
         mine.workgroups = a.k + a.helpers;
         next = (next + 1) % Turns::kKept;
-    } else {
-        (void)hipGetLastError();
     }
     return launched;
 }
@@ -1381,7 +1381,9 @@ bool launch_batch(const DelayArgs &a, hipStream_t s, hipError_t *launched)
     *launched = hipGetLastError();
     if (*launched != hipSuccess) return true;
     if constexpr (TEAM) {
-        *launched = launch_in_turn(a, s, [&]() { hipLaunchKernelGGL(kernel, dim3(a.k + a.helpers), dim3(kDelayThreads), bytes, s, a); });
+        *launched = launch_in_turn(a, s, [&](hipEvent_t done) {
+            hipExtLaunchKernelGGL(kernel, dim3(a.k + a.helpers), dim3(kDelayThreads), bytes, s, nullptr, done, 0, a);
+        });
     } else {
         hipLaunchKernelGGL(kernel, dim3(a.k), dim3(kDelayThreads), bytes, s, a);
         *launched = hipGetLastError();
