@@ -738,17 +738,17 @@ static int run_chains_from(const wpsgd_matrix *X, const float *y, int k, const i
         if (e != hipSuccess) return hip_fail(e);
     }
     // Between two spans the chains of short rows form the average themselves (start_values), one launch instead of two: the models then
-    // lie in two places in turn, W and a part of the workspace that the plan leaves idle (the vectors of the HBM-state kernels, else
-    // the shuffled order).  Every chain reads all models, 16 rows at once, in the order in which combine_kernel adds fewer than
-    // 64.  us a span, two launches -> one, spans of 40 to 200 steps: d = 64 hinge, 16 chains 18.9 -> 15.3, 63 chains 27.3 -> 17.7;
-    // d = 128 logistic, 32 chains 21.3 -> 17.4; d = 64 logistic, 32 chains of 5 to 20 steps 11.7 -> 6.7.  Longer rows gain nothing
+    // lie in two places in turn, W and the part of the workspace that holds the vectors of the HBM-state kernels, which these plans leave
+    // idle.  Every chain reads all models, 16 rows at once, in the order in which combine_kernel adds fewer than
+    // 64.  us a span, two launches -> one: d = 64 hinge, spans of up to 200 steps, 16 chains 19.6 -> 16.3, 63 chains 28.9 -> 18.4, of up to 20
+    // 11.3 -> 7.8, 20.0 -> 10.0; d = 128 logistic, up to 120, 4 chains 15.1 -> 13.0, 63 chains 25.8 -> 17.1; d = 256 logistic, up to 520, 4 chains 47.0 -> 45.9,
+    // 63 chains 57.8 -> 49.7, bf16 hinge 74.8 -> 73.1, 85.0 -> 79.8.  Longer rows gain nothing
     // or lose (blocks of eight steps: d = 1024, 16 chains 29.4 -> 30.2, bf16 d = 2048 34.8 -> 45.8: a workgroup alone draws k rows more
     // slowly than the average's own launch does).
     float *other = nullptr;
     if (spans && spans->count > 1 && p.family == Family::DenseReg && p.scouts > 0 && !p.octets && k <= kStartModelsMost) {
         const size_t models = (size_t)k * (size_t)X->d * sizeof(float), used = h.total + perm_bytes(X->m);
         if (workspace_bytes >= used + models) other = reinterpret_cast<float *>(ws + used);
-        else if (!a.perm && models <= perm_bytes(X->m)) other = reinterpret_cast<float *>(perm_dev);
     }
     for (int64_t span = 0; span < (spans ? spans->count : 1); ++span) {
         a.span = span;

@@ -107,8 +107,8 @@ def test_few_samples_and_narrow_rows(tau, d):
 
 @pytest.mark.parametrize("tau", [0, 2, 4])
 def test_servers_that_visit_few_of_many_rows(tau):
-    """When the servers together visit less than a quarter of the rows, no table of per-row quantities is
-    built and every sample is decided on its own (another kernel than in the cases above)."""
+    """When the servers together visit less than a quarter of the rows, the table of what the test needs of a row
+    has an entry per visit instead of one per row."""
     w = wl.delay_servers(m=16384, d=1024, k=3, n_lo=300, n_hi=900, tau=tau, data_seed=70 + tau)
     assert 4 * w.n_steps.sum() < w.m
     Wg, acc_g, Wo, acc_o, gap = run_both(w, tau, check=True)
