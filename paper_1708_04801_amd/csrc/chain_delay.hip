@@ -1,5 +1,5 @@
 // Delay SGD under the Check function (Section IV, Algorithms 3 and 4; Lemma 4): one workgroup is one
-// server.  It keeps the accepted iterates w_{J-reach} .. w_J (reach = max(tau, 1)) and room for one
+// server, or one of several that share its samples.  It keeps the accepted iterates w_{J-reach} .. w_J (reach = max(tau, 1)) and room for one
 // candidate as a ring of fp64 vectors in the workspace.  Every thread owns the same columns of every
 // vector in every pass, so the ring needs no synchronisation of its own; it is re-read every sample
 // and stays in the cache of the compute unit's XCD.
@@ -17,11 +17,12 @@
 // Four kernels.  delay_server_reg_kernel holds the ring in registers, newest iterate first, and shifts
 // it when a candidate is accepted; the rows of the next samples (which do not depend on what is
 // accepted) are requested PF samples ahead, so a sample costs the pass over its row, one exchange of
-// sums and the decision.  It covers rows of up to 256 x EPT aligned elements and delays up to 4.
-// For the same shapes, delay_server_batch_kernel decides B samples per exchange under the Check
-// function, where nearly every sample is thrown away, with several workgroups per server while compute units are idle, and delay_server_plain_kernel takes tau + 1 samples
-// per exchange without it, where the delay makes their gradients independent; both stage rows in LDS.
-// delay_server_kernel keeps the ring in the workspace and covers everything else.
+// sums and the decision.  It covers rows of up to 256 x EPT elements (bfloat16 ones that are not aligned by a load
+// per element) and delays up to 4.  For the same delays and rows of whole 16-byte pieces,
+// delay_server_batch_kernel decides B samples per exchange under the Check function, where nearly every sample is
+// thrown away, with several workgroups per server while compute units are idle, and delay_server_plain_kernel takes
+// tau + 1 samples per exchange without it, where the delay makes their gradients independent; both stage rows in LDS.
+// delay_server_kernel keeps the ring in the workspace and covers longer rows and delays.
 #include <hip/hip_ext.h>
 
 #include <atomic>
@@ -341,7 +342,7 @@ __global__ __launch_bounds__(kDelayThreads) void delay_server_reg_kernel(DelayAr
 
     // Rows and labels of the next PF samples are on their way at any time; beyond the end the last sample's again, so that no request
     // sits under a branch, where each would be waited for on the spot, and labels travel with the rows (a scalar load would be
-    // drained by the exchange of sums, its address takes no registers).  128 servers of up to 400 samples, fp32, d = 4096, tau = 0,
+    // drained by the exchange of sums; through a resource of their own they need no address registers).  128 servers of up to 400 samples, fp32, d = 4096, tau = 0,
     // without Check: 470 -> 301 us.
     RowWindow win;
     win.init(a.seed_lo, a.seed_hi, (uint32_t)chain, (uint32_t)a.m);
@@ -720,12 +721,15 @@ __device__ inline bool window_passes(const double *L, const double (&n2)[R1], do
 //  * A member learns of the others' acceptances from their records, one load per batch that lands in LDS behind the rows
 //    (an ordinary load would wait for them).
 //  * Nobody waits for a workgroup that is not running: a team is made of those that have reported within some 0.1 ms of the
-//    owner's start (owners are launched first), the others leave when they see that an order has been given without them.  All waits are bounded: an owner whose members do not
-//    answer goes on alone from the base of the epoch, members without orders leave.
-// fp32, d = 4096, m = 65536, tau = 2, up to 8000 samples a server, ms per call: 128 servers 4.20 -> 2.37 (half of it HBM: 10.8 GB of
-// rows), 64: 4.13 -> 1.36, 8: 4.10 -> 0.55.
+//    owner's start (owners are launched first), the others leave when they see that an order has been given without them.  All
+//    waits are bounded: an owner whose members do not answer goes on alone from the base of the epoch, members without orders leave.
 //  * An epoch costs some 8 us of exchange, row fetch and new requests; when acceptances come closer than kTeamGap samples for good
-//    the owner sends its members away and goes on alone, as without a team.
+//    the owner sends its members away and goes on alone, as without a team.  (The first updates of a server come thick: 9 to 17 of the
+//    first 32 samples and 20 to 40 in all on rows along one direction, which kTeamSlack lets pass.)
+// fp32, d = 4096, m = 65536, tau = 2, up to 8000 samples a server, ms per call: 128 servers 4.16 -> 2.16 (two thirds of it HBM: 10.8 GB of
+// rows at 6.8 TB/s are 1.6), 64: 4.10 -> 1.06, 8: 3.63 -> 0.29.  Streams of which one sample in ten and more is accepted pay for the
+// epochs up to the dissolution, 0.26 ms, and 0.2 us per update for the team's code: 8 servers of 1000 samples, d = 1024, us: 100 accepted 392 -> 628,
+// all 1279 -> 1597; 27 accepted 334 -> 256, 9 318 -> 122.
 constexpr int kTeamMax = kDelayTeamMax;         // members: one lane each
 static_assert(kTeamMax == kWave, "a member is a lane");
 constexpr int kTeamPresent = 2 * kTeamMax, kTeamOrder = kTeamPresent + kTeamMax / 2;     // 64-bit words: records, presence (32 bits each), orders

@@ -108,10 +108,10 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(6))) vo
 
 // Few columns and fewer than 64 rows (no workgroup of the kernel above splits those): one wave per 64 columns, so that no
 // compute unit draws many of them, and no load under a branch: the rows of a batch, the last one's repeated behind the end, are all on
-// their way at once.  The same additions in the same order.  (us per span of 40 to 200 steps with its average:
+// their way at once.  The same fused multiply-adds in the same order.  (us per span of 40 to 200 steps with its average:
 // d = 1024, 16 chains 29.45 -> 28.11, 32 chains 32.35 -> 29.21, 63 chains 46.8 -> 37.4; d = 8192, 60 chains of 20 to 60 steps 54.7 -> 45.1;
 // k = 4 within 1 %.)  From 64 rows or 64 columns per compute unit on the kernel above has loads enough in flight.
-constexpr int kSmallCombineRows = 64, kSmallCombineColumns = 64 * 256;
+constexpr int kSmallCombineRows = 64, kSmallCombineColumns = 64 * 256;     // (256 compute units)
 __global__ __launch_bounds__(kWave) void combine_small_kernel(const float *__restrict__ W, const double *__restrict__ a, int k, int64_t d,
                                                               float *__restrict__ out)
 {
