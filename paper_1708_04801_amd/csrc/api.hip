@@ -856,9 +856,10 @@ int wpsgd_run_delay_chains(const wpsgd_matrix *X, const float *y, int k, const i
         most = std::max(most, n_samples[i]);
     }
     const bool per_visit = visits < X->m / 4, table = check != 0 && (!per_visit || most >= kDelayVisitsWorth);
-    // With an entry per visit go the servers' first entries, where the ring begins (no kernel that has a table keeps its iterates there).
+    // With an entry per visit go the servers' first entries, where the ring begins (no kernel that has a table keeps its iterates there);
+    // up to 64 servers a wave adds them up as fast as it reads them, and short rings keep their room for teams.
     size_t used = 0;
-    if (table && per_visit) {
+    if (table && per_visit && k > kWave) {
         rc = upload_filled(base, head + (size_t)k * sizeof(int64_t), s, [&](void *host) {
             int64_t *counts = static_cast<int64_t *>(host), *first = counts + head / sizeof(int64_t);
             int64_t before = 0;
@@ -893,7 +894,7 @@ int wpsgd_run_delay_chains(const wpsgd_matrix *X, const float *y, int k, const i
     a.W = W;
     a.accepted = accepted;
     a.row_table = table ? base + head + ring : nullptr;
-    a.visits = used ? visits : 0;
+    a.visits = table && per_visit ? visits : 0;
     a.visits_before = used ? reinterpret_cast<const int64_t *>(base + head) : nullptr;
     if (a.row_table && used + (size_t)k * kDelayTeamWords * sizeof(uint64_t) <= ring) {
         a.team_share = delay_team_share(k, n_samples, &a.helpers);

@@ -648,8 +648,18 @@ __global__ __launch_bounds__(kDelayThreads) void delay_row_table_kernel(DelayArg
     int64_t row = entry;
     if (a.visits) {
         if (entry >= a.visits) return;
-        const int server = server_of_visit(a.k, entry, a.visits_before);
-        row = sample_row(a.seed_lo, a.seed_hi, (uint32_t)server, (uint64_t)(entry - a.visits_before[server]), (uint32_t)a.m);
+        int64_t first;
+        int server;
+        if (a.visits_before) {
+            server = server_of_visit(a.k, entry, a.visits_before);
+            first = a.visits_before[server];
+        } else {
+            int sum;
+            server = server_of_item(a.k, (int)entry, sum, [&](int i) { return (int)a.n_samples[i]; });
+            if (server < 0) return;
+            first = sum;
+        }
+        row = sample_row(a.seed_lo, a.seed_hi, (uint32_t)server, (uint64_t)(entry - first), (uint32_t)a.m);
     }
     if (row >= a.m) return;
     const TX *xr = static_cast<const TX *>(a.dense) + row * a.ld;
@@ -919,7 +929,13 @@ __global__ __launch_bounds__(kDelayThreads) void delay_server_batch_kernel(Delay
     using Index = std::conditional_t<TEAM, int32_t, int64_t>;
     const Index end = (Index)n;
     uint32_t first_visit = 0;                       // this server's first entry in a table of visits
-    if (a.visits) first_visit = (uint32_t)a.visits_before[chain];
+    if (a.visits_before) {
+        first_visit = (uint32_t)a.visits_before[chain];
+    } else if (a.visits) {                          // (at most 64 servers: a lane each)
+        int sum = lane < chain ? (int)a.n_samples[lane] : 0;
+        for (int o = 1; o < kWave; o <<= 1) sum += __shfl_xor(sum, o);
+        first_visit = (uint32_t)__builtin_amdgcn_readfirstlane(sum);
+    }
     Index base = 0, limit = end, window = -1;
     uint32_t window_rows = 0;
     auto sample_of = [&](Index l) {

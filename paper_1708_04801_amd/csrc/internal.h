@@ -80,7 +80,7 @@ struct DelayArgs {
     void *row_table;          // DEVICE, m x 32 bytes: room for what the Check function needs of each row, or of each visit
     int64_t visits;           // samples of all servers together where they are so few that the table has an entry per visit
                               // (the servers' samples one server after the other), 0: an entry per row
-    const int64_t *visits_before;   // DEVICE, k: each server's first entry in a table of visits
+    const int64_t *visits_before;   // DEVICE, k: each server's first entry in a table of visits, or NULL with k <= 64: added up from the counts
     float *W;                 // k x d out
     int64_t *accepted;        // k out: updates each server has made
     uint64_t *team;           // DEVICE, k x kDelayTeamWords: tables of the servers' teams (cleared by the launch), or NULL: no teams

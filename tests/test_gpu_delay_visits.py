@@ -53,3 +53,30 @@ def test_many_servers_cost_what_their_visits_cost():
     few, many = clock(5000), clock(40000)
     print(f"5000 servers {few * 1e6:.0f} us, 40000 servers {many * 1e6:.0f} us")
     assert many < 16 * few
+
+
+@pytest.mark.parametrize("k", [1, 10])
+@pytest.mark.parametrize("d", [60, 64, 72])
+def test_short_rows_keep_their_teams(k, d):
+    """The least room for the teams' tables.  Servers of 4000 samples in teams take a tenth of the time that they take in a call whose servers
+    outnumber the compute units (no teams); a half lies between."""
+    m = 1 << 18
+    X = api.Matrix(m, d, dense=torch.randn((m, d), device="cuda") * 0.05)
+    y = torch.ones(m, device="cuda")
+    units = torch.cuda.get_device_properties(0).multi_processor_count
+
+    def clock(n):
+        space = torch.empty(api.wpsgd_run_delay_chains_workspace(X, len(n), 1), dtype=torch.uint8, device="cuda")
+        took = []
+        for _ in range(6):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            api.wpsgd_run_delay_chains(X, y, n, 0.05, 0.1, wl.LOGISTIC, 1, 1, workspace=space)
+            torch.cuda.synchronize()
+            took.append(time.perf_counter() - t)
+        return min(took[1:])
+
+    n = np.full(k, 4000, dtype=np.int64)
+    teams, alone = clock(n), clock(np.concatenate([n, np.ones(units, dtype=np.int64)]))
+    print(f"teams {teams * 1e6:.0f} us, alone {alone * 1e6:.0f} us")
+    assert teams < 0.5 * alone
