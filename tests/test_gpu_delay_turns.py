@@ -85,7 +85,7 @@ def test_units_taken_by_another_call(k, n):
 
 def test_two_streams_take_no_longer_than_one_after_the_other():
     """Half as many servers as compute units.  128 servers: one call 824 us, two on two streams 1565 us in turn; 2045 us where the second's
-    servers find their teams' units taken (2.5 times one call; 2.2 lies between)."""
+    servers find their teams' units taken (2.5 times one call; 2.3 lies between)."""
     calls = Calls(torch.cuda.get_device_properties(0).multi_processor_count // 2, 4000, 2)
 
     def clock(which):
@@ -101,4 +101,4 @@ def test_two_streams_take_no_longer_than_one_after_the_other():
 
     one, two = clock([0]), clock([0, 1])
     print(f"one call {one * 1e6:.0f} us, two {two * 1e6:.0f} us")
-    assert two < 2.2 * one
+    assert two < 2.3 * one
