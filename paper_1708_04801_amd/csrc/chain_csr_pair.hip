@@ -1,5 +1,5 @@
 // Sparse-row (CSR) SGD chains, three wavefronts per chain.  (Matrices whose rows have at most 16 entries
-// and seldom share columns run four steps at a time instead: chain_csr_short.h.)
+// and seldom share columns run four steps at a time instead, chain_csr_short.h, or sixteen, chain_csr_sixteen.h.)
 //
 // A step of a sparse chain is a short dependent recursion (gather the model at the row's columns,
 // reduce, decide, scatter), and one wavefront issues one instruction at a time: with a single
@@ -173,6 +173,7 @@ __device__ inline uint32_t stamp_slot_b(uint32_t col) { return (col + (col >> 13
 }  // namespace wpsgd
 
 #include "chain_csr_short.h"
+#include "chain_csr_sixteen.h"
 
 namespace wpsgd {
 namespace {
@@ -201,12 +202,13 @@ __global__ __launch_bounds__(kPairThreads) void chain_csr_pair_kernel(ChainArgs 
     // then only shrinks the vector), has nothing to do here.
     if (nnz == 0 || n == 0) return;
     const uint32_t rows_are_short = a.status[1];
+    if (rows_are_short == kShortApart && n >= kShortWorth) return;       // sixteen steps at a time: chain_csr_sixteen_kernel
     TV *head = reinterpret_cast<TV *>(lds + L::head);
     using S = ShortLds<TV>;
     static_assert(S::head == L::head && kWave <= kSlots, "both forms keep the same columns at the same place");
     for (int c = tid; c < kPHead + kSlots; c += kPairThreads)                             // values and scratch slots
         head[c] = (a.w_start && c < kPHead && c < d) ? (TV)a.w_start[c] : (TV)0;
-    if (rows_are_short != 0 && n >= (rows_are_short == kShortAlways ? kShortWorth : kShortWorthInTurn)) {        // four steps at a time: chain_csr_short.h
+    if (rows_are_short != 0 && rows_are_short != kShortApart && n >= (rows_are_short == kShortAlways ? kShortWorth : kShortWorthInTurn)) {        // four steps at a time: chain_csr_short.h
         // (the head's values must be written before the stamps that overlap their scratch slots)
         __syncthreads();
         for (int c = tid; c < 2 * (kPStamps + kWave); c += kPairThreads) reinterpret_cast<uint16_t *>(lds + S::stamp_a)[c] = 0;
@@ -576,10 +578,10 @@ __global__ __launch_bounds__(kLookThreads) void csr_state_start_kernel(TV *state
                                                                        int64_t longest, const int64_t *row_ptr, const int32_t *col_idx, int64_t m,
                                                                        uint32_t *answer)
 {
-    __shared__ uint8_t owner[kLookThreads / kWave][kLookSlots + kWave];
+    __shared__ __attribute__((aligned(4))) uint8_t owner[kLookThreads / kWave][kLookSlots + kWave];
     TV *v = state + (int64_t)(row0 + (int)blockIdx.y) * d;
     if (row0 == 0 && blockIdx.x == 0 && blockIdx.y == 0 && longest >= kShortWorth)       // (for shorter chains the word stays zero)
-        look_for_short_rows(row_ptr, col_idx, m, owner[threadIdx.x / kWave], answer);
+        look_for_short_rows(row_ptr, col_idx, m, d, owner[threadIdx.x / kWave], answer);
     for (int64_t c = (int64_t)blockIdx.x * kLookThreads + threadIdx.x; c < d; c += (int64_t)gridDim.x * kLookThreads)
         v[c] = w_start ? (TV)w_start[c] : (TV)0;
 }
@@ -619,6 +621,8 @@ static hipError_t launch_pair(const ChainArgs &a, hipStream_t s)
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((chain_csr_pair_kernel<LOSS>), dim3(a.k), dim3(kPairThreads), 0, s, a);
+    if (a.longest >= kShortWorth && a.d >= kApartColumns)
+        hipLaunchKernelGGL((chain_csr_sixteen_kernel<LOSS>), dim3(a.k), dim3(kXThreads), 0, s, a);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     for (int row0 = 0; row0 < a.k; row0 += kRows) {

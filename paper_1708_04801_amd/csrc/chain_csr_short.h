@@ -66,14 +66,21 @@ struct ShortLds {
 //   0.22 | 0.20 | 0.06 if all its columns are in LDS.  The first costs more than it gains from two groups in five on (a
 //   column that all rows share, such as a constant term, at d = 100000: 0.22 one at a time, 0.46 in groups).  The second
 //   has to earn back the start of the scouts' deeper pipeline.
-constexpr uint32_t kShortAlways = 1, kShortLongChains = 2;       // answers, in the word behind the status word
+//   Rows far apart: among the 48 rows that a wave looks at, entries that find their column with one looked at before are counted.  Sixteen steps
+//   at a time (chain_csr_sixteen.h) pay for each such pair where groups of four hardly notice one.  us, four at a time | sixteen, ten
+//   chains of 10000 steps, hinge, 5 to 10 uniform columns (the count expected): d = 15000 (13) 669 | 826, 30000 (7) 660 | 650, 40000 (5) 652 | 608, 100000 (2)
+//   634 | 514, a million (0) 631 | 437; ten chains of 200 steps, d = 100000 61 | 50.
+constexpr uint32_t kShortAlways = 1, kShortLongChains = 2, kShortApart = 3;       // answers, in the word behind the status word
+constexpr int kLookPairs = 5;
+// With fewer columns rows of this length meet too often, and calls do without the count and the launch (2 us of a call of 200 steps).
+constexpr int64_t kApartColumns = 24576;
 constexpr int kLookThreads = 256, kLookEach = 3, kLookGroups = 48, kLookMost = 19, kLookSlots = 4096;
 // Chains of less than 128 steps do not earn back that start (8 steps of rows without a shared column: 24 us one at a
 // time, 30 in groups; 100 steps, d = 100000: 52.6 and 52.5), nor ones of less than 512 if most groups run in turn.
 constexpr int64_t kShortWorth = 128, kShortWorthInTurn = 512;
 
 // owner: this wave's table.  (All loads of the look go out at once, a quarter of the groups per wave: two trips to memory.)
-__device__ inline void look_for_short_rows(const int64_t *row_ptr, const int32_t *col_idx, int64_t m, uint8_t *owner, uint32_t *answer)
+__device__ inline void look_for_short_rows(const int64_t *row_ptr, const int32_t *col_idx, int64_t m, int64_t d, uint8_t *owner, uint32_t *answer)
 {
     constexpr int kRows = kLookThreads * kLookEach, kMine = kLookGroups / (kLookThreads / kWave);        // groups of a wave
     static_assert(kMine <= kShortLen, "lane 16*r + g holds row r of the wave's group g");
@@ -99,24 +106,65 @@ __device__ inline void look_for_short_rows(const int64_t *row_ptr, const int32_t
         col[g] = 0;
         if (entries > 0) col[g] = (uint32_t)col_idx[in ? p + e : 0];         // (the matrix has an entry 0)
     }
+    // (the columns are on their way: other matrices need not wait for them)
+    if (__syncthreads_count(too_long) > 1 || entries == 0) {
+        if (threadIdx.x == 0) *answer = 0u;
+        return;
+    }
+    int npairs = kLookPairs + 1;
+    if (d >= kApartColumns) {
+        // the wave's rows against those it has looked at before: a table of columns (one that another column has replaced is not found again)
+        uint32_t *const seen = reinterpret_cast<uint32_t *>(owner);
+        constexpr int kSeen = kLookSlots / 4;
+#pragma unroll
+        for (int q = 0; q < kSeen / kWave; ++q) seen[q * kWave + lane] = 0;
+        uint32_t before[kMine];
+#pragma unroll
+        for (int g = 0; g < kMine; ++g) {
+            uint32_t *const slot = seen + ((real >> g) & 1u ? col[g] & (kSeen - 1) : (uint32_t)(kSeen + e));
+            asm volatile("" ::: "memory");      // (one wave's LDS accesses keep their order)
+            before[g] = *slot;
+            *slot = col[g] + 1u;
+        }
+        asm volatile("" ::: "memory");
+        npairs = 0;
+#pragma unroll
+        for (int g = 0; g < kMine; ++g) npairs += (int)__builtin_popcountll(__builtin_amdgcn_ballot_w64(((real >> g) & 1u) != 0 && before[g] == col[g] + 1u));
+    }
     uint32_t in_turn = 0, far = 0;            // a bit per group
+    int who[kMine];
+#pragma unroll
+    for (int g = 0; g < kMine; ++g) {
+        uint8_t *const slot = owner + ((real >> g) & 1u ? col[g] & (kLookSlots - 1) : (uint32_t)(kLookSlots + lane));
+        *slot = (uint8_t)lane;
+        asm volatile("" ::: "memory");          // the slot is read back after all lanes have written (one wave's LDS accesses keep their order)
+        who[g] = *slot;
+        asm volatile("" ::: "memory");
+    }
 #pragma unroll
     for (int g = 0; g < kMine; ++g) {
         const bool in = (real >> g) & 1u;
-        uint8_t *const slot = owner + (in ? col[g] & (kLookSlots - 1) : (uint32_t)(kLookSlots + lane));
-        *slot = (uint8_t)lane;
-        asm volatile("" ::: "memory");          // the slot is read back after all lanes have written (one wave's LDS accesses keep their order)
-        const int who = *slot;
-        asm volatile("" ::: "memory");
         // (the table is small: its owner's column is compared)
-        const bool shared = in & (who / kShortLen != r) & ((uint32_t)__shfl((int)col[g], who) == col[g]);
+        const bool shared = in & (who[g] / kShortLen != r) & ((uint32_t)__shfl((int)col[g], who[g]) == col[g]);
         if (__builtin_amdgcn_ballot_w64(shared) != 0) in_turn |= 1u << g;
         if (__builtin_amdgcn_ballot_w64(in & (col[g] >= (uint32_t)kPHead)) != 0) far |= 1u << g;
     }
-    const bool rows_are_short = __syncthreads_count(too_long) <= 1 && entries > 0;
-    const int nturn = __syncthreads_count(lane < kMine && (in_turn >> lane & 1u));
-    const int nfar = __syncthreads_count(lane < kMine && ((in_turn & far) >> lane & 1u));
-    if (threadIdx.x == 0) *answer = !rows_are_short || nfar > kLookMost ? 0u : (nturn > kLookMost ? kShortLongChains : kShortAlways);
+    __shared__ int found[kLookThreads / kWave][4];
+    if (lane == 0) {
+        found[wave][0] = npairs;
+        found[wave][1] = __builtin_popcount(in_turn);
+        found[wave][2] = __builtin_popcount(in_turn & far);
+    }
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    int pairs = 0, nturn = 0, nfar = 0;
+#pragma unroll
+    for (int w = 0; w < kLookThreads / kWave; ++w) {
+        pairs += found[w][0];
+        nturn += found[w][1];
+        nfar += found[w][2];
+    }
+    *answer = nfar > kLookMost ? 0u : pairs <= kLookPairs ? kShortApart : (nturn > kLookMost ? kShortLongChains : kShortAlways);
 }
 
 template <int LOSS, typename TV>
