@@ -487,9 +487,7 @@ struct SixteenSteps {
                     const double x = (double)__uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)w, who));
                     uint32_t bits = 0;       // bit 7 - R: this lane's entry of unit R of the two blocks has the column
 #pragma unroll
-                    for (int R = 0; R < 2 * kXUnits; ++R)
-                        asm("v_cmp_eq_u32 vcc, %2, %1\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc"
-                            : "+v"(bits) : "v"(off[R < kXUnits ? BEFORE : NOW][R % kXUnits]), "s"(place) : "vcc");
+                    for (int R = 0; R < 2 * kXUnits; ++R) bits = 2u * bits + (off[R < kXUnits ? BEFORE : NOW][R % kXUnits] == place ? 1u : 0u);
                     const uint64_t losers = at_lds<uint64_t>(lds, L::losers + (uint32_t)(r & 1) * (kXUnits * 8) + (uint32_t)unit * 8u);
                     const uint32_t here = 1u << (kXUnits - 1 - unit);
                     const uint64_t beside = __builtin_amdgcn_ballot_w64((bits & here) != 0);        // the unit's lanes with this column
