@@ -102,13 +102,13 @@ __device__ inline float state_load(__amdgpu_buffer_rsrc_t r, uint32_t off, float
 __device__ inline double drained_state_load(pu32x4 rsrc, uint32_t off, double)
 {
     double r;
-    asm volatile("s_waitcnt vmcnt(0)\n\tbuffer_load_dwordx2 %0, %1, %2, 0 offen sc1\n\ts_waitcnt vmcnt(0)" : "=v"(r) : "v"(off), "s"(rsrc) : "memory");
+    asm volatile("s_nop 3\n\ts_waitcnt vmcnt(0)\n\tbuffer_load_dwordx2 %0, %1, %2, 0 offen sc1\n\ts_waitcnt vmcnt(0)" : "=v"(r) : "v"(off), "s"(rsrc) : "memory");
     return r;
 }
 __device__ inline float drained_state_load(pu32x4 rsrc, uint32_t off, float)
 {
     float r;
-    asm volatile("s_waitcnt vmcnt(0)\n\tbuffer_load_dword %0, %1, %2, 0 offen sc1\n\ts_waitcnt vmcnt(0)" : "=v"(r) : "v"(off), "s"(rsrc) : "memory");
+    asm volatile("s_nop 3\n\ts_waitcnt vmcnt(0)\n\tbuffer_load_dword %0, %1, %2, 0 offen sc1\n\ts_waitcnt vmcnt(0)" : "=v"(r) : "v"(off), "s"(rsrc) : "memory");
     return r;
 }
 

@@ -524,9 +524,11 @@ struct LdsRows {
         const uint32_t row = ahead.get_stream(s < n ? s : n - 1);
         request_row(s, row, row);
     }
+    // (s_nop: a load to LDS wants a wait state behind the write of M0, and any memory access five behind a vector instruction that
+    // wrote one of its scalars; a descriptor that the compiler has spilled comes back by v_readlane)
     __device__ void request_row(int64_t s, uint32_t row, uint32_t record)
     {
-        asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dword %1, %2, 0 offen lds"
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tbuffer_load_dword %1, %2, 0 offen lds"
                      :
                      : "s"(labels0 + (uint32_t)(s % S) * (NW * kLabelBytes)), "v"(record * (uint32_t)(SIDE * 4) + side_lane), "s"(ry)
                      : "memory", "m0");
@@ -539,7 +541,7 @@ struct LdsRows {
         const uint32_t slot = slot0 + (uint32_t)(s % S) * kSlotBytes;
 #pragma unroll
         for (int c = 0; c < CHUNKS; ++c)
-            asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
                          :
                          : "s"(slot + c * (kWave * 16)), "v"(voff), "s"(rx), "s"(c * (NT * 16))
                          : "memory", "m0");
@@ -970,7 +972,7 @@ __global__ __launch_bounds__(kDelayThreads) void delay_server_batch_kernel(Delay
     typedef __attribute__((address_space(3))) uint32_t *lds_words;
     auto request_records = [&]() {
         const uint32_t pad = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(size_t)(lds_words)&others[0]);
-        asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dword %1, %2, 0 offen sc1 lds"
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tbuffer_load_dword %1, %2, 0 offen sc1 lds"
                      :
                      : "s"(pad), "v"((uint32_t)lane * 16u + 4u), "s"(rteam)
                      : "memory", "m0");

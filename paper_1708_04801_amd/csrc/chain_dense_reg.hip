@@ -224,13 +224,13 @@ __global__ __launch_bounds__(NT) void chain_dense_reg_kernel(ChainArgs a)
         // does not see that load, and nothing waits for it: memory operations of a wave complete
         // in order and at most 63 can be outstanding, so after the hundreds of row loads of one
         // window it has landed.  (A scalar load would be drained at every LDS wait, a per-step
-        // vector load costs a descriptor and an instruction per step.)
+        // vector load costs a descriptor and an instruction per step.)  (s_nop: the wait state that M0 wants in front of it.)
         typedef __attribute__((address_space(3))) float *lds_fptr;
         const uint32_t ylab_base = (uint32_t)(size_t)(lds_fptr)&ylab[0][0][0] + (uint32_t)wave * (2 * kWave * 4);
         auto request_labels = [&](int64_t w, uint32_t rows) {
             const float *py = a.y + rows;
             const uint32_t slot = (uint32_t)__builtin_amdgcn_readfirstlane((int)(ylab_base + (uint32_t)(w & 1) * (kWave * 4)));
-            asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, off" : : "s"(slot), "v"(py) : "memory", "m0");
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" : : "s"(slot), "v"(py) : "memory", "m0");
         };
         request_labels(0, rows_a);
         request_labels(1, rows_b);

@@ -226,7 +226,8 @@ __global__ __launch_bounds__(NT) void chain_dense_lds_kernel(ChainArgs a)
             (int)((uint32_t)(size_t)(lds_ptr)&stage[0][0][0] + (uint32_t)wave * (CHUNKS * kWave * 16)));
         auto request_chunk = [&](int c, u32x4 rx) {
             // the chunk's offset in the row rides in a scalar, so one vector register serves all chunks
-            asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+            // (s_nop: one wait state for M0, five for scalars that a vector instruction may have written)
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
                          :
                          : "s"(slot0 + c * (kWave * 16)), "v"(off0), "s"(rx), "s"(c * kChunkStride)
                          : "memory", "m0");

@@ -105,13 +105,14 @@ __device__ inline void slice_publish(uint32_t *slot, const uint32_t (&w)[kSliceM
         rec[0] = w[3 * q]; rec[1] = w[3 * q + 1]; rec[2] = w[3 * q + 2]; rec[3] = stamp;
         mirror[0] = stamp; mirror[1] = w[3 * q + 2]; mirror[2] = w[3 * q + 1]; mirror[3] = w[3 * q];
         uint32_t *at = slot + 64 * q;
+        // (s_nop: the registers of a store of 16 bytes may be written again one wait state behind it)
         if constexpr (NEAR) {
-            asm volatile("global_store_dwordx4 %0, %1, off\n\tglobal_store_dwordx4 %0, %2, off offset:128"
+            asm volatile("global_store_dwordx4 %0, %1, off\n\tglobal_store_dwordx4 %0, %2, off offset:128\n\ts_nop 0"
                          :
                          : "v"(at), "v"(rec), "v"(mirror)
                          : "memory");
         } else {
-            asm volatile("global_store_dwordx4 %0, %1, off sc1\n\tglobal_store_dwordx4 %0, %2, off offset:128 sc1"
+            asm volatile("global_store_dwordx4 %0, %1, off sc1\n\tglobal_store_dwordx4 %0, %2, off offset:128 sc1\n\ts_nop 0"
                          :
                          : "v"(at), "v"(rec), "v"(mirror)
                          : "memory");

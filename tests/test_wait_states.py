@@ -17,7 +17,7 @@ OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
 REG = re.compile(r"\b([sv])(\d+)\b|\b([sv])\[(\d+):(\d+)\]|\b(vcc|m0)")
 CARRY_OUT = re.compile(r"v_(add|sub|subrev)_co_u32|v_addc_co|v_subb(rev)?_co|v_mad_[ui]64|v_div_scale")
 TRANS = re.compile(r"v_(rcp|rsq|exp|log|sqrt|sin|cos)_")
-Instruction = collections.namedtuple("Instruction", "text kind writes reads dpp lane_read lane_select to_lds trans states ends")
+Instruction = collections.namedtuple("Instruction", "text kind writes reads dpp lane_read lane_select to_lds stored trans states ends")
 
 
 def _regs(operands):
@@ -51,14 +51,18 @@ def _parse(text):
     elif op.startswith("s_") and not op.startswith(("s_cmp", "s_bitcmp", "s_waitcnt", "s_nop", "s_barrier", "s_cbranch", "s_branch")):
         kind, writes, reads = "salu", _regs(ops[:1]), _regs(ops[1:])
     states = int(ops[0], 0) + 1 if op == "s_nop" else 1
+    # (stores of more than eight bytes: the address of a global store comes first, the data of a buffer store)
+    stored = _regs(ops[1:2] if op.startswith("global") else ops[:1]) if re.search(r"_store_dwordx[34]", op) else frozenset()
     lane_select = _regs(ops[2:3]) if op.startswith(("v_readlane", "v_writelane")) else frozenset()
     return Instruction(text, kind, writes, reads, _regs(ops[1:2]) if "_dpp" in op else frozenset(), op.startswith(("v_readlane", "v_readfirstlane")),
-                       lane_select, kind == "vmem" and ("_lds_" in op or rest.endswith(" lds")), bool(TRANS.match(op)), states,
+                       lane_select, kind == "vmem" and ("_lds_" in op or rest.endswith(" lds")), stored, bool(TRANS.match(op)), states,
                        op in ("s_branch", "s_endpgm", "s_setpc_b64"))
 
 
 def _needed(w, r):
     """wait states between the two, and what for"""
+    if w.stored:
+        return (1, "data of a store") if r.kind == "valu" and w.stored & r.writes else (0, "")
     if w.kind == "salu":
         return (1, "M0, then a load to LDS") if "m0" in w.writes and r.to_lds else (0, "")
     scalars = [x for x in w.writes if x[0] == "s" or x == "vcc"]
@@ -94,7 +98,7 @@ def short_of_waits(lines):
         if now.kind in ("valu", "vmem"):
             states = 0
             for before in reversed(window):
-                if before.kind in ("valu", "salu") and before.writes:
+                if before.writes or before.stored:
                     need, why = _needed(before, now)
                     if need > states:
                         found.append((function, why, need, states, before.text, now.text))
@@ -118,6 +122,8 @@ def short_of_waits(lines):
     ("v_add_f32_e32 v1, v2, v3\nv_add_f32_dpp v1, v1, v1 row_mirror row_mask:0xf bank_mask:0xf\n", 1),
     ("v_add_f32_dpp v1, v1, v1 row_mirror row_mask:0xf bank_mask:0xf\nv_readlane_b32 s0, v1, 63\n", 1),
     ("v_exp_f32_e32 v1, v1\nv_add_f32_e32 v1, 1.0, v1\n", 1),
+    ("global_store_dwordx4 v[0:1], v[4:7], off\nv_mov_b32_e32 v5, 0\n", 1),
+    ("global_store_dwordx4 v[0:1], v[4:7], off\ns_nop 0\nv_mov_b32_e32 v5, 0\n", 0),
     ("v_cmp_eq_u32_e32 vcc, s3, v15\ns_branch 7\nv_addc_co_u32_e32 v26, vcc, v26, v26, vcc\n", 0),
 ])
 def test_the_rules(listing, count):
@@ -144,7 +150,8 @@ def found(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("why", ["scalar register, then vector instruction", "lane select", "v_div_fmas", "DPP operand", "lane read", "transcendental result"])
+@pytest.mark.parametrize("why", ["scalar register, then vector instruction", "lane select", "v_div_fmas", "DPP operand", "lane read", "transcendental result",
+                                 "M0, then a load to LDS", "scalar register, then memory", "data of a store"])
 def test_no_kernel_is_short_of_wait_states(found, why):
     short = [f for f in found if f[1] == why]
     assert not short, f"{len(short)}, such as:\n" + "\n".join(map(str, short[:20]))
