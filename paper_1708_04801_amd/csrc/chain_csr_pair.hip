@@ -103,28 +103,29 @@ __device__ inline void wait_lds_then_barrier()
 // Memory instructions the compiler does not see; each drains the queue, so the value is there (or
 // the store is done) when the statement ends.  Used off the fast path only, so that the compiler's
 // count of outstanding loads, and with it the partial waits of the fast path, is the same whether
-// or not the slow path ran.  (s_nop: five wait states for a descriptor that a vector instruction may have written.)
+// or not the slow path ran.  (A descriptor fresh out of a spill would want five wait states in front of them.  None is, which a
+// test reads from the built library: an s_nop in each costs chains that read many values again half a per cent.)
 __device__ inline double drained_buffer_load(pu32x4 rsrc, uint32_t off, double)
 {
     double r;
-    asm volatile("s_nop 3\n\ts_waitcnt vmcnt(0)\n\tbuffer_load_dwordx2 %0, %1, %2, 0 offen\n\ts_waitcnt vmcnt(0)"
+    asm volatile("s_waitcnt vmcnt(0)\n\tbuffer_load_dwordx2 %0, %1, %2, 0 offen\n\ts_waitcnt vmcnt(0)"
                  : "=v"(r) : "v"(off), "s"(rsrc) : "memory");
     return r;
 }
 __device__ inline float drained_buffer_load(pu32x4 rsrc, uint32_t off, float)
 {
     float r;
-    asm volatile("s_nop 3\n\ts_waitcnt vmcnt(0)\n\tbuffer_load_dword %0, %1, %2, 0 offen\n\ts_waitcnt vmcnt(0)"
+    asm volatile("s_waitcnt vmcnt(0)\n\tbuffer_load_dword %0, %1, %2, 0 offen\n\ts_waitcnt vmcnt(0)"
                  : "=v"(r) : "v"(off), "s"(rsrc) : "memory");
     return r;
 }
 __device__ inline void drained_buffer_store(pu32x4 rsrc, uint32_t off, double x)
 {
-    asm volatile("s_nop 4\n\tbuffer_store_dwordx2 %0, %1, %2, 0 offen\n\ts_waitcnt vmcnt(0)" : : "v"(x), "v"(off), "s"(rsrc) : "memory");
+    asm volatile("buffer_store_dwordx2 %0, %1, %2, 0 offen\n\ts_waitcnt vmcnt(0)" : : "v"(x), "v"(off), "s"(rsrc) : "memory");
 }
 __device__ inline void drained_buffer_store(pu32x4 rsrc, uint32_t off, float x)
 {
-    asm volatile("s_nop 4\n\tbuffer_store_dword %0, %1, %2, 0 offen\n\ts_waitcnt vmcnt(0)" : : "v"(x), "v"(off), "s"(rsrc) : "memory");
+    asm volatile("buffer_store_dword %0, %1, %2, 0 offen\n\ts_waitcnt vmcnt(0)" : : "v"(x), "v"(off), "s"(rsrc) : "memory");
 }
 __device__ inline uint32_t drained_global_load_u32(const void *p)
 {
