@@ -36,7 +36,7 @@
 // judge for themselves (430), blocks of 32 steps (twice the pairs and the stamps), sums unit by unit in four registers instead of folded into
 // one, scalars read in the block's own turn.
 // Precision: products, sums and slopes' arguments in fp64 for either loss, updates one rounding to the state's type.  Error of a logistic chain of
-// 10000 steps against fp64, groups of four | this way: d = 60000 6.97e-8 | 6.48e-8, 100000 6.83e-8 | 6.29e-8, a million 4.99e-8 | 4.75e-8; hinge the same in all digits.
+// 10000 steps against fp64, groups of four | this way: d = 60000 6.97e-8 | 6.48e-8, 100000 6.83e-8 | 6.29e-8, a million 4.99e-8 | 4.75e-8; hinge the same.
 #pragma once
 
 namespace wpsgd {
@@ -531,10 +531,9 @@ __device__ inline void run_sixteen(const ChainArgs &a, char *lds, typename State
     else waves.pairs();
 }
 
-// (waves_per_eu: with the default, which aims at the most waves the workgroup's size allows, the same code is scheduled for fewer registers and takes
-// 4.64 ms instead of 4.06.  A kernel of its own, and not a branch of chain_csr_pair_kernel: there it cost the other chains 0.8 %.)
+// (A kernel of its own, and not a branch of chain_csr_pair_kernel: there it cost the other chains 0.8 %.)
 template <int LOSS>
-__global__ __launch_bounds__(kXThreads) __attribute__((amdgpu_waves_per_eu(1, 2))) void chain_csr_sixteen_kernel(ChainArgs a)
+__global__ __launch_bounds__(kXThreads) void chain_csr_sixteen_kernel(ChainArgs a)
 {
     using TV = typename StateType<LOSS>::type;
     __shared__ __attribute__((aligned(16))) char lds[XLds::bytes];
