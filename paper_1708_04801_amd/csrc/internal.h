@@ -50,7 +50,8 @@ struct ChainArgs {
     uint32_t slice_max_polls; // how often a slice polls for the others' sums before it gives up (a poll takes
                               // 600 to 1200 cycles); 0: it does not poll at all
     uint32_t *status;         // DEVICE, first word of the workspace: bit 0 is set by a slice that gave up; the word behind it:
-                              // whether the sparse chains run four steps at a time (chain_csr_short.h)
+                              // how the sparse chains run: 0 one step at a time, 1 and 2 four (all chains, long ones: chain_csr_short.h),
+                              // 3 sixteen (chain_csr_sixteen.h; the pair kernel leaves these chains alone); shorter ones one at a time
     // outputs / scratch
     float *W;                 // k x d
     void *state;              // k x d model vectors in HBM (state_in_hbm plans), else unused
