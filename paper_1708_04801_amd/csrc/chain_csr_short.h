@@ -67,12 +67,14 @@ struct ShortLds {
 //   column that all rows share, such as a constant term, at d = 100000: 0.22 one at a time, 0.46 in groups).  The second
 //   has to earn back the start of the scouts' deeper pipeline.
 //   Rows far apart: among the 48 rows that a wave looks at, entries that find their column with one looked at before are counted.  Sixteen steps
-//   at a time (chain_csr_sixteen.h) pay for each such pair where groups of four hardly notice one.  us, four at a time | sixteen, ten
-//   chains of 10000 steps, hinge, 5 to 10 uniform columns (the count expected): d = 15000 (13) 669 | 826, 30000 (7) 660 | 650, 40000 (5) 652 | 608, 100000 (2)
-//   634 | 514, a million (0) 631 | 437; ten chains of 200 steps, d = 100000 61 | 50.
+//   at a time (chain_csr_sixteen.h) read some values again for each such pair, where groups of four hardly notice one.  us, four at a time | sixteen, ten
+//   chains of 10000 steps, hinge, uniform columns (the count expected): 5 to 10 entries, d = 10000 (20) 641 | 657, 15000 (13) 633 | 597, 30000 (7)
+//   632 | 493, 100000 (2) 620 | 400; 12 to 16 entries, d = 15000 (45) 1014 | 953, 60000 (14) 938 | 615; 2 or 3 entries, d = 2000 (11) 523 | 536, 5000 (5)
+//   514 | 436.  Rows that come back are not counted: with 1000 rows of 5 to 10 entries 636 | 441, with 200 802 | 605; fewer show as pairs.
 constexpr uint32_t kShortAlways = 1, kShortLongChains = 2, kShortApart = 3;       // answers, in the word behind the status word
-constexpr int kLookPairs = 5;
-// With fewer columns rows of this length meet too often, and calls do without the count and the launch (2 us of a call of 200 steps).
+constexpr int kLookPairs = 16;
+// Calls with fewer columns do without the count and the launch, 2 us of a call whose matrix is refused (200 steps, 5 to 10 entries, d = 100000: 49 one way,
+// 37 the other).  Rows of 5 to 10 entries are near the line there; ones of two or three would gain down to d = 3000.
 constexpr int64_t kApartColumns = 24576;
 constexpr int kLookThreads = 256, kLookEach = 3, kLookGroups = 48, kLookMost = 19, kLookSlots = 4096;
 // Chains of less than 128 steps do not earn back that start (8 steps of rows without a shared column: 24 us one at a

@@ -86,6 +86,21 @@ def test_rows_that_come_back(m, loss):
 
 
 @BOTH
+@pytest.mark.parametrize("d,length", [(26000, None), (60000, 14), (120000, 16)])
+def test_rows_that_often_share_a_column(d, length, loss):
+    """Near the line behind which such matrices run four steps at a time: one block in two reads again, one in three has a step in turn."""
+    m, n = 20000, [900, 131, 2500, 400]
+    ptr, cols, vals, y = _matrix(m, d, 11)
+    if length:
+        rng = np.random.default_rng(12)
+        cols = np.concatenate([np.sort(rng.choice(d, length, replace=False)) for _ in range(m)]).astype(np.int32)
+        ptr, vals = np.arange(m + 1, dtype=np.int64) * length, (rng.standard_normal(m * length) / 4).astype(np.float32)
+    W = _run(*_upload(m, d, ptr, cols, vals, y), n, 0.3, 1e-4, loss).cpu().numpy()
+    ref = orc.run_chains(orc.CSR(ptr, cols, vals, d), y, np.array(n, dtype=np.int64), 0.3, 1e-4, loss, SEED, csr_mode=1)[0]
+    _close(W, ref, n, loss)
+
+
+@BOTH
 @pytest.mark.parametrize("length", [17, 63, 64, 65, 128, 129])
 @pytest.mark.parametrize("places", [(0,), (15,), (0, 1), (14, 15, 16, 17), (3, 9, 18, 40), tuple(range(32, 64))])
 def test_long_rows_in_every_place_of_a_block(places, length, loss):
