@@ -460,8 +460,8 @@ __global__ __launch_bounds__(kDelayThreads) void delay_server_reg_kernel(DelayAr
 }
 
 // Rows on their way from HBM into LDS.  A ring of S row slots (sample s in slot s mod S), filled by loads
-// that land in LDS directly and need no registers while in flight; behind the slots, S pads that
-// receive, the same way, a small record per sample: SIDE dwords from an array indexed by the sample's
+// that land in LDS directly and need no registers while in flight; in front of each wave's part of a slot, a pad that
+// receives, the same way, a small record per sample: SIDE dwords from an array indexed by the sample's
 // row (SIDE = 1: its label; SIDE = 8: its entry of the row table, see DelayRowEntry).  Every wave requests, and later reads back, only its own
 // part of a row (the columns its lanes own), so the slots need no barrier.  The compiler does not see
 // these loads; a wave's loads complete in issue order, so waiting until at most (S - B) samples' worth of
@@ -477,15 +477,15 @@ struct LdsRows {
     static_assert(VEC * sizeof(TX) == 16, "16-byte loads only");
     static constexpr int CHUNKS = EPT / VEC;
     static_assert(Frag::kWords == 4 * CHUNKS, "four words per chunk");
-    static constexpr uint32_t kWaveBytes = CHUNKS * kWave * 16;          // what one wave holds of one row
+    static constexpr uint32_t kPadBytes = kWave * 4;                     // a wave's copy of one record (64 / SIDE times)
+    static constexpr uint32_t kWaveBytes = kPadBytes + CHUNKS * kWave * 16;      // and what it holds of one row, behind it
     static constexpr uint32_t kSlotBytes = NW * kWaveBytes;
-    static constexpr uint32_t kLabelBytes = kWave * 4;                   // a wave's copy of one record (64 / SIDE times)
     static constexpr int kLoadsPerSample = CHUNKS + 1;                   // the row's chunks and its record
-    static constexpr size_t kBytes = (size_t)S * (kSlotBytes + NW * kLabelBytes);
+    static constexpr size_t kBytes = (size_t)S * kSlotBytes;
     typedef __attribute__((address_space(3))) uint32_t *lds_words;
 
-    lds_words stage;            // S slots, then S x NW record pads
-    uint32_t slot0, labels0;    // LDS byte addresses of this wave's part of slot 0 and of its pad 0
+    lds_words stage;            // S slots
+    uint32_t slot0;             // LDS byte address of this wave's part of slot 0
     uint32_t voff, lane, wave, side_lane;
     u32x4 ry;                   // the records as a buffer
     const char *X;
@@ -502,7 +502,6 @@ struct LdsRows {
         lane = (uint32_t)(tid & (kWave - 1));
         wave = (uint32_t)__builtin_amdgcn_readfirstlane(tid / kWave);
         slot0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint32_t)(size_t)lds + wave * kWaveBytes));
-        labels0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint32_t)(size_t)lds + (uint32_t)S * kSlotBytes + wave * kLabelBytes));
         voff = (uint32_t)(tid * 16);                 // this lane's bytes of chunk 0; chunk c adds c*NT*16
         const uint64_t ybase = (uint64_t)(uintptr_t)records;
         ry[0] = (uint32_t)ybase;
@@ -524,27 +523,39 @@ struct LdsRows {
         const uint32_t row = ahead.get_stream(s < n ? s : n - 1);
         request_row(s, row, row);
     }
-    // (s_nop: a load to LDS wants a wait state behind the write of M0, and any memory access five behind a vector instruction that
-    // wrote one of its scalars; a descriptor that the compiler has spilled comes back by v_readlane)
+    // One statement that writes M0 once: an instruction's offset moves the place in LDS and the place in memory alike, so the row's first chunk
+    // takes kPadBytes of it, which its descriptor starts early, and chunk c another c KiB, with the rest of its way through memory from a scalar.
+    // (s_nop: the wait state that a load to LDS wants behind the write of M0.  A scalar that a vector instruction wrote, as a descriptor that the compiler
+    // has spilled is, wants five; none comes that late, which a test reads from the built library.)  us, 128 servers of up to 8000 samples, tau = 2, without
+    // Check, a write of M0 and four wait states for each load -> this: d = 4096 fp32 3420 -> 3265, bf16 3480 -> 3225; d = 2048 2675 -> 2490 and
+    // 2440 -> 2365; under Check 2490 -> 2490, 1930 -> 1850, 1645 -> 1540 and 1500 -> 1440.
     __device__ void request_row(int64_t s, uint32_t row, uint32_t record)
     {
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tbuffer_load_dword %1, %2, 0 offen lds"
-                     :
-                     : "s"(labels0 + (uint32_t)(s % S) * (NW * kLabelBytes)), "v"(record * (uint32_t)(SIDE * 4) + side_lane), "s"(ry)
-                     : "memory", "m0");
-        const uint64_t base = (uint64_t)(uintptr_t)(X + (int64_t)row * row_stride);
+        const uint64_t base = (uint64_t)(uintptr_t)(X + (int64_t)row * row_stride) - kPadBytes;
         u32x4 rx;
         rx[0] = (uint32_t)base;
         rx[1] = (uint32_t)(base >> 32) & 0xffffu;
-        rx[2] = row_bytes;
+        rx[2] = row_bytes + kPadBytes;
         rx[3] = 0x00020000u;
-        const uint32_t slot = slot0 + (uint32_t)(s % S) * kSlotBytes;
-#pragma unroll
-        for (int c = 0; c < CHUNKS; ++c)
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+        constexpr uint32_t kRest = NT * 16 - kWave * 16;
+        static_assert(kPadBytes == 256 && kWave * 16 == 1024 && (CHUNKS == 1 || CHUNKS == 2 || CHUNKS == 4), "the offsets below");
+        const uint32_t slot = slot0 + (uint32_t)(s % S) * kSlotBytes, at = record * (uint32_t)(SIDE * 4) + side_lane;
+#define WPSGD_RECORD_AND_CHUNK                                                                                                    \
+    "s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds\n\tbuffer_load_dwordx4 %3, %4, 0 offen offset:256 lds"
+        if constexpr (CHUNKS == 1)
+            asm volatile(WPSGD_RECORD_AND_CHUNK : : "s"(slot), "v"(at), "s"(ry), "v"(voff), "s"(rx) : "memory", "m0");
+        else if constexpr (CHUNKS == 2)
+            asm volatile(WPSGD_RECORD_AND_CHUNK "\n\tbuffer_load_dwordx4 %3, %4, %5 offen offset:1280 lds"
                          :
-                         : "s"(slot + c * (kWave * 16)), "v"(voff), "s"(rx), "s"(c * (NT * 16))
+                         : "s"(slot), "v"(at), "s"(ry), "v"(voff), "s"(rx), "s"(kRest)
                          : "memory", "m0");
+        else
+            asm volatile(WPSGD_RECORD_AND_CHUNK "\n\tbuffer_load_dwordx4 %3, %4, %5 offen offset:1280 lds\n\t"
+                                                "buffer_load_dwordx4 %3, %4, %6 offen offset:2304 lds\n\tbuffer_load_dwordx4 %3, %4, %7 offen offset:3328 lds"
+                         :
+                         : "s"(slot), "v"(at), "s"(ry), "v"(voff), "s"(rx), "s"(kRest), "s"(2 * kRest), "s"(3 * kRest)
+                         : "memory", "m0");
+#undef WPSGD_RECORD_AND_CHUNK
     }
     // waits until the B oldest of the S samples requested last have landed
     // (gfx9 encoding: vmcnt split over bits 3:0 and 15:14; expcnt and lgkmcnt left open)
@@ -559,7 +570,7 @@ struct LdsRows {
     // this thread's elements of the row of sample s
     __device__ void take(int64_t s, Frag &x) const
     {
-        const lds_words src = stage + (size_t)(s % S) * (kSlotBytes / 4) + (size_t)wave * (kWaveBytes / 4) + lane * 4;
+        const lds_words src = stage + (size_t)(s % S) * (kSlotBytes / 4) + (size_t)wave * (kWaveBytes / 4) + kPadBytes / 4 + lane * 4;
         typedef __attribute__((address_space(3))) const u32x4 *lds_quads;
 #pragma unroll
         for (int c = 0; c < CHUNKS; ++c) {
@@ -573,7 +584,7 @@ struct LdsRows {
     // dword j of sample s's record (the same address in every lane)
     __device__ uint32_t side(int64_t s, int j) const
     {
-        return stage[(size_t)S * (kSlotBytes / 4) + (size_t)(s % S) * (NW * kLabelBytes / 4) + (size_t)wave * (kLabelBytes / 4) + j];
+        return stage[(size_t)(s % S) * (kSlotBytes / 4) + (size_t)wave * (kWaveBytes / 4) + j];
     }
     __device__ double side_f64(int64_t s, int j) const
     {

@@ -83,31 +83,52 @@ def _needed(w, r):
     return 0, ""
 
 
-def short_of_waits(lines):
-    """[(function, what for, needed, there, writer, reader)] of a disassembly"""
-    found, function, window = [], "?", collections.deque(maxlen=5)
+def _functions(lines):
+    """(name, instructions, which one a branch goes to) of a disassembly"""
+    name, base, code, places, targets = "?", 0, [], {}, {}
+
+    def done():
+        return name, code, {i: places[at] for i, at in targets.items() if at in places}
+
     for line in lines:
         if line.endswith(">:\n"):
-            function = line[line.index("<") + 1:-3]
-            window.clear()
+            yield done()
+            name, base, code, places, targets = line[line.index("<") + 1:-3], int(line.split()[0], 16), [], {}, {}
             continue
-        text = line.partition("//")[0].strip()
+        text, _, comment = line.partition("//")
+        text = text.strip()
         if not text or text[0] not in "vsdbgf" or "_" not in text:
             continue
-        now = _parse(" ".join(text.split()))
-        if now.kind in ("valu", "vmem"):
-            states = 0
-            for before in reversed(window):
-                if before.writes or before.stored:
-                    need, why = _needed(before, now)
-                    if need > states:
-                        found.append((function, why, need, states, before.text, now.text))
-                states += before.states
-                if states >= 5:
-                    break
-        window.append(now)
-        if now.ends:
-            window.clear()
+        if comment:
+            places[int(comment.split(":")[0], 16)] = len(code)
+        if "branch" in text and "+0x" in comment:
+            targets[len(code)] = base + int(comment[comment.rindex("+0x") + 1:comment.rindex(">")], 16)
+        code.append(_parse(" ".join(text.split())))
+    yield done()
+
+
+def short_of_waits(lines):
+    """[(function, what for, needed, there, writer, reader)] of a disassembly, on every way from the one to the other"""
+    found = []
+    for function, code, targets in _functions(lines):
+        for i, before in enumerate(code):
+            if not before.writes and not before.stored:
+                continue
+            ways = [(i + 1, 0)]
+            while ways:
+                j, states = ways.pop()
+                while j < len(code) and states < 5:
+                    now = code[j]
+                    if now.kind in ("valu", "vmem"):
+                        need, why = _needed(before, now)
+                        if need > states:
+                            found.append((function, why, need, states, before.text, now.text))
+                    states += now.states
+                    if j in targets:
+                        ways.append((targets[j], states))
+                    if now.ends:
+                        break
+                    j += 1
     return found
 
 
@@ -125,6 +146,10 @@ def short_of_waits(lines):
     ("global_store_dwordx4 v[0:1], v[4:7], off\nv_mov_b32_e32 v5, 0\n", 1),
     ("global_store_dwordx4 v[0:1], v[4:7], off\ns_nop 0\nv_mov_b32_e32 v5, 0\n", 0),
     ("v_cmp_eq_u32_e32 vcc, s3, v15\ns_branch 7\nv_addc_co_u32_e32 v26, vcc, v26, v26, vcc\n", 0),
+    ("0000000000000100 <f>:\nv_addc_co_u32_e32 v26, s[0:1], v26, v26, vcc // 000000000100: 00\nv_cmp_eq_u32_e32 vcc, s3, v15 // 000000000104: 00\n"
+     "s_cbranch_scc1 65533 // 000000000108: 00 <f+0x0>\ns_endpgm // 00000000010C: 00\n", 1),
+    ("0000000000000100 <f>:\ns_nop 0 // 000000000100: 00\nv_addc_co_u32_e32 v26, s[0:1], v26, v26, vcc // 000000000104: 00\n"
+     "v_cmp_eq_u32_e32 vcc, s3, v15 // 000000000108: 00\ns_cbranch_scc1 65533 // 00000000010C: 00 <f+0x0>\ns_endpgm // 000000000110: 00\n", 0),
 ])
 def test_the_rules(listing, count):
     assert len(short_of_waits(listing.splitlines(keepends=True))) == count
