@@ -130,11 +130,11 @@ static int resolve_plan(const wpsgd_matrix *X, int k, wpsgd_loss loss, const wps
         p.block_steps = 1;
         // The LDS-cached kernels (prefetch 4: one wave per chain, 8: three) never fold their lazy scale
         // back into the vector, so they need (1-eta*lambda)^steps to stay well inside fp32 range.
-        // They park unused lanes on scratch columns at the start of the vector, and the two-wave
-        // kernel addresses the vector with 32-bit byte offsets.
+        // They park unused lanes on scratch columns at the start of the vector, and the kernels of more waves
+        // address the vector with 32-bit byte offsets, of which 0xFFFFFFF0 stands for no access: it may not lie inside the vector.
         const bool no_fold = (double)max_steps * std::log(rho) > -55.0;       // scale > 2^-80
         const bool cached_ok = X->d >= 64 && no_fold;
-        const bool pair_ok = X->d >= 128 && no_fold && (uint64_t)X->d * state_elem < (1ull << 32);
+        const bool pair_ok = X->d >= 128 && no_fold && (uint64_t)X->d * state_elem <= 0xFFFFFFF0ull;
         if (f.prefetch == 4 && !cached_ok) return WPSGD_UNSUPPORTED;
         if (f.prefetch == 8 && !pair_ok) return WPSGD_UNSUPPORTED;
         p.prefetch = f.prefetch ? f.prefetch : (pair_ok ? 8 : (cached_ok ? 4 : 1));

@@ -164,6 +164,17 @@ def test_planner_picks_registers_when_the_vector_fits_and_hbm_otherwise():
         assert err.value.status == api.INVALID_ARG
 
 
+@pytest.mark.parametrize("loss,most", [(api.HINGE, 0xFFFFFFF0 // 8), (api.LOGISTIC, 0xFFFFFFF0 // 4)])
+def test_an_offset_that_means_no_access_is_outside_the_vector(loss, most):
+    """The three-wave sparse kernels take 0xFFFFFFF0 for no access: longer vectors go to the kernel with one wave."""
+    d = api.wpsgd_describe_plan
+    assert d(_FakeMatrix(100, most, csr=True), 1, loss) == d(_FakeMatrix(100, most, csr=True), 1, loss, plan={"prefetch": 8})
+    for cols in (most + 1, most | 3, most + 100):                        # (most | 3: the last vector below 4 GiB)
+        assert d(_FakeMatrix(100, cols, csr=True), 1, loss) == d(_FakeMatrix(100, cols, csr=True), 1, loss, plan={"prefetch": 4})
+        with pytest.raises(api.WpsgdError):
+            d(_FakeMatrix(100, cols, csr=True), 1, loss, plan={"prefetch": 8})
+
+
 def test_a_forced_plan_names_one_kernel():
     d = api.wpsgd_describe_plan
     for loss in (api.HINGE, api.LOGISTIC):
