@@ -488,7 +488,7 @@ struct LdsRows {
     uint32_t slot0;             // LDS byte address of this wave's part of slot 0
     uint32_t voff, lane, wave, side_lane;
     u32x4 ry;                   // the records as a buffer
-    const char *X;
+    const char *X;              // kPadBytes in front of the rows
     int64_t row_stride, n;
     uint32_t row_bytes;
     RowWindow ahead;
@@ -509,7 +509,7 @@ struct LdsRows {
         ry[2] = (uint32_t)(SIDE > 1 && a.visits ? a.visits : a.m) * (uint32_t)(SIDE * 4);
         ry[3] = 0x00020000u;
         side_lane = (lane & (uint32_t)(SIDE - 1)) * 4u;
-        X = static_cast<const char *>(a.dense);
+        X = static_cast<const char *>(a.dense) - kPadBytes;
         row_stride = a.ld * (int64_t)sizeof(TX);
         row_bytes = (uint32_t)a.d * (uint32_t)sizeof(TX);
         n = samples;
@@ -524,14 +524,14 @@ struct LdsRows {
         request_row(s, row, row);
     }
     // One statement that writes M0 once: an instruction's offset moves the place in LDS and the place in memory alike, so the row's first chunk
-    // takes kPadBytes of it, which its descriptor starts early, and chunk c another c KiB, with the rest of its way through memory from a scalar.
+    // takes kPadBytes of it, which its descriptor starts early (X does), and chunk c another c KiB, with the rest of its way through memory from a scalar.
     // (s_nop: the wait state that a load to LDS wants behind the write of M0.  A scalar that a vector instruction wrote, as a descriptor that the compiler
     // has spilled is, wants five; none comes that late, which a test reads from the built library.)  us, 128 servers of up to 8000 samples, tau = 2, without
-    // Check, a write of M0 and four wait states for each load -> this: d = 4096 fp32 3420 -> 3265, bf16 3480 -> 3225; d = 2048 2675 -> 2490 and
-    // 2440 -> 2365; under Check 2490 -> 2490, 1930 -> 1850, 1645 -> 1540 and 1500 -> 1440.
+    // Check, a write of M0 and four wait states for each load -> this: d = 4096 fp32 3420 -> 3250, bf16 3480 -> 3230; d = 2048 2675 -> 2470 and
+    // 2440 -> 2365; under Check 2490 -> 2480, 1930 -> 1840, 1645 -> 1525 and 1500 -> 1405.
     __device__ void request_row(int64_t s, uint32_t row, uint32_t record)
     {
-        const uint64_t base = (uint64_t)(uintptr_t)(X + (int64_t)row * row_stride) - kPadBytes;
+        const uint64_t base = (uint64_t)(uintptr_t)(X + (int64_t)row * row_stride);
         u32x4 rx;
         rx[0] = (uint32_t)base;
         rx[1] = (uint32_t)(base >> 32) & 0xffffu;
